@@ -120,7 +120,8 @@ struct BatchArgs {
     int kmax;      // paired body: most copies an item has
 };
 
-// ND = 0: byte-parallel body; DK > 0: every image has exactly DK records per site.
+// ND = 0: byte-parallel body, else the general body with ND digits; DK > 0: every image
+// has exactly DK records per site.
 template <int ND, int DK = 0>
 __global__ __launch_bounds__(1024) void batch_sa_kernel(BatchArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -168,10 +169,10 @@ __global__ __launch_bounds__(1024) void batch_sa_kernel(BatchArgs a) {
             core::swar_run<DK, 1>(L, it, cs);
         } else {
             if (b != loaded) {
-                core::sa_load_instance(L, it, cs);
+                core::sa_load_instance<DK>(L, it, cs);
                 loaded = b;
             }
-            core::sa_run<ND>(L, it, cs);
+            core::sa_run<ND, false, DK>(L, it, cs);
         }
     }
 }
@@ -282,15 +283,19 @@ hipError_t launch_batch_sa(const BatchLaunch &L, hipStream_t s) {
             else
                 hipLaunchKernelGGL(batch_sa_kernel<0>, dim3(L.grid), dim3(L.threads), lds, s, a);
             break;
+#define SPV_GEN(ND_)                                                                                              \
+    if (L.dk == kSiteRecs)                                                                                  \
+        hipLaunchKernelGGL((batch_sa_kernel<ND_, kSiteRecs>), dim3(L.grid), dim3(L.threads), lds, s, a);    \
+    else                                                                                                          \
+        hipLaunchKernelGGL((batch_sa_kernel<ND_>), dim3(L.grid), dim3(L.threads), lds, s, a);                     \
+    break
         case 1:
-            hipLaunchKernelGGL(batch_sa_kernel<1>, dim3(L.grid), dim3(L.threads), lds, s, a);
-            break;
+            SPV_GEN(1);
         case 2:
-            hipLaunchKernelGGL(batch_sa_kernel<2>, dim3(L.grid), dim3(L.threads), lds, s, a);
-            break;
+            SPV_GEN(2);
         case 3:
-            hipLaunchKernelGGL(batch_sa_kernel<3>, dim3(L.grid), dim3(L.threads), lds, s, a);
-            break;
+            SPV_GEN(3);
+#undef SPV_GEN
         default:
             return hipErrorInvalidValue;
     }

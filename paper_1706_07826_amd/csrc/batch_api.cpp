@@ -289,8 +289,9 @@ spv_status sample_batch_inst(spv_ctx *ctx, int32_t B, const Inst *problems, cons
     if (pl.nd > 3) return set_err(c, SPV_ERANGE, "x_bound=%d needs %d digits (max 3)", x_max, pl.nd);
     pl.row_len = table_row_len(x_max);
     // The byte-parallel body has straight-line variants for 4, 6 and 8 records per
-    // site: pad every image of the batch to the largest degree (zero-coupling records).
-    if (sa_use_swar(pl.nd, pl.row_len) && (pl.D_max == 4 || pl.D_max == 6 || pl.D_max == 8)) {
+    // site, the general body for kSiteRecs: pad every image of the batch to the largest degree (zero-coupling records).
+    const bool swar = sa_use_swar(pl.nd, pl.row_len);
+    if (swar ? (pl.D_max == 4 || pl.D_max == 6 || pl.D_max == 8) : pl.D_max == kSiteRecs) {
         pl.dk = pl.D_max;
         pl.image_words = 0;
         for (int b = 0; b < B; ++b) {
@@ -308,7 +309,7 @@ spv_status sample_batch_inst(spv_ctx *ctx, int32_t B, const Inst *problems, cons
     // Shape: explicit, tuned, or default.  The paired body serves batches whose images
     // have 4, 6 or 8 records per site on the byte-parallel path.
     const uint32_t flags = opts ? opts->flags : 0u;
-    const bool paired_ok = pl.dk == 4 || pl.dk == 6 || pl.dk == 8;
+    const bool paired_ok = swar && (pl.dk == 4 || pl.dk == 6 || pl.dk == 8);
     const size_t lds_cu = c->lds_max;  // LDS of one CU (the largest workgroup allocation)
     Shape sh{256, 2, 4};
     if (paired_ok) sh = Shape{1024, 2, 1, true};

@@ -49,6 +49,9 @@ constexpr int kIngestStructure = 2;
 //   uint32 nbr[n*D]   ELL neighbour records by position: (pos_j << 16) | (uint16)J_ij,
 //                     padded with (p << 16) | 0 (self, zero coupling)
 constexpr int kImgHeader = 32;
+// Records per site (cubes, Chimera graphs) the general sampler bodies have straight-line
+// variants and LDS site blocks for.
+constexpr int kSiteRecs = 6;
 
 inline size_t image_words(int n, int D) { return (size_t)kImgHeader + 3ull * n + (size_t)n * D; }
 

@@ -109,7 +109,7 @@ __global__ __launch_bounds__(256) void prep_nbr_kernel(const int32_t *__restrict
     hpos[p] = h[i];
 }
 
-// ND = number of threshold digits; ND = 0 selects the byte-parallel path, whose
+// ND = number of threshold digits; ND = 0 selects the byte-parallel path.  The
 // neighbour loop is straight-line code for a record count DK (0: any).
 // BIG: the instance lives in global memory, LDS holds the tables and the spins.
 // The byte-parallel body reads its own records from a.big (built beforehand by
@@ -137,12 +137,12 @@ __global__ __launch_bounds__(1024) void sa_kernel(core::SaItem a) {
         core::SaLds L;
         core::sa_big_layout(a.n, a.row_len, a.qw, &L, smem);
         core::sa_bind_image(&L, a, cs);
-        core::sa_run<ND, true>(L, a, cs);
+        core::sa_run<ND, true, DK>(L, a, cs);
     } else {
         core::SaLds L;
         core::sa_layout(a.n, a.D, a.row_len, a.qw, &L, smem);
-        core::sa_load_instance(L, a, cs);
-        core::sa_run<ND>(L, a, cs);
+        core::sa_load_instance<DK>(L, a, cs);
+        core::sa_run<ND, false, DK>(L, a, cs);
     }
 }
 
@@ -386,16 +386,23 @@ hipError_t launch_sa(const SaLaunch &L, hipStream_t s, size_t lds_limit) {
     if (lds > lds_limit || (big && swar && L.big == nullptr)) return hipErrorInvalidValue;
     const int quads = (L.reads + 3) / 4;
     const int grid = (quads + L.qw - 1) / L.qw;
+#define SPV_GEN(ND_, BIG_)                                                                                    \
+    do {                                                                                                      \
+        if (L.D == 6)                                                                                         \
+            hipLaunchKernelGGL((sa_kernel<ND_, 6, BIG_>), dim3(grid), dim3(L.threads), lds, s, a);            \
+        else                                                                                                  \
+            hipLaunchKernelGGL((sa_kernel<ND_, 0, BIG_>), dim3(grid), dim3(L.threads), lds, s, a);            \
+    } while (0)
     if (big && !swar) {
         switch (L.nd) {
             case 1:
-                hipLaunchKernelGGL((sa_kernel<1, 0, true>), dim3(grid), dim3(L.threads), lds, s, a);
+                SPV_GEN(1, true);
                 break;
             case 2:
-                hipLaunchKernelGGL((sa_kernel<2, 0, true>), dim3(grid), dim3(L.threads), lds, s, a);
+                SPV_GEN(2, true);
                 break;
             case 3:
-                hipLaunchKernelGGL((sa_kernel<3, 0, true>), dim3(grid), dim3(L.threads), lds, s, a);
+                SPV_GEN(3, true);
                 break;
             default:
                 return hipErrorInvalidValue;
@@ -423,17 +430,18 @@ hipError_t launch_sa(const SaLaunch &L, hipStream_t s, size_t lds_limit) {
                 hipLaunchKernelGGL(sa_kernel<0>, dim3(grid), dim3(L.threads), lds, s, a);
             break;
         case 1:
-            hipLaunchKernelGGL(sa_kernel<1>, dim3(grid), dim3(L.threads), lds, s, a);
+            SPV_GEN(1, false);
             break;
         case 2:
-            hipLaunchKernelGGL(sa_kernel<2>, dim3(grid), dim3(L.threads), lds, s, a);
+            SPV_GEN(2, false);
             break;
         case 3:
-            hipLaunchKernelGGL(sa_kernel<3>, dim3(grid), dim3(L.threads), lds, s, a);
+            SPV_GEN(3, false);
             break;
         default:
             return hipErrorInvalidValue;
     }
+#undef SPV_GEN
     return hipGetLastError();
 }
 

@@ -2,8 +2,8 @@
 // Monte Carlo of the transverse-field Ising model over P Trotter slices, the
 // Suzuki-Trotter mapping of Martonak, Santoro and Tosatti, PRB 66, 094203).
 //
-// One workgroup per read.  LDS holds the position-ordered instance (the same
-// ELL image as the general SA body; read from global memory instead when it
+// One workgroup per read.  LDS holds the position-ordered instance (as the
+// general SA body does; read from global memory instead when it
 // does not fit beside the slices), the acceptance rows of this sweep and the
 // next (beta_t / P) and the read's P slices as P/4 words per site: slice
 // k = 2m + parity lives in word parity * P/8 + m/4, byte m % 4, so a word holds
@@ -44,74 +44,21 @@ struct SqaArgs {
     uint32_t k0, k1;
 };
 
-// Xor mask (0xFE per accepted byte) of the digit tests for x[b] (slice tag); digits
-// from ndt on are zero for every x of this sweep (ndt is wave-uniform).  A byte is
-// accepted iff every nonzero digit of x passes (x <= 0 has none).  The first digit's
-// block is drawn without a branch (some byte of a word almost always has a nonzero
-// first digit); a later digit's block is drawn where some byte has that digit nonzero
-// (a byte already rejected stays rejected, so testing it again changes nothing).
-template <int ND>
-__device__ __forceinline__ uint32_t sqa_mask(const int32_t x[4], const uint32_t *tab, uint32_t i, uint32_t t,
-                                             uint32_t quad, uint32_t k0, uint32_t k1, int ndt) {
-    uint32_t d[4], th[4], mask = 0;
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-        d[b] = x[b] > 0 ? ((uint32_t)x[b] & (kDigitSize - 1)) : 0u;
-        th[b] = tab[d[b]];  // a zero digit reads a valid entry it ignores
-    }
-    {
-        const dev::Words4 w = dev::philox(i, t, quad, kTagSqa << 24, k0, k1);
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-            if ((d[b] == 0) | (w.w[b] < th[b])) mask |= 0xFEu << (8 * b);
-    }
-#pragma unroll
-    for (int j = 1; j < ND; ++j) {
-        if (j >= ndt) break;
-        bool need = false;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            d[b] = x[b] > 0 ? (((uint32_t)x[b] >> (kDigitBits * j)) & (kDigitSize - 1)) : 0u;
-            need |= d[b] != 0;
-            th[b] = tab[j * kDigitSize + d[b]];
-        }
-        if (need) {
-            const dev::Words4 w = dev::philox(i, t, quad, (kTagSqa << 24) | (uint32_t)j, k0, k1);
-#pragma unroll
-            for (int b = 0; b < 4; ++b)
-                if ((d[b] != 0) & (w.w[b] >= th[b])) mask &= ~(0xFEu << (8 * b));
-        }
-    }
-    return mask;
-}
-
-// Classical fields of the four slices of one word from records expanded for the
-// slice rows: record k of a position holds the LDS byte address of its neighbour's
-// row of slice words and J sign-extended, so a neighbour costs one 8-byte read, one
-// add and the four multiply-adds.  `w4` is the word's byte offset in a row.
-__device__ __forceinline__ core::Fields sqa_fields(const uint2 *__restrict__ nb, int n, int D, uint32_t w4,
-                                                   int32_t hv) {
-    core::Fields F;
-#pragma unroll
-    for (int b = 0; b < 4; ++b) F.f[b] = hv;
-    for (int k = 0; k < D; ++k) {
-        const uint2 r = nb[(size_t)k * n];
-        const uint32_t s = core::swar_ld32(r.x + w4);
-        const int32_t J = (int32_t)r.y;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) F.f[b] += __mul24(J, dev::spin_of(s, b));  // |J| < 2^15
-    }
-    return F;
-}
-
+// Bound by VALU issue: about 170 instructions a word of four slices on one-digit sweeps.
+// Capping the registers at 64 (a fourth workgroup a CU) spilled and was slower, 5.20
+// against 4.82 ms on Chimera 8 x 8, 1000 reads x 500 sweeps.
 // BIG: the instance stays in the global image (position-major records), LDS holds
-// the acceptance rows and the slices only.
-template <int ND, bool BIG = false>
+// the acceptance rows and the slices only.  DK: records per site fixed at compile time
+// (LDS instance in site blocks; 0: D at run time).
+template <int ND, bool BIG = false, int DK = 0>
 __global__ __launch_bounds__(1024) void sqa_kernel(SqaArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int cs[kMaxColours + 1];
     __shared__ int best_s;
     __shared__ long long bestE_s;
+    constexpr bool SITE = DK == kSiteRecs;
+    static_assert(DK == 0 || (SITE && !BIG), "site blocks hold kSiteRecs records in LDS");
+    constexpr int SH = core::field_shift<ND>;
     const int n = a.n, D = a.D, P = a.P, qw = P / 4, G8 = P / 8, T = blockDim.x, tid = threadIdx.x;
     const int read = blockIdx.x;
     core::SaItem it;
@@ -124,33 +71,24 @@ __global__ __launch_bounds__(1024) void sqa_kernel(SqaArgs a) {
         core::sa_big_layout(n, a.row_len, qw, &L, smem);
         core::sa_bind_image(&L, it, cs);  // ends with a barrier
     } else {
-        // the record area holds n * D expanded records of two words each
-        core::sa_layout(n, 2 * D, a.row_len, qw, &L, smem);
-        if (tid <= a.C) cs[tid] = a.image[3 + tid];
-        const uint32_t *recs = reinterpret_cast<const uint32_t *>(a.image + kImgHeader + 3 * n);
-        uint2 *nb2 = reinterpret_cast<uint2 *>(L.nbr);
-        const uint32_t sb = core::swar_lds_addr(L.S), row_bytes = 4u * (uint32_t)qw;
-        for (int idx = tid; idx < n * D; idx += T) {  // neighbour-major: record k of p at [k * n + p]
-            const int p = idx / D, k = idx - p * D;
-            const uint32_t r = recs[idx];
-            nb2[(size_t)k * n + p] = make_uint2(sb + (r >> 16) * row_bytes, (uint32_t)(int32_t)(int16_t)(r & 0xffffu));
-        }
-        for (int k = tid; k < n; k += T) {
-            L.hpos[k] = a.image[kImgHeader + 2 * n + k];
-            L.ord[k] = a.image[kImgHeader + k];
-        }
-        __syncthreads();
+        core::sa_layout(n, D, a.row_len, qw, &L, smem);
+        core::sa_load_instance<DK>(L, it, cs);  // ends with a barrier
     }
-    const uint2 *const nb2 = reinterpret_cast<const uint2 *>(L.nbr);
     // record k of position p: nbr[p * rec_p + k * rec_k]
-    const size_t rec_p = BIG ? (size_t)D : 1, rec_k = BIG ? 1 : (size_t)n;
+    const size_t rec_p = SITE ? (size_t)(DK + 2) : BIG ? (size_t)D : 1, rec_k = (BIG || SITE) ? 1 : (size_t)n;
+    auto bias = [&](int p) __attribute__((always_inline)) -> int32_t {
+        return SITE ? (int32_t)L.nbr[p * (DK + 2) + DK] : L.hpos[p];
+    };
+    auto index = [&](int p) __attribute__((always_inline)) -> uint32_t {
+        return SITE ? L.nbr[p * (DK + 2) + DK + 1] : (uint32_t)L.ord[p];
+    };
     const uint32_t quad0 = (uint32_t)read * (uint32_t)qw;
     for (int k = tid; a.sweeps > 0 && k < a.row_len; k += T) L.tab[k] = a.tables[k];  // none uploaded without sweeps
     for (int k = tid; k < 4 * qw; k += T) L.E2[k] = 0ull;
     // Initial slices: replica r = read * P + parity * P/2 + m, i.e. quad quad0 + word.
     for (int idx = tid; idx < n * qw; idx += T) {
         const int p = idx / qw, w = idx - p * qw;
-        const dev::Words4 r = dev::philox((uint32_t)L.ord[p], 0u, quad0 + (uint32_t)w, 1u << 24, a.k0, a.k1);
+        const dev::Words4 r = dev::philox(index(p), 0u, quad0 + (uint32_t)w, 1u << 24, a.k0, a.k1);
         uint32_t word = 0;
 #pragma unroll
         for (int b = 0; b < 4; ++b) word |= ((r.w[b] >> 31) ? 0x01u : 0xFFu) << (8 * b);
@@ -160,6 +98,7 @@ __global__ __launch_bounds__(1024) void sqa_kernel(SqaArgs a) {
 
     const int q = tid % G8, slot = tid / G8, nslots = T / G8;
     const bool active = slot < nslots;
+    const uint32_t s_addr = core::swar_lds_addr(L.S), s_row = 4u * (uint32_t)qw;
     // Race-detection build: each (class, parity) pass's slice-word writes, then its
     // reads (the ring neighbours' words of the other parity and the classical
     // neighbours' words), against the LDS bitmap.
@@ -175,13 +114,8 @@ __global__ __launch_bounds__(1024) void sqa_kernel(SqaArgs a) {
                 shadow::check(sh, (uint32_t)(p * qw + wa));
                 shadow::check(sh, (uint32_t)(p * qw + wb));
                 for (int k = 0; k < D; ++k) {
-                    if constexpr (BIG) {
-                        const uint32_t rec = L.nbr[(size_t)p * rec_p + (size_t)k * rec_k];
-                        if ((rec & 0xffffu) != 0u) shadow::check(sh, (rec >> 16) * (uint32_t)qw + (uint32_t)w);
-                    } else {
-                        const uint2 r = nb2[(size_t)k * n + p];
-                        if (r.y != 0u) shadow::check(sh, (r.x - core::swar_lds_addr(L.S)) / 4u + (uint32_t)w);
-                    }
+                    const uint32_t rec = L.nbr[(size_t)p * rec_p + (size_t)k * rec_k];
+                    if ((rec & 0xffffu) != 0u) shadow::check(sh, (rec >> 16) * (uint32_t)qw + (uint32_t)w);
                 }
             }
             shadow::count_pass(sh);
@@ -190,17 +124,24 @@ __global__ __launch_bounds__(1024) void sqa_kernel(SqaArgs a) {
             shadow::barrier();
         }
     };
+    int32_t jp_next = a.sweeps > 0 ? a.jp[0] : 0;  // loaded a sweep ahead, like the acceptance row
     for (int ls = 0; ls < a.sweeps; ++ls) {
         const uint32_t t = (uint32_t)ls;
-        const int32_t jp = a.jp[ls];
+        const int32_t jp = __builtin_amdgcn_readfirstlane(jp_next);
+        if (ls + 1 < a.sweeps) jp_next = a.jp[ls + 1];
         // digits that |x| <= x_bound + 2 Jp can have in this sweep
         const int64_t xmax = (int64_t)a.x_bound + 2 * (int64_t)jp;
         int ndt = 1;
         while (ndt < ND && (xmax >> (kDigitBits * ndt)) != 0) ++ndt;
         const uint32_t *tcur = L.tab + (ls & 1) * a.row_len;
         uint32_t *tnext = L.tab + ((ls + 1) & 1) * a.row_len;
-        if (ls + 1 < a.sweeps)
-            for (int k = tid; k < a.row_len; k += T) tnext[k] = a.tables[(size_t)(ls + 1) * a.row_len + k];
+        const int next_len = ls + 1 < a.sweeps ? a.row_len : 0;
+        uint32_t nrow[core::kRowRegs];
+        core::row_load(a.tables + (size_t)(ls + 1) * a.row_len, tnext, next_len, nrow);
+        // The ring neighbours are two more neighbours with coupling -Jp, as one pair of
+        // int16 lanes while Jp fits (else a multiplication apart).
+        const bool jp16 = jp <= 32767;
+        const uint32_t jpp = ((uint32_t)(-jp) & 0xffffu) * 0x10001u;
         for (int c = 0; c < a.C; ++c) {
             const int pe = cs[c + 1];
 #pragma unroll 1
@@ -213,25 +154,44 @@ __global__ __launch_bounds__(1024) void sqa_kernel(SqaArgs a) {
                 for (int p = cs[c] + slot; active && p < pe; p += nslots) {
                     const uint32_t *row = L.S + (size_t)p * qw;
                     const uint32_t self = row[w], A = row[wa], B = row[wb];
-                    core::Fields F;
-                    if constexpr (BIG)
-                        F = core::local_fields(L.nbr + p * rec_p, L.S, D, qw, w, L.hpos[p], rec_k);
-                    else
-                        F = sqa_fields(nb2 + p, n, D, 4u * (uint32_t)w, L.hpos[p]);
                     // even word: k-1 = odd slice m-1 (A byte b-1, or B byte 3), k+1 = odd slice m (A byte b);
                     // odd word: k-1 = even slice m (A byte b), k+1 = even slice m+1 (A byte b+1, or B byte 0)
                     const uint32_t up = par ? A : __builtin_amdgcn_alignbyte(A, B, 3);
                     const uint32_t dn = par ? __builtin_amdgcn_alignbyte(B, A, 1) : A;
+                    int32_t f[4], hv;
+                    uint32_t ord;
+                    auto start = [&]() __attribute__((always_inline)) {
+#pragma unroll
+                        for (int b = 0; b < 4; ++b) f[b] = SH ? hv << SH : 0;
+                        if (jp16) dev::pair_dot(up, dn, jpp, f);
+                    };
+                    if constexpr (SITE) {
+                        const core::Site<DK> site = core::load_site(L.nbr, p);
+                        hv = site.h;
+                        ord = site.ord;
+                        start();
+                        core::neighbour_sum(site.r, s_addr + 4u * (uint32_t)w, s_row, f);
+                    } else {
+                        hv = L.hpos[p];
+                        ord = (uint32_t)L.ord[p];
+                        start();
+                        core::neighbour_sum_any(L.nbr + p * rec_p, rec_k, D, s_addr + 4u * (uint32_t)w, s_row, f);
+                    }
+                    if constexpr (SH == 0)
+#pragma unroll
+                        for (int b = 0; b < 4; ++b) f[b] = hv + (f[b] >> 8);
+                    if (!jp16)  // full 32-bit products: Jp <= 2^24 (below 2^17 where the shift is 8)
+#pragma unroll
+                        for (int b = 0; b < 4; ++b)
+                            f[b] -= (jp * (dev::spin_of(up, b) + dev::spin_of(dn, b))) << SH;
                     int32_t x[4];
 #pragma unroll
-                    for (int b = 0; b < 4; ++b) {
-                        const int32_t g = F.f[b] - jp * (dev::spin_of(up, b) + dev::spin_of(dn, b));  // full 32-bit product: Jp <= 2^24
-                        x[b] = dev::spin_of(self, b) > 0 ? -g : g;
-                    }
-                    const uint32_t mask =
-                        sqa_mask<ND>(x, tcur, (uint32_t)L.ord[p], t, quad0 + (uint32_t)w, a.k0, a.k1, ndt);
+                    for (int b = 0; b < 4; ++b) x[b] = core::flip_cost(self, b, f[b]);
+                    const uint32_t mask = core::metropolis_mask<ND>(x, tcur, ord, t, quad0 + (uint32_t)w, a.k0, a.k1,
+                                                                    kTagSqa << 24, ndt);
                     if (mask) L.S[(size_t)p * qw + w] = self ^ mask;
                 }
+                if (c + 1 == a.C && par == 1) core::row_store(tnext, next_len, nrow);
                 __syncthreads();
                 if constexpr (shadow::kOn) shadow_pass(c, par, false);
             }
@@ -243,15 +203,12 @@ __global__ __launch_bounds__(1024) void sqa_kernel(SqaArgs a) {
         for (int idx = tid; idx < n * qw; idx += T) {
             const int p = idx / qw, w = idx - p * qw;
             const uint32_t self = L.S[idx];
-            core::Fields F;
-            if constexpr (BIG)
-                F = core::local_fields(L.nbr + p * rec_p, L.S, D, qw, w, L.hpos[p], rec_k);
-            else
-                F = sqa_fields(nb2 + p, n, D, 4u * (uint32_t)w, L.hpos[p]);
+            const int32_t hv = bias(p);
+            const core::Fields F = core::local_fields(L.nbr + p * rec_p, L.S, D, qw, w, hv, rec_k);
 #pragma unroll
             for (int b = 0; b < 4; ++b)
                 atomicAdd(&L.E2[w * 4 + b],
-                          (unsigned long long)((long long)dev::spin_of(self, b) * ((long long)L.hpos[p] + F.f[b])));
+                          (unsigned long long)((long long)dev::spin_of(self, b) * ((long long)hv + F.f[b])));
         }
     }
     __syncthreads();
@@ -282,7 +239,7 @@ __global__ __launch_bounds__(1024) void sqa_kernel(SqaArgs a) {
 
 size_t sqa_lds_bytes(int n, int D, int row_len, int P, bool big) {
     return big ? core::sa_big_layout(n, row_len, P / 4, nullptr, nullptr)
-               : core::sa_layout(n, 2 * D, row_len, P / 4, nullptr, nullptr);  // expanded records
+               : core::sa_layout(n, D, row_len, P / 4, nullptr, nullptr);
 }
 
 hipError_t launch_sqa(const SqaLaunch &L, hipStream_t s) {
@@ -308,8 +265,10 @@ hipError_t launch_sqa(const SqaLaunch &L, hipStream_t s) {
     do {                                                                                              \
         if (L.global_instance)                                                                        \
             hipLaunchKernelGGL((sqa_kernel<ND_, true>), dim3(L.reads), dim3(L.threads), lds, s, a);   \
+        else if (L.D == kSiteRecs)                                                              \
+            hipLaunchKernelGGL((sqa_kernel<ND_, false, kSiteRecs>), dim3(L.reads), dim3(L.threads), lds, s, a); \
         else                                                                                          \
-            hipLaunchKernelGGL((sqa_kernel<ND_, false>), dim3(L.reads), dim3(L.threads), lds, s, a);  \
+            hipLaunchKernelGGL((sqa_kernel<ND_>), dim3(L.reads), dim3(L.threads), lds, s, a);         \
     } while (0)
     switch (L.nd) {
         case 1:

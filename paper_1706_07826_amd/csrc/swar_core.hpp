@@ -44,20 +44,6 @@ constexpr int kSwarTabWords = 2 * kSwarTabHalf;
 // no address arithmetic.
 constexpr size_t kSwarSOffset = (size_t)2 * kSwarTabWords * 4;
 
-typedef unsigned int swar_v2u __attribute__((ext_vector_type(2)));
-typedef __attribute__((address_space(3))) const uint32_t swar_lds_u32;
-typedef __attribute__((address_space(3))) const swar_v2u swar_lds_v2u;
-
-// The 32-bit LDS address of a shared-memory object.
-__device__ __forceinline__ uint32_t swar_lds_addr(const void *p) {
-    return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p;
-}
-__device__ __forceinline__ uint32_t swar_ld32(uint32_t a) { return *(swar_lds_u32 *)(uintptr_t)a; }
-__device__ __forceinline__ uint2 swar_ld64(uint32_t a) {
-    const swar_v2u v = *(swar_lds_v2u *)(uintptr_t)a;
-    return make_uint2(v.x, v.y);
-}
-
 struct SwarLds {
     uint32_t *tab;   // [2][kSwarTabWords]
     uint32_t *S;     // [2][n][qw]: spins, then their complements
