@@ -271,7 +271,9 @@ spv_status upload(Ctx *c, DevBuf &dst, size_t dst_off, const void *src, size_t b
 // stays in LDS.  Groups hold a multiple of 4 slots; with cluster moves on, and
 // more workgroups available than quads, groups of 2 slots (half a quad each) or,
 // beyond K / 2 groups, of 1 slot: every group's cluster-move work shrinks with
-// its slot count.  SPVAR_PT_SPLIT=0 disables the
+// its slot count.  A ladder that is no multiple of four is split when its run also
+// fits one workgroup (which then serves where no split launch is resident at
+// once).  SPVAR_PT_SPLIT=0 disables the
 // split, =1 forces it (K % 4 == 0); SPVAR_PT_GROUPS fixes G; SPVAR_PT_BIG=1
 // reads the instance from global memory even when it would fit in LDS;
 // SPVAR_PT_ESUM=0 keeps a group with one slot pair on the separate cluster
@@ -287,34 +289,57 @@ spv_status plan_pt_split(Ctx *c, int n, int D, int K, int runs, int chains, int 
                          int icm_hi, bool single_fits, PtSplit *sp) {
     sp->use = false;
     const int mode = env_int("SPVAR_PT_SPLIT", -1);
-    if (mode == 0 || K % 4 != 0 || n < 1) return SPV_OK;
-    const int quads = K / 4, maxg = icm_hi > icm_lo ? K : quads;
+    const bool k4 = K % 4 == 0;
+    if (mode == 0 || n < 1 || (!k4 && !single_fits)) return SPV_OK;
+    const bool icm = icm_hi > icm_lo, forced = mode == 1 && k4;
+    const int quads = (K + 3) / 4, maxg = icm ? K : quads;
     int G = env_int("SPVAR_PT_GROUPS", 0);
+    // Without cluster moves a small ladder off the quads' grid is not split: each group
+    // draws the quads at its ends whole, and below about 768 words a sweep's exchange
+    // messages cost more than its updates (300 sweeps, n x K x chains, split / one group:
+    // 64 x 6 x 1 1.88 / 1.61 ms, 125 x 10 x 2 2.83 / 2.78, 216 x 10 x 1 2.27 / 3.15,
+    // 64 x 30 x 2 2.74 / 4.13).
+    if (G <= 0 && !k4 && !icm && (long long)n * ((chains * K + 3) / 4) < 768) G = 1;
     if (G <= 0) G = std::max(1, std::min(maxg, c->num_cus / std::max(runs, 1)));
     G = std::min(G, maxg);
-    if (mode != 1 && single_fits && G == 1) return SPV_OK;
+    // One group a run: with cluster moves the one-workgroup kernel (a wavefront per slot
+    // pair), else this kernel with the instance in LDS (16 slots of 512 sites, 160 runs,
+    // 100 sweeps: 1.00 ms against 1.88 in the one-workgroup kernel).
+    if (single_fits && G == 1 && icm && !forced) return SPV_OK;
     for (;; ++G) {
-        if (G > maxg)
+        if (G > maxg) {
+            if (!k4) return SPV_OK;
             return set_err(c, SPV_ECAPACITY, "PT run does not fit even split into %d groups (n=%d)", maxg, n);
-        const int m = G > K / 2 ? 1 : G > quads ? 2 : 4 * ((quads + G - 1) / G);
+        }
+        // (a ladder that is no multiple of four never makes more groups than asked for)
+        int m = 4 * ((quads + G - 1) / G);
+        if (k4 ? G > K / 2 : G >= K)
+            m = 1;
+        else if (k4 ? G > quads : 2 * G >= K && G > quads)
+            m = 2;
         const int Gr = (K + m - 1) / m;
-        const int nq = chains * ((m + 3) / 4);  // (one word per site when packed: fewer tasks)
+        const int nq = ptx_words_per_site(K, m, chains);  // (one word per site when packed: fewer tasks)
         const long long tasks = (long long)n * nq;
         int threads = env_int("SPVAR_PT_THREADS", tasks >= 1536 ? 1024 : tasks >= 768 ? 512 : 256);
         while (threads < nq) threads *= 2;
         if (threads > 1024) continue;
         const int icm_slots = icm_hi > icm_lo ? std::min(m, icm_hi - icm_lo) : 0;
         for (int big = env_int("SPVAR_PT_BIG", 0) ? 1 : 0; big < 2; ++big) {
+            if (Gr == 1 && big && single_fits && !forced) return SPV_OK;
             for (int nw = std::min(icm_slots, 4); nw >= (icm_slots ? 1 : 0); --nw)
             for (int esum = nw == 1 && env_int("SPVAR_PT_ESUM", 1) ? 1 : 0; esum >= 0; --esum) {
-                const size_t lds = ptx_lds_bytes(n, D, m, chains, row_len, nw, big != 0, esum != 0) + 256;
+                const PtxShape shape{n, D, K, m, chains, row_len, nd, nw, big != 0, esum != 0};
+                const size_t lds = ptx_lds_bytes(shape) + 256;
                 if (lds > c->lds_max) continue;
                 int bpc = 0;
-                hipError_t e = ptx_max_groups_resident(nd, big != 0, D, threads, lds, &bpc);
+                hipError_t e = ptx_max_groups_resident(shape, threads, lds, &bpc);
                 if (e != hipSuccess) return hip_check(c, e, "occupancy query");
-                if ((long long)bpc * c->num_cus < (long long)runs * Gr)
+                // (a run of one group waits for no other)
+                if (Gr > 1 && (long long)bpc * c->num_cus < (long long)runs * Gr) {
+                    if (!k4) return SPV_OK;
                     return set_err(c, SPV_ECAPACITY, "split PT grid %d x %d exceeds %d resident workgroups", runs,
                                    Gr, bpc * c->num_cus);
+                }
                 sp->use = true;
                 sp->G = Gr;
                 sp->m = m;
@@ -342,7 +367,8 @@ spv_status pt_lds_footprint(Ctx *c, const Inst *P, int K, int runs, int chains, 
                                   lds <= c->lds_max, &sp);
     if (st) return st;
     if (sp.use)
-        *lds_total = (int64_t)runs * sp.G * (int64_t)(ptx_lds_bytes(n, D, sp.m, chains, row_len, sp.nw_icm, sp.big, sp.esum) + 256);
+        *lds_total = (int64_t)runs * sp.G *
+                     (int64_t)(ptx_lds_bytes({n, D, K, sp.m, chains, row_len, nd, sp.nw_icm, sp.big, sp.esum}) + 256);
     else
         *lds_total = (int64_t)runs * (int64_t)lds;
     return SPV_OK;

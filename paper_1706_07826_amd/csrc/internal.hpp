@@ -396,9 +396,15 @@ unsigned pt_spin_limit();
 // LDS claimed by one spv_pt_sample launch with the shapes it would pick.
 spv_status pt_lds_footprint(Ctx *c, const Inst *P, int K, int runs, int chains, int icm_lo, int icm_hi,
                             int64_t *lds_total);
-size_t ptx_lds_bytes(int n, int D, int m, int chains, int row_len, int nw_icm, bool big, bool esum);
+// What a split launch's kernel and LDS layout depend on.
+struct PtxShape {
+    int n, D, K, m, chains, row_len, nd, nw_icm;
+    bool big, esum;
+};
+size_t ptx_lds_bytes(const PtxShape &s);
+int ptx_words_per_site(int K, int m, int chains);
 int ptx_msg_words(int n);
-hipError_t ptx_max_groups_resident(int nd, bool big, int D, int threads, size_t lds, int *blocks_per_cu);
+hipError_t ptx_max_groups_resident(const PtxShape &s, int threads, size_t lds, int *blocks_per_cu);
 hipError_t launch_ptx(const PtxLaunch &L, hipStream_t s);
 
 // Components and sorted-merge recombination (components.hip).

@@ -10,8 +10,10 @@
 //   2. replica exchange of pairs (k, k+1), k = t mod 2, decided from the
 //      energies held in LDS, configurations swapped byte-wise,
 //   3. Houdayer moves (chains 0/1): a wavefront per slot picks the seed with
-//      ballots, grows the cluster with a wavefront BFS (LDS visited bitset +
-//      queue, ballot/mbcnt compaction) and flips it in both replicas,
+//      ballots, finds its component with a union-find over the disagreeing
+//      sites (no barrier: a wavefront owns its forest) and flips it in both
+//      replicas.  A breadth-first growth, a queue chunk and a ballot per record
+//      at a time, was a chain of dependent LDS reads as long as the cluster,
 //   4. the colder half is offered to per-slot lists of the 10 lowest-energy
 //      distinct states (a wavefront per list: ballot compare, byte copy).
 // Replicas of a quad that belong to a neighbouring run (when chains*K is not
@@ -60,8 +62,8 @@ struct PtLds {
     int32_t *Lbad;     // [L] checkpoint count was outside 0..10
     int32_t *Lord;     // [L][10]
     int32_t *acc;      // [cK]
-    uint32_t *vis;     // [nw_icm][nwords]
-    uint16_t *queue;   // [nw_icm][n]
+    uint32_t *dis;     // [nw_icm][nwords] disagreement bits by position
+    uint16_t *parent;  // [nw_icm][n] union-find forests over positions
 };
 
 __host__ __device__ inline size_t al16(size_t x) { return (x + 15) & ~(size_t)15; }
@@ -80,8 +82,8 @@ __host__ __device__ inline size_t pt_layout(int n, int D, int K, int chains, int
                  o_S = take((size_t)n * nqa * 4), o_E = take((size_t)cK * 8), o_LE = take((size_t)Ls * 80),
                  o_Lw = take((size_t)Ls * 40), o_Lc = take((size_t)Ls * 4), o_Lb = take((size_t)Ls * 4),
                  o_Lo = take((size_t)Ls * 40),
-                 o_acc = take((size_t)cK * 4 + 4), o_vis = take((size_t)nw_icm * nwords * 4),
-                 o_q = take((size_t)nw_icm * n * 2);
+                 o_acc = take((size_t)cK * 4 + 4), o_dis = take((size_t)nw_icm * nwords * 4),
+                 o_par = take((size_t)nw_icm * n * 2);
     if (L) {
         L->nbr = reinterpret_cast<uint32_t *>(base + o_nbr);
         L->hpos = reinterpret_cast<int32_t *>(base + o_h);
@@ -97,8 +99,8 @@ __host__ __device__ inline size_t pt_layout(int n, int D, int K, int chains, int
         L->Lbad = reinterpret_cast<int32_t *>(base + o_Lb);
         L->Lord = reinterpret_cast<int32_t *>(base + o_Lo);
         L->acc = reinterpret_cast<int32_t *>(base + o_acc);
-        L->vis = reinterpret_cast<uint32_t *>(base + o_vis);
-        L->queue = reinterpret_cast<uint16_t *>(base + o_q);
+        L->dis = reinterpret_cast<uint32_t *>(base + o_dis);
+        L->parent = reinterpret_cast<uint16_t *>(base + o_par);
     }
     return o;
 }
@@ -239,22 +241,20 @@ __global__ __launch_bounds__(1024) void pt_kernel(PtArgs a) {
             const int pe = cs[c + 1];
             for (int p = cs[c] + slot_t; active && p < pe; p += nslots) {
                 const uint32_t self = L.S[(size_t)p * nqa + q];
-                int32_t f[4];
-                ptc::quad_fields(nbr_rec, D, p, L.S, nqa, q, L.hpos[p], f);
                 int32_t x[4];
-#pragma unroll
-                for (int b = 0; b < 4; ++b) x[b] = dev::spin_of(self, b) > 0 ? -f[b] : f[b];
+                ptc::quad_costs<ND, 0>(nbr_rec, D, p, L.S, nqa, q, L.hpos[p], self, x);
                 const uint32_t mask =
                     ptc::metropolis_mask4<ND>(x, tb, (uint32_t)L.ord[p], t, quad, a.k0, a.k1);
 #pragma unroll
-                for (int b = 0; b < 4; ++b)
-                    if (mask & (0xFEu << (8 * b))) dE[b] += 2ll * x[b];
+                for (int b = 0; b < 4; ++b) ptc::add_flip(dE[b], x[b], (mask >> (8 * b + 1)) & 1u);
                 if (mask) L.S[(size_t)p * nqa + q] = self ^ mask;
             }
             __syncthreads();
             if constexpr (shadow::kOn) shadow_pass(c, false);
         }
-        // Fold the energy changes of the sweep.
+        // Fold the energy changes of the sweep (2 x a flip).
+#pragma unroll
+        for (int b = 0; b < 4; ++b) dE[b] = 2 * (dE[b] >> core::field_shift<ND>);
         if (pow2) {
 #pragma unroll
             for (int b = 0; b < 4; ++b)
@@ -303,8 +303,8 @@ __global__ __launch_bounds__(1024) void pt_kernel(PtArgs a) {
         }
         // 3. Houdayer cluster moves between chains 0 and 1.
         if (a.nw_icm > 0 && wid < a.nw_icm) {
-            uint32_t *vis = L.vis + (size_t)wid * nwords;
-            uint16_t *queue = L.queue + (size_t)wid * n;
+            uint32_t *dis = L.dis + (size_t)wid * nwords;
+            uint16_t *parent = L.parent + (size_t)wid * n;
             for (int k = a.icm_lo + wid; k < a.icm_hi; k += a.nw_icm) {
                 const int la = k, lb = K + k;
                 const int ra = r0 + la, rb = r0 + lb;
@@ -312,29 +312,27 @@ __global__ __launch_bounds__(1024) void pt_kernel(PtArgs a) {
                 const int ba = ra & 3, bb = rb & 3;
                 auto byteA = [=](int p) __attribute__((always_inline)) -> unsigned char * { return L.Sb + ((size_t)p * nqa + qa_) * 4 + ba; };
                 auto byteB = [=](int p) __attribute__((always_inline)) -> unsigned char * { return L.Sb + ((size_t)p * nqa + qb_) * 4 + bb; };
-                // sites where the replicas disagree, counted in variable-index order
+                // disagreement bits by position, and a fresh forest
                 int n_neg = 0;
-                for (int i0 = 0; i0 < n; i0 += 64) {
-                    const int i = i0 + lane;
-                    bool f = false;
-                    if (i < n) {
-                        const int p = L.pos[i];
-                        f = *byteA(p) != *byteB(p);
-                    }
-                    n_neg += __popcll(__ballot(f));
+                for (int p0 = 0; p0 < n; p0 += 64) {
+                    const int p = p0 + lane;
+                    const bool f = p < n && *byteA(p) != *byteB(p);
+                    const unsigned long long m = __ballot(f);
+                    n_neg += __popcll(m);
+                    if (lane < 2 && (p0 >> 5) + lane < nwords) dis[(p0 >> 5) + lane] = (uint32_t)(m >> (32 * lane));
+                    if (p < n) parent[p] = (uint16_t)p;
                 }
                 if (n_neg == 0) continue;
+                __builtin_amdgcn_wave_barrier();
+                auto differs = [=](int p) __attribute__((always_inline)) -> bool { return (dis[p >> 5] >> (p & 31)) & 1u; };
+                // the seed: the target-th disagreeing site in variable-index order
                 const uint32_t w = dev::philox((uint32_t)k, t, (uint32_t)run, 4u << 24, a.k0, a.k1).w[0];
                 const int target = (int)(((unsigned long long)w * (unsigned long long)n_neg) >> 32);
                 int seed_p = -1, seen = 0;
                 for (int i0 = 0; i0 < n && seed_p < 0; i0 += 64) {
                     const int i = i0 + lane;
-                    bool f = false;
-                    int p = 0;
-                    if (i < n) {
-                        p = L.pos[i];
-                        f = *byteA(p) != *byteB(p);
-                    }
+                    const int p = i < n ? L.pos[i] : 0;
+                    const bool f = i < n && differs(p);
                     const unsigned long long m = __ballot(f);
                     const int cnt = __popcll(m);
                     if (target < seen + cnt) {
@@ -345,67 +343,39 @@ __global__ __launch_bounds__(1024) void pt_kernel(PtArgs a) {
                     }
                     seen += cnt;
                 }
-                for (int wd = lane; wd < nwords; wd += 64) vis[wd] = 0u;
-                __builtin_amdgcn_wave_barrier();
-                if (lane == 0) {
-                    vis[seed_p >> 5] = 1u << (seed_p & 31);
-                    queue[0] = (uint16_t)seed_p;
-                }
-                __builtin_amdgcn_wave_barrier();
-                int head = 0, tail = 1;
-                while (head < tail) {
-                    const int chunk = min(64, tail - head);
-                    const bool act = lane < chunk;
-                    const int v = act ? (int)queue[head + lane] : 0;
-                    int newtail = tail;
+                // join the ends of every J != 0 edge between disagreeing sites (from its smaller end)
+                for (int p = lane; p < n; p += 64) {
+                    if (!differs(p)) continue;
                     for (int kk = 0; kk < D; ++kk) {
-                        bool added = false;
-                        int u = 0;
-                        if (act) {
-                            const uint32_t rec = L.nbr[(size_t)kk * n + v];
-                            u = (int)(rec >> 16);
-                            if ((rec & 0xffffu) != 0u && *byteA(u) != *byteB(u)) {
-                                const uint32_t bit = 1u << (u & 31);
-                                const uint32_t old = atomicOr(&vis[u >> 5], bit);
-                                added = !(old & bit);
-                            }
-                        }
-                        const unsigned long long m = __ballot(added);
-                        if (added) queue[newtail + __popcll(m & lanemask_lt())] = (uint16_t)u;
-                        newtail += __popcll(m);
-                    }
-                    head += chunk;
-                    tail = newtail;
-                    __builtin_amdgcn_wave_barrier();
-                }
-                // energy change of flipping the cluster, then the flips
-                long long dA = 0, dB = 0;
-                for (int e = lane; e < tail; e += 64) {
-                    const int v = queue[e];
-                    const int sA = (int)(int8_t)*byteA(v), sB = (int)(int8_t)*byteB(v);
-                    dA += -2ll * L.hpos[v] * sA;
-                    dB += -2ll * L.hpos[v] * sB;
-                    for (int kk = 0; kk < D; ++kk) {
-                        const uint32_t rec = L.nbr[(size_t)kk * n + v];
+                        const uint32_t rec = L.nbr[(size_t)kk * n + p];
                         const int u = (int)(rec >> 16);
-                        if (!((vis[u >> 5] >> (u & 31)) & 1u)) {
-                            const long long Jv = (int16_t)(rec & 0xffffu);
-                            dA += -2ll * Jv * sA * (int)(int8_t)*byteA(u);
-                            dB += -2ll * Jv * sB * (int)(int8_t)*byteB(u);
-                        }
+                        if (u > p && (rec & 0xffffu) != 0u && differs(u)) ptc::uf_union(parent, (uint32_t)p, (uint32_t)u);
                     }
+                }
+                __builtin_amdgcn_wave_barrier();
+                // Energy change and flip of the seed's component.  A neighbour outside it agrees
+                // in both replicas and keeps its value, so a site is flipped as soon as it is
+                // summed; replica B's spin is -s_A and its field the same, so its change is -dA.
+                const uint32_t root = ptc::uf_find(parent, (uint32_t)seed_p);
+                long long dA = 0;
+                for (int p = lane; p < n; p += 64) {
+                    if (!differs(p) || ptc::uf_find(parent, (uint32_t)p) != root) continue;
+                    int32_t f = L.hpos[p];
+                    for (int kk = 0; kk < D; ++kk) {
+                        const uint32_t rec = L.nbr[(size_t)kk * n + p];
+                        const int u = (int)(rec >> 16);
+                        if ((rec & 0xffffu) != 0u && !differs(u))
+                            f += (int32_t)(int16_t)(rec & 0xffffu) * (int32_t)(int8_t)*byteA(u);
+                    }
+                    const int sA = (int)(int8_t)*byteA(p);
+                    dA -= 2ll * sA * f;
+                    *byteA(p) = (unsigned char)(-sA);
+                    *byteB(p) = (unsigned char)sA;
                 }
                 dA = wave_sum(dA);
-                dB = wave_sum(dB);
-                __builtin_amdgcn_wave_barrier();
-                for (int e = lane; e < tail; e += 64) {
-                    const int v = queue[e];
-                    *byteA(v) = (unsigned char)(-(int)(int8_t)*byteA(v));
-                    *byteB(v) = (unsigned char)(-(int)(int8_t)*byteB(v));
-                }
                 if (lane == 0) {
                     L.E[la] += dA;
-                    L.E[lb] += dB;
+                    L.E[lb] -= dA;
                 }
                 __builtin_amdgcn_wave_barrier();
             }

@@ -8,6 +8,7 @@
 
 #include "device.hpp"
 #include "internal.hpp"
+#include "sa_core.hpp"
 
 namespace spv {
 namespace ptc {
@@ -23,7 +24,8 @@ __device__ __forceinline__ long long wave_sum(long long v) {
 }
 
 // Xor mask (0xFE per accepted byte) of the Metropolis decisions for x[b] = -s f of
-// four replicas at their own temperatures (acceptance rows tb[b]): a byte is accepted
+// four replicas at their own temperatures (acceptance rows tb[b]), x scaled by
+// 2^field_shift<ND>: a byte is accepted
 // iff every nonzero digit of x passes (x <= 0 has none).  The first digit's block is
 // drawn without a branch (some byte of a word almost always has a nonzero first
 // digit), so the decisions stay lane masks; a later digit's block is drawn where
@@ -31,10 +33,12 @@ __device__ __forceinline__ long long wave_sum(long long v) {
 template <int ND>
 __device__ __forceinline__ uint32_t metropolis_mask4(const int32_t x[4], const uint32_t *const tb[4], uint32_t i,
                                                      uint32_t t, uint32_t quad, uint32_t k0, uint32_t k1) {
-    uint32_t d[4], th[4], mask = 0;
+    constexpr int SH = core::field_shift<ND>;
+    uint32_t xp[4], d[4], th[4], mask = 0;
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-        d[b] = x[b] > 0 ? ((uint32_t)x[b] & (kDigitSize - 1)) : 0u;
+        xp[b] = (uint32_t)max(x[b], 0);
+        d[b] = (xp[b] >> SH) & (kDigitSize - 1);
         th[b] = tb[b][d[b]];  // a zero digit reads a valid entry it ignores
     }
     {
@@ -48,7 +52,7 @@ __device__ __forceinline__ uint32_t metropolis_mask4(const int32_t x[4], const u
         bool need = false;
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
-            d[b] = x[b] > 0 ? (((uint32_t)x[b] >> (kDigitBits * j)) & (kDigitSize - 1)) : 0u;
+            d[b] = (xp[b] >> (SH + kDigitBits * j)) & (kDigitSize - 1);
             need |= d[b] != 0;
             th[b] = tb[b][j * kDigitSize + d[b]];
         }
@@ -86,48 +90,64 @@ __device__ inline bool swap_test(long long D, const uint32_t *__restrict__ T, in
     return ok;
 }
 
-// Neighbour records are fetched this many at a time, so their loads (LDS or
-// global) are in flight together instead of one after another.
-constexpr int kRecBatch = 8;
+// Neighbour records are fetched this many at a time when their count is only known at
+// run time, so their loads (LDS or global) are in flight together; even, so they pair up.
+constexpr int kRecBatch = 4;
 
-// Local fields f[b] = h + sum_k J_k s_k[b] of the 4 replicas in word q of
-// position p (spins S[pos][nq], records rec(k, p) = pos << 16 | uint16 J).
+// 256 times the neighbour sums of NB replicas, bytes b0 .. b0 + NB - 1 of word q of
+// position p (spins S[pos][nq], records rec(k, p) = pos << 16 | uint16 J), added to acc.
 // DK > 0: exactly DK records per site (straight-line code); DK = 0: D at run time.
-// Positions (16 bits) and word counts fit 24 bits, so the word index takes the
-// full-rate 24-bit multiply rather than the quarter-rate 32-bit one.
+template <int DK, int NB = 4, typename Rec>
+__device__ __forceinline__ void quad_sums(Rec rec, int D, int p, const uint32_t *__restrict__ S, int nq, int q,
+                                          int32_t (&acc)[NB], int b0 = 0) {
+    const uint32_t sa = core::swar_lds_addr(S) + 4u * (uint32_t)q, row = 4u * (uint32_t)nq;
+    if constexpr (DK > 0) {
+        uint32_t rr[DK];
+#pragma unroll
+        for (int u = 0; u < DK; ++u) rr[u] = rec(u, p);
+        core::neighbour_sum<DK, NB>(rr, sa, row, acc, b0);
+        return;
+    }
+    int k0 = 0;
+    for (; k0 + kRecBatch <= D; k0 += kRecBatch) {
+        uint32_t rr[kRecBatch];
+#pragma unroll
+        for (int u = 0; u < kRecBatch; ++u) rr[u] = rec(k0 + u, p);
+        core::neighbour_sum<kRecBatch, NB>(rr, sa, row, acc, b0);
+    }
+    for (; k0 < D; ++k0) {
+        const uint32_t rr[1] = {rec(k0, p)};
+        core::neighbour_sum<1, NB>(rr, sa, row, acc, b0);
+    }
+}
+
+// Local fields f[b] = h + sum_k J_k s_k[b] of the 4 replicas in word q of position p.
 template <int DK = 0, typename Rec>
 __device__ __forceinline__ void quad_fields(Rec rec, int D, int p, const uint32_t *__restrict__ S, int nq, int q,
                                             int32_t h, int32_t f[4]) {
+    int32_t acc[4] = {0, 0, 0, 0};
+    quad_sums<DK>(rec, D, p, S, nq, q, acc);
 #pragma unroll
-    for (int b = 0; b < 4; ++b) f[b] = h;
-    if constexpr (DK > 0) {
-        uint32_t rr[DK], w[DK];
+    for (int b = 0; b < 4; ++b) f[b] = h + (acc[b] >> 8);
+}
+
+// Flip costs x[i] = -s f of NB replicas, bytes b0 .. of the word `self`, scaled by
+// 2^field_shift<ND>.
+template <int ND, int DK, int NB = 4, typename Rec>
+__device__ __forceinline__ void quad_costs(Rec rec, int D, int p, const uint32_t *__restrict__ S, int nq, int q,
+                                           int32_t h, uint32_t self, int32_t (&x)[NB], int b0 = 0) {
+    constexpr int SH = core::field_shift<ND>;
+    int32_t f[NB];
 #pragma unroll
-        for (int u = 0; u < DK; ++u) rr[u] = rec(u, p);
+    for (int i = 0; i < NB; ++i) f[i] = SH ? h << SH : 0;
+    quad_sums<DK, NB>(rec, D, p, S, nq, q, f, b0);
 #pragma unroll
-        for (int u = 0; u < DK; ++u) w[u] = S[__umul24(rr[u] >> 16, (uint32_t)nq) + (uint32_t)q];
-#pragma unroll
-        for (int u = 0; u < DK; ++u) {
-            const int32_t Jv = (int32_t)(int16_t)(rr[u] & 0xffffu);
-#pragma unroll
-            for (int b = 0; b < 4; ++b) f[b] += Jv * dev::spin_of(w[u], b);
-        }
-        return;
-    }
-    for (int k0 = 0; k0 < D; k0 += kRecBatch) {
-        uint32_t rr[kRecBatch];
-#pragma unroll
-        for (int u = 0; u < kRecBatch; ++u) rr[u] = (k0 + u < D) ? rec(k0 + u, p) : 0u;
-        uint32_t w[kRecBatch];
-#pragma unroll
-        for (int u = 0; u < kRecBatch; ++u) w[u] = (k0 + u < D) ? S[__umul24(rr[u] >> 16, (uint32_t)nq) + q] : 0u;
-#pragma unroll
-        for (int u = 0; u < kRecBatch; ++u) {
-            const int32_t Jv = (int32_t)(int16_t)(rr[u] & 0xffffu);
-#pragma unroll
-            for (int b = 0; b < 4; ++b) f[b] += Jv * dev::spin_of(w[u], b);
-        }
-    }
+    for (int i = 0; i < NB; ++i) x[i] = core::flip_cost(self, b0 + i, SH ? f[i] : h + (f[i] >> 8));
+}
+
+// Energy change of an accepted flip added to `sum`, which is kept scaled like x.
+__device__ __forceinline__ void add_flip(long long &sum, int32_t x, uint32_t taken) {
+    sum += (long long)x * (long long)(int32_t)taken;
 }
 
 // Lock-free union-find in LDS over 16-bit parents (parent[x] <= x always: a

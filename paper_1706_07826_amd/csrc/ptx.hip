@@ -7,6 +7,11 @@
 // chain) * K + slot lies inside one group), or m = 2 or 1 (a group owns half
 // or a quarter of its quad: it draws the quad's whole random block and updates
 // its own bytes; the other bytes of its LDS copy are never changed or read out).
+// When K is no multiple of 4 the quads of a chain start at another slot in every
+// (run, chain), so a group holds every quad its slots of a chain touch and owns
+// some of their bytes, at an offset of the chain's own (26 slots x 2 chains x 8 runs of
+// the L = 6 cube with cluster moves, 300 sweeps: 54.3 ms in one workgroup a run, 5.3 ms
+// as 26 groups of one slot).
 // A group of one slot reading its instance from the global image keeps both
 // chains' bytes of that slot in one word per site (byte c: chain c), each byte
 // drawing from its own chain's quad block.
@@ -97,9 +102,14 @@ struct PtxLds {
 // Pending-join buffer per wavefront (64 appended at most on top of < 64 pending).
 constexpr int kJoinBuf = 128;
 
-__host__ __device__ inline size_t ptx_layout(int n, int D, int m, int chains, int row_len, int nw_icm, bool big,
+// Quad words a group of m slots holds per chain: with K a multiple of 4 its slots start
+// on a quad's boundary (or lie inside one quad), else at any byte.
+__host__ __device__ inline int ptx_chain_words(int K, int m) { return (m + (K % 4 == 0 ? 3 : 6)) / 4; }
+__host__ __device__ inline bool ptx_packed(bool big, int m, int chains) { return big && m == 1 && chains == 2; }
+
+__host__ __device__ inline size_t ptx_layout(int n, int D, int K, int m, int chains, int row_len, int nw_icm, bool big,
                                              bool esum, PtxLds *L, unsigned char *base) {
-    const int nq = (big && m == 1 && chains == 2) ? 1 : chains * ((m + 3) / 4), nl = chains * m,
+    const int nq = ptx_packed(big, m, chains) ? 1 : chains * ptx_chain_words(K, m), nl = chains * m,
               vstride = 2 * ((n + 63) / 64);
     size_t o = 0;
     auto take = [&](size_t bytes) {
@@ -157,21 +167,35 @@ __global__ void xw_zero_kernel(uint32_t *w, size_t count) {
         w[i] = 0u;
 }
 
-// ND threshold digits; BIG: instance read from the global image; DK: records per
-// site fixed at compile time (0: D at run time).
 // a byte in LDS, addressed with 32-bit offsets
 typedef __attribute__((address_space(3))) const unsigned char lds_u8;
 typedef __attribute__((address_space(3))) unsigned char lds_mu8;
 
-template <int ND, bool BIG, int DK>
+// What a launch's groups do between exchanges, fixed at compile time for the common
+// shapes: one kernel with every body in it held 128 registers and spilled 132 bytes (216
+// with the instance in global memory), whichever body ran; alone they spill 0 to 76.
+// With the 16-bit dot-product fields, before -> after: L = 10 Gaussian cube, 32 slots x
+// 64 runs, no moves, 11.8 -> 11.1 ms per 1000 sweeps; L = 20, 40 slots x 2 chains, packed
+// single pairs, 18.0 -> 15.5 ms per 300.
+enum PtxMove {
+    kMoveNone,    // no cluster moves
+    kMoveSingle,  // one slot pair at a time, its energy terms gathered in the join scan
+    kMovePacked,  // the same, both chains' bytes of the group's slot in one word per site
+    kMoveAny      // up to kIcmBatch pairs at a time (or none, or one), decided at run time
+};
+
+// ND threshold digits; BIG: instance read from the global image; DK: records per
+// site fixed at compile time (0: D at run time).
+template <int ND, bool BIG, int DK, int MV>
 __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
+    constexpr int kBatch = MV == kMoveAny ? kIcmBatch : 1;  // slot pairs of a pass
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int cs[kMaxColours + 1];
     __shared__ int nacc;
     __shared__ int stop;
     const int n = a.n, D = a.D, K = a.K, chains = a.chains, G = a.G, row_len = a.row_len, xmsg = a.xmsg;
     PtxLds Lay;
-    ptx_layout(n, D, a.m, chains, row_len, a.nw_icm, BIG, a.esum != 0, &Lay, smem);
+    ptx_layout(n, D, K, a.m, chains, row_len, a.nw_icm, BIG, a.esum != 0, &Lay, smem);
     // LDS regions as plain locals (keeps the layout record out of scratch memory)
     auto *const L_nbr = Lay.nbr;
     auto *const L_hpos = Lay.hpos;
@@ -199,13 +223,20 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
     auto *const L_es = Lay.esite;
     const int tid = threadIdx.x, T = blockDim.x, lane = dev::lane_id(), wid = tid >> 6, nw = T >> 6;
     const int run = blockIdx.x / G, g = blockIdx.x - run * G;
-    // boff: byte of the quad word holding the group's first slot (0 when m is a
-    // multiple of 4)
-    const int s0 = g * a.m, mg = min(a.m, K - s0), boff = s0 & 3, qpc = (boff + mg + 3) >> 2;
+    const int s0 = g * a.m, mg = min(a.m, K - s0);
+    // byte of its quad word that holds the group's first slot of a chain; with K a
+    // multiple of 4 the same in every chain and run, and 0 when m is one too
+    const uint32_t r00 = (uint32_t)run * (uint32_t)(chains * K) + (uint32_t)s0;
+    auto boff_of = [=](int ch) __attribute__((always_inline)) -> int {
+        return (int)((r00 + (uint32_t)(ch * K)) & 3u);
+    };
+    const int boff = boff_of(0), boff1 = chains > 1 ? boff_of(1) : boff;
+    const bool k4 = (K & 3) == 0;
+    const int qpc = k4 ? (boff + mg + 3) >> 2 : ptx_chain_words(K, a.m);
     // pk: a group of one slot (cluster moves on, two chains) reading its instance from
     // the global image keeps both chains' bytes of its slot in one word per site,
     // chain c in byte c (with the instance in LDS the layout stays one word per chain)
-    const bool pk = BIG && mg == 1 && chains == 2;
+    const bool pk = MV == kMoveAny ? ptx_packed(BIG, a.m, chains) : MV == kMovePacked;
     const int nq = pk ? 1 : chains * qpc, nl = chains * mg;
     const int32_t *img = a.image;
     const uint32_t *gnbr = reinterpret_cast<const uint32_t *>(img + kImgHeader + 3 * n);
@@ -227,7 +258,7 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
     // byte of local replica l = chain * mg + (slot - s0) at position p
     auto sbyte = [=](int l, int p) __attribute__((always_inline)) -> unsigned char * {
         if (pk) return Sb + (size_t)p * 4 + l;
-        const int ch = l / mg, o = l - ch * mg + boff;
+        const int ch = l / mg, o = l - ch * mg + boff_of(ch);
         return Sb + ((size_t)p * nq + ch * qpc + (o >> 2)) * 4 + (o & 3);
     };
     // a replica's bytes lie pst apart: loops over positions take sbyte(l, 0) once
@@ -289,21 +320,21 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
 
     const int q = tid % nq, pt = tid / nq, nstr = T / nq;
     const bool active = pt < nstr;
-    const int chq = q / qpc, jq = q - chq * qpc;
+    const int chq = q / qpc, jq = q - chq * qpc, boffq = boff_of(chq);
     const uint32_t quad = (uint32_t)((((size_t)run * chains + chq) * K + s0) / 4 + jq);
-    // pk: chain 1's quad (byte 1 of the word draws its word boff from that quad's block)
+    // pk: chain 1's quad (byte 1 of the word draws its word boff1 from that quad's block)
     const uint32_t quad1 = (uint32_t)((((size_t)run * chains + 1) * K + s0) / 4);
     auto wsel = [](const dev::Words4 &w, int i) __attribute__((always_inline)) -> uint32_t {
         return i == 0 ? w.w[0] : i == 1 ? w.w[1] : i == 2 ? w.w[2] : w.w[3];
     };
-    // byte b of the thread's word is the group's local slot 4 jq + b - boff; own marks
+    // byte b of the thread's word is the group's local slot 4 jq + b - boffq; own marks
     // (0xFE) the bytes that are the group's
     int loc[4];
     const uint32_t *tb[4];
     uint32_t own = 0;
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-        const int o = 4 * jq + b - boff;
+        const int o = 4 * jq + b - boffq;
         const bool mine = o >= 0 && o < mg;
         own |= mine ? 0xFEu << (8 * b) : 0u;
         loc[b] = chq * mg + (mine ? o : 0);
@@ -317,7 +348,8 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
     if (pk) own = 0xFEFEu;
     const bool pow2 = (nq & (nq - 1)) == 0 && nq <= 64;
     // the group owns 1 or 2 bytes of each of its words (the same bytes in every word)
-    const bool part = !pk && qpc == 1 && mg < 4;
+    const bool part = !pk && k4 && qpc == 1 && mg < 4;
+    const bool owner = active && own != 0;  // (a quad the group's slots of a chain do not reach has nothing to update)
 
     // Initial state and energies.
     for (int p = pt; active && p < n; p += nstr) {
@@ -325,7 +357,7 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
         uint32_t word = 0;
         if (pk) {
             const dev::Words4 w1 = dev::philox((uint32_t)ORD(p), 0u, quad1, 1u << 24, a.k0, a.k1);
-            word = ((wsel(w, boff) >> 31) ? 0x01u : 0xFFu) | (((wsel(w1, boff) >> 31) ? 0x01u : 0xFFu) << 8) |
+            word = ((wsel(w, boff) >> 31) ? 0x01u : 0xFFu) | (((wsel(w1, boff1) >> 31) ? 0x01u : 0xFFu) << 8) |
                    0x01010000u;
         } else {
 #pragma unroll
@@ -386,18 +418,16 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
 
     for (int ls = 0; ls < a.sweeps; ++ls) {
         const uint32_t t = a.sweep_offset + (uint32_t)ls;
-        // 1. Metropolis on the group's replicas.
+        // 1. Metropolis on the group's replicas (costs and their sums scaled by 2^SH).
+        constexpr int SH = core::field_shift<ND>;
         long long dE[4] = {0, 0, 0, 0}, dEp[2] = {0, 0};
         for (int c = 0; c < a.C; ++c) {
             if constexpr (shadow::kOn) shadow_pass(c, true);
             const int pe = cs[c + 1];
             auto update = [&](int p, auto rec, int32_t hp, uint32_t ord) __attribute__((always_inline)) {
                 const uint32_t self = L_S[(size_t)p * nq + q];
-                int32_t f[4];
-                ptc::quad_fields<DK>(rec, D, p, L_S, nq, q, hp, f);
                 int32_t x[4];
-#pragma unroll
-                for (int b = 0; b < 4; ++b) x[b] = dev::spin_of(self, b) > 0 ? -f[b] : f[b];
+                ptc::quad_costs<ND, DK>(rec, D, p, L_S, nq, q, hp, self, x);
                 // The key enters each site's draws opaquely: otherwise the twenty round
                 // keys are hoisted out of the loop, outgrow the scalar registers and
                 // come back one vector-lane read at a time.  (Unoptimised device builds
@@ -408,17 +438,18 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
 #endif
                 const uint32_t mask = own & ptc::metropolis_mask4<ND>(x, tb, ord, t, quad, k0, k1);
 #pragma unroll
-                for (int b = 0; b < 4; ++b)
-                    if (mask & (0xFEu << (8 * b))) dE[b] += 2ll * x[b];
+                for (int b = 0; b < 4; ++b) ptc::add_flip(dE[b], x[b], (mask >> (8 * b + 1)) & 1u);
                 if (mask) L_S[(size_t)p * nq + q] = self ^ mask;
             };
             // A group of 1 or 2 slots owns bytes boff.. of its words: those bytes alone are
             // updated (the quad's random blocks drawn whole, so the draws are the same).
             auto update_part = [&](int p, const uint32_t *rr, int32_t hp, uint32_t ord) __attribute__((always_inline)) {
                 const uint32_t self = L_S[(size_t)p * nq + q];
-                uint32_t wv[DK > 0 ? DK : 1];
-#pragma unroll
-                for (int u = 0; u < DK; ++u) wv[u] = L_S[__umul24(rr[u] >> 16, (uint32_t)nq) + (uint32_t)q];
+                // bytes b0 and b0 + 1 hold the owned ones (a 1-slot group's other is unused)
+                const int b0 = min(boff, 2), o0 = boff - b0;
+                int32_t xx[2];
+                ptc::quad_costs<ND, DK, 2>([&](int u, int) __attribute__((always_inline)) { return rr[u]; }, D, p, L_S,
+                                           nq, q, hp, self, xx, b0);
                 uint32_t k0 = a.k0, k1 = a.k1;
 #ifdef __OPTIMIZE__
                 asm volatile("" : "+s"(k0), "+s"(k1));
@@ -427,13 +458,8 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
                 uint32_t d[2], th[2];
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
-                    const int sh = 24 - 8 * min(boff + i, 3);  // (i = 1 of a 1-slot group is unused)
-                    int32_t f = hp;
-#pragma unroll
-                    for (int u = 0; u < DK; ++u)
-                        f += (int32_t)(int16_t)(rr[u] & 0xffffu) * ((int32_t)(wv[u] << sh) >> 24);
-                    x[i] = ((int32_t)(self << sh) >> 24) > 0 ? -f : f;
-                    d[i] = x[i] > 0 ? ((uint32_t)x[i] & (kDigitSize - 1)) : 0u;
+                    x[i] = xx[min(o0 + i, 1)];
+                    d[i] = ((uint32_t)max(x[i], 0) >> SH) & (kDigitSize - 1);
                     th[i] = L_tab[(size_t)min(i, mg - 1) * row_len + d[i]];
                 }
                 auto pick = [&](const dev::Words4 &w, int i) __attribute__((always_inline)) -> uint32_t {
@@ -451,7 +477,7 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
                     bool need = false;
 #pragma unroll
                     for (int i = 0; i < 2; ++i) {
-                        d[i] = x[i] > 0 ? (((uint32_t)x[i] >> (kDigitBits * j)) & (kDigitSize - 1)) : 0u;
+                        d[i] = ((uint32_t)max(x[i], 0) >> (SH + kDigitBits * j)) & (kDigitSize - 1);
                         need |= i < mg && d[i] != 0;
                         th[i] = L_tab[(size_t)min(i, mg - 1) * row_len + j * kDigitSize + d[i]];
                     }
@@ -467,7 +493,7 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
                 for (int i = 0; i < 2; ++i)
                     if (i < mg && acc[i]) {
                         mask |= 0xFEu << (8 * (boff + i));
-                        dEp[i] += 2ll * x[i];
+                        dEp[i] += x[i];
                     }
                 if (mask) L_S[(size_t)p * nq + q] = self ^ mask;
             };
@@ -475,18 +501,16 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
             // each draws word boff of its own chain's quad block, digit by digit.
             auto update_pk = [&](int p, auto rec, int32_t hp, uint32_t ord) __attribute__((always_inline)) {
                 const uint32_t self = L_S[p];
-                int32_t f[4];
-                ptc::quad_fields<DK>(rec, D, p, L_S, 1, 0, hp, f);
+                int32_t x[2];
+                ptc::quad_costs<ND, DK, 2>(rec, D, p, L_S, 1, 0, hp, self, x);
                 uint32_t k0 = a.k0, k1 = a.k1;
 #ifdef __OPTIMIZE__
                 asm volatile("" : "+s"(k0), "+s"(k1));
 #endif
-                int32_t x[2];
                 uint32_t d[2], th[2];
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
-                    x[i] = dev::spin_of(self, i) > 0 ? -f[i] : f[i];
-                    d[i] = x[i] > 0 ? ((uint32_t)x[i] & (kDigitSize - 1)) : 0u;
+                    d[i] = ((uint32_t)max(x[i], 0) >> SH) & (kDigitSize - 1);
                     th[i] = L_tab[d[i]];
                 }
                 bool acc[2];
@@ -494,13 +518,13 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
                     const dev::Words4 w0 = dev::philox(ord, t, quad, 2u << 24, k0, k1);
                     const dev::Words4 w1 = dev::philox(ord, t, quad1, 2u << 24, k0, k1);
                     acc[0] = (d[0] == 0) | (wsel(w0, boff) < th[0]);
-                    acc[1] = (d[1] == 0) | (wsel(w1, boff) < th[1]);
+                    acc[1] = (d[1] == 0) | (wsel(w1, boff1) < th[1]);
                 }
 #pragma unroll
                 for (int j = 1; j < ND; ++j) {
 #pragma unroll
                     for (int i = 0; i < 2; ++i) {
-                        d[i] = x[i] > 0 ? (((uint32_t)x[i] >> (kDigitBits * j)) & (kDigitSize - 1)) : 0u;
+                        d[i] = ((uint32_t)max(x[i], 0) >> (SH + kDigitBits * j)) & (kDigitSize - 1);
                         th[i] = L_tab[j * kDigitSize + d[i]];
                     }
                     if (d[0] != 0) {
@@ -509,7 +533,7 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
                     }
                     if (d[1] != 0) {
                         const dev::Words4 w = dev::philox(ord, t, quad1, (2u << 24) | (uint32_t)j, k0, k1);
-                        if (wsel(w, boff) >= th[1]) acc[1] = false;
+                        if (wsel(w, boff1) >= th[1]) acc[1] = false;
                     }
                 }
                 uint32_t mask = 0;
@@ -517,7 +541,7 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
                 for (int i = 0; i < 2; ++i)
                     if (acc[i]) {
                         mask |= 0xFEu << (8 * i);
-                        dEp[i] += 2ll * x[i];
+                        dEp[i] += x[i];
                     }
                 if (mask) L_S[p] = self ^ mask;
             };
@@ -534,8 +558,8 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
                 };
                 auto sites = [&](auto body) __attribute__((always_inline)) {
                     int p = cs[c] + pt;
-                    if (active && p < pe) fetch(p);
-                    for (; active && p < pe; p += nstr) {
+                    if (owner && p < pe) fetch(p);
+                    for (; owner && p < pe; p += nstr) {
                         uint32_t rr[DK];
 #pragma unroll
                         for (int u = 0; u < DK; ++u) rr[u] = rn[u];
@@ -556,9 +580,9 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
                         update(p, [&](int u, int) __attribute__((always_inline)) { return rr[u]; }, hp, od);
                     });
             } else if (pk) {
-                for (int p = cs[c] + pt; active && p < pe; p += nstr) update_pk(p, NBR, HPOS(p), (uint32_t)ORD(p));
+                for (int p = cs[c] + pt; owner && p < pe; p += nstr) update_pk(p, NBR, HPOS(p), (uint32_t)ORD(p));
             } else {
-                for (int p = cs[c] + pt; active && p < pe; p += nstr) update(p, NBR, HPOS(p), (uint32_t)ORD(p));
+                for (int p = cs[c] + pt; owner && p < pe; p += nstr) update(p, NBR, HPOS(p), (uint32_t)ORD(p));
             }
             __syncthreads();
             if constexpr (shadow::kOn) shadow_pass(c, false);
@@ -573,6 +597,8 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
             dE[0] += dEp[0];
             dE[1] += dEp[1];
         }
+#pragma unroll
+        for (int b = 0; b < 4; ++b) dE[b] = 2 * (dE[b] >> SH);  // a flip changes E by 2 x
         if (pow2) {
 #pragma unroll
             for (int b = 0; b < 4; ++b)
@@ -776,17 +802,18 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
         // disagreeing site v, E_v = sum of J s_v s_u over its agreeing neighbours u in
         // replica A, so the energy pass needs no neighbour reads (a cluster's change is
         // -2 sum over its sites of s_v h_v + E_v, as in the general pass below).
-        const bool esum = a.esum != 0;
+        const bool esum = MV == kMoveAny ? a.esum != 0 : true;
         constexpr int KB = DK > 0 ? DK : ptc::kRecBatch;
         const size_t pstride = (size_t)nq * 4;
-        for (int kq = kb; a.nw_icm > 0 && kq < ke; kq += a.nw_icm) {
-            const int nb = min(a.nw_icm, ke - kq);
-            unsigned char *pa[kIcmBatch], *pb[kIcmBatch];
+        if constexpr (MV != kMoveNone)
+        for (int kq = kb; a.nw_icm > 0 && kq < ke; kq += kBatch == 1 ? 1 : a.nw_icm) {
+            const int nb = kBatch == 1 ? 1 : min(a.nw_icm, ke - kq);
+            unsigned char *pa[kBatch], *pb[kBatch];
 #pragma unroll
-            for (int j = 0; j < kIcmBatch; ++j) {
-                const int o = min(kq + j, ke - 1) - s0 + boff;
-                pa[j] = pk ? Sb : Sb + (size_t)(o >> 2) * 4 + (o & 3);
-                pb[j] = pk ? Sb + 1 : Sb + (size_t)(qpc + (o >> 2)) * 4 + (o & 3);
+            for (int j = 0; j < kBatch; ++j) {
+                const int o = min(kq + j, ke - 1) - s0;
+                pa[j] = pk ? Sb : Sb + o + boff;
+                pb[j] = pk ? Sb + 1 : Sb + 4 * qpc + o + boff1;
             }
             auto dis = [=](int j, int p) __attribute__((always_inline)) -> bool {
                 return pa[j][(size_t)p * pstride] != pb[j][(size_t)p * pstride];
@@ -795,7 +822,7 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
             // pairs lie in one quad word per chain, one XOR of the two words gives them all
             // (a byte is 0xFE where the replicas differ and 0 where they agree).
             const int o0 = kq - s0 + boff, qa0 = o0 >> 2, off0 = o0 & 3;
-            const bool word_dis = off0 + nb <= 4;
+            const bool word_dis = off0 + nb <= 4 && boff1 == boff;
             const uint32_t pmask = (1u << nb) - 1u;
             // Chain 0's spin bytes of the batch's pairs at position p (byte j: pair j) and
             // their disagreement bits.
@@ -819,7 +846,7 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
                 wa = 0;
                 db = 0;
 #pragma unroll
-                for (int j = 0; j < kIcmBatch; ++j) {
+                for (int j = 0; j < kBatch; ++j) {
                     const unsigned char x = pa[j][(size_t)p * pstride], y = pb[j][(size_t)p * pstride];
                     wa |= (uint32_t)x << (8 * j);
                     if (j < nb && x != y) db |= 1u << j;
@@ -840,7 +867,7 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
                 }
                 uint32_t m = 0;
 #pragma unroll
-                for (int j = 0; j < kIcmBatch; ++j)
+                for (int j = 0; j < kBatch; ++j)
                     if (j < nb && dis(j, p)) m |= 1u << j;
                 return m;
             };
@@ -858,7 +885,7 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
 #pragma unroll
-                    for (int j = 0; j < kIcmBatch; ++j) {
+                    for (int j = 0; j < kBatch; ++j) {
                         if (j >= nb) break;
                         const unsigned long long m = __ballot((db[u] >> j) & 1u);
                         if (lane == 0 && c0 + u * nw < nchunks) L_dmask[(size_t)j * nchunks + c0 + u * nw] = m;
@@ -977,7 +1004,7 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
                             if (k0 + uu >= Dn) break;
                             const int u = (int)(rr[uu] >> 16);
 #pragma unroll
-                            for (int j = 0; j < kIcmBatch; ++j) {
+                            for (int j = 0; j < kBatch; ++j) {
                                 if (j >= nb) break;
                                 const bool f = (fb[uu] >> j) & 1u;
                                 const unsigned long long msk = __ballot(f);
@@ -1019,20 +1046,20 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
             // agreeing neighbours J s_u) per site (a neighbour across a J != 0 edge is in
             // the cluster exactly when it disagrees); the replicas are only written after
             // every site has been read
-            uint32_t root[kIcmBatch];
+            uint32_t root[kBatch];
 #pragma unroll
-            for (int j = 0; j < kIcmBatch; ++j) {
+            for (int j = 0; j < kBatch; ++j) {
                 const int sp = j < nb ? L_misc[j] : -1;
                 root[j] = sp >= 0 ? ptc::uf_find(L_parent + (size_t)j * n16, (uint32_t)sp) : 0xffffffffu;
             }
-            long long dA[kIcmBatch];
+            long long dA[kBatch];
 #pragma unroll
-            for (int j = 0; j < kIcmBatch; ++j) dA[j] = 0;
+            for (int j = 0; j < kBatch; ++j) dA[j] = 0;
             auto energy_site = [&](int p, auto rec, int32_t hp) __attribute__((always_inline)) {
                 unsigned in = 0;
                 const uint32_t dpb = dis_bits(p);
 #pragma unroll
-                for (int j = 0; j < kIcmBatch; ++j)
+                for (int j = 0; j < kBatch; ++j)
                     if (root[j] != 0xffffffffu && ((dpb >> j) & 1u) &&
                         ptc::uf_find(L_parent + (size_t)j * n16, (uint32_t)p) == root[j])
                         in |= 1u << j;
@@ -1041,9 +1068,9 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
                 // cluster); replica B's field is the same (it agrees with A there) and its
                 // spin at p is -s_A, so its energy change is -dA: the pair energy is
                 // conserved exactly
-                int32_t fA[kIcmBatch];
+                int32_t fA[kBatch];
 #pragma unroll
-                for (int j = 0; j < kIcmBatch; ++j) fA[j] = hp;
+                for (int j = 0; j < kBatch; ++j) fA[j] = hp;
                 for (int k0 = 0; k0 < Dn; k0 += KB) {
                     uint32_t rr[KB];
 #pragma unroll
@@ -1056,7 +1083,7 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
                         const int32_t Jv = (int32_t)(int16_t)(rr[uu] & 0xffffu);
                         if (k0 + uu >= Dn || Jv == 0) continue;
 #pragma unroll
-                        for (int j = 0; j < kIcmBatch; ++j)
+                        for (int j = 0; j < kBatch; ++j)
                             if (((in >> j) & 1u) && !((db[uu] >> j) & 1u))
                                 fA[j] += Jv * (int32_t)(int8_t)(wa[uu] >> (8 * j));
                     }
@@ -1064,7 +1091,7 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
                 uint32_t wp, dbp;
                 pair_bytes(p, wp, dbp);
 #pragma unroll
-                for (int j = 0; j < kIcmBatch; ++j)
+                for (int j = 0; j < kBatch; ++j)
                     if ((in >> j) & 1u) {
                         atomicOr(&memb[(size_t)j * vstr + (p >> 5)], 1u << (p & 31));
                         dA[j] += -2ll * (int32_t)(int8_t)(wp >> (8 * j)) * (long long)fA[j];
@@ -1120,7 +1147,7 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
                 }
             }
 #pragma unroll
-            for (int j = 0; j < kIcmBatch; ++j) {
+            for (int j = 0; j < kBatch; ++j) {
                 if (j >= nb) break;
                 const long long sa = wave_sum(dA[j]), sb = -sa;
                 const int la = kq + j - s0, lb = mg + la;
@@ -1133,7 +1160,7 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
             // flip the clusters in both replicas (the gathered-terms pass flipped its own)
             for (int p = tid; !esum && p < n; p += T)
 #pragma unroll
-                for (int j = 0; j < kIcmBatch; ++j)
+                for (int j = 0; j < kBatch; ++j)
                     if (j < nb && ((memb[(size_t)j * vstr + (p >> 5)] >> (p & 31)) & 1u)) {
                         pa[j][(size_t)p * pstride] = (unsigned char)(-(int)(int8_t)pa[j][(size_t)p * pstride]);
                         pb[j][(size_t)p * pstride] = (unsigned char)(-(int)(int8_t)pb[j][(size_t)p * pstride]);
@@ -1311,20 +1338,37 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
     }
 }
 
-template <int ND, bool BIG>
-void *ptx_entry(int D) {
-    if (D == 6) return reinterpret_cast<void *>(ptx_kernel<ND, BIG, 6>);
-    return reinterpret_cast<void *>(ptx_kernel<ND, BIG, 0>);
+// The kernel of a launch: instances with kSiteRecs records and up to two digits have
+// their move compiled in, the others decide it at run time.
+template <int ND, bool BIG, int DK>
+void *ptx_entry(int move) {
+    if constexpr (DK > 0 && ND <= 2) {
+        if (move == kMoveNone) return reinterpret_cast<void *>(ptx_kernel<ND, BIG, DK, kMoveNone>);
+        if (move == kMoveSingle) return reinterpret_cast<void *>(ptx_kernel<ND, BIG, DK, kMoveSingle>);
+        if constexpr (BIG)
+            if (move == kMovePacked) return reinterpret_cast<void *>(ptx_kernel<ND, BIG, DK, kMovePacked>);
+    }
+    return reinterpret_cast<void *>(ptx_kernel<ND, BIG, DK, kMoveAny>);
 }
 
-void *ptx_fn(int nd, bool big, int D) {
-    switch (nd) {
+template <int ND>
+void *ptx_pick(bool big, int D, int move) {
+    if (D == kSiteRecs) return big ? ptx_entry<ND, true, kSiteRecs>(move) : ptx_entry<ND, false, kSiteRecs>(move);
+    return big ? ptx_entry<ND, true, 0>(move) : ptx_entry<ND, false, 0>(move);
+}
+
+void *ptx_fn(const PtxShape &s) {
+    const int move = s.nw_icm == 0                        ? kMoveNone
+                     : !s.esum                            ? kMoveAny
+                     : ptx_packed(s.big, s.m, s.chains) ? kMovePacked
+                                                          : kMoveSingle;
+    switch (s.nd) {
         case 1:
-            return big ? ptx_entry<1, true>(D) : ptx_entry<1, false>(D);
+            return ptx_pick<1>(s.big, s.D, move);
         case 2:
-            return big ? ptx_entry<2, true>(D) : ptx_entry<2, false>(D);
+            return ptx_pick<2>(s.big, s.D, move);
         case 3:
-            return big ? ptx_entry<3, true>(D) : ptx_entry<3, false>(D);
+            return ptx_pick<3>(s.big, s.D, move);
         default:
             return nullptr;
     }
@@ -1334,12 +1378,14 @@ void *ptx_fn(int nd, bool big, int D) {
 
 int ptx_msg_words(int n) { return 4 + (n + 1) / 2; }
 
-size_t ptx_lds_bytes(int n, int D, int m, int chains, int row_len, int nw_icm, bool big, bool esum) {
-    return ptx_layout(n, D, m, chains, row_len, nw_icm, big, esum, nullptr, nullptr);
+int ptx_words_per_site(int K, int m, int chains) { return chains * ptx_chain_words(K, m); }
+
+size_t ptx_lds_bytes(const PtxShape &s) {
+    return ptx_layout(s.n, s.D, s.K, s.m, s.chains, s.row_len, s.nw_icm, s.big, s.esum, nullptr, nullptr);
 }
 
-hipError_t ptx_max_groups_resident(int nd, bool big, int D, int threads, size_t lds, int *blocks_per_cu) {
-    void *f = ptx_fn(nd, big, D);
+hipError_t ptx_max_groups_resident(const PtxShape &s, int threads, size_t lds, int *blocks_per_cu) {
+    void *f = ptx_fn(s);
     if (!f) return hipErrorInvalidValue;
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, f, threads, lds);
 }
@@ -1383,8 +1429,9 @@ hipError_t launch_ptx(const PtxLaunch &P, hipStream_t s) {
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    const size_t lds = ptx_lds_bytes(P.n, P.D, P.m, P.chains, P.row_len, P.nw_icm, P.big, P.esum);
-    void *f = ptx_fn(P.nd, P.big, P.D);
+    const PtxShape shape{P.n, P.D, P.K, P.m, P.chains, P.row_len, P.nd, P.nw_icm, P.big, P.esum};
+    const size_t lds = ptx_lds_bytes(shape);
+    void *f = ptx_fn(shape);
     if (!f) return hipErrorInvalidValue;
     void *args[] = {&a};
     return hipLaunchKernel(f, dim3(P.runs * P.G), dim3(P.threads), args, lds, s);
