@@ -401,6 +401,10 @@ bool sa_big_env() {  // SPVAR_SA_BIG=1: the global-memory instance even when the
     const char *v = getenv("SPVAR_SA_BIG");
     return v && v[0] == '1';
 }
+int sa_held_env() {  // SPVAR_SA_HELD=0: never; =<q>: with q quads per workgroup where it fits
+    const char *v = getenv("SPVAR_SA_HELD");
+    return v && *v ? atoi(v) : -1;
+}
 int sa_wpl_env() {
     const char *v = getenv("SPVAR_SA_WPL");
     return v ? atoi(v) : 0;
@@ -524,13 +528,19 @@ spv_status sample_inst(spv_ctx *ctx, const Inst *P, const double *betas, int32_t
     if (reads == 0) return SPV_OK;
     if (!energies || (P->n > 0 && !spins)) return set_err(c, SPV_EINVAL, "NULL spins/energies");
     if (P->n == 0) return hip_check(c, hipMemsetAsync(energies, 0, 8ull * reads, stream), "memset");
-    const int n = P->n, D = P->max_degree;
     const int nd = digits_for(P->x_bound);
     if (nd > 3) return set_err(c, SPV_ERANGE, "x_bound=%d needs %d digits (max 3)", P->x_bound, nd);
     const int row_len = table_row_len(P->x_bound);
+    const bool swar = sa_use_swar(nd, row_len);
+    // The byte-parallel body has straight-line variants for 4, 6 and 8 records a site, whose
+    // LDS blocks are no larger than those of 3, 5 and 7: an odd longest row is padded to the
+    // next (zero-coupling records).
+    Inst Q = *P;
+    if (swar && (Q.max_degree == 3 || Q.max_degree == 5 || Q.max_degree == 7)) ++Q.max_degree;
+    const int n = Q.n, D = Q.max_degree;
     st = ensure(c, c->image, image_words(n, D) * 4);
     if (st) return st;
-    hipError_t e = launch_prep(P, static_cast<int32_t *>(c->image.p), stream);
+    hipError_t e = launch_prep(&Q, static_cast<int32_t *>(c->image.p), stream);
     if (e != hipSuccess) return hip_check(c, e, "prep launch");
     if (sweeps > 0) {
         st = upload_tables(c, c->tables, betas, sweeps, 2, P->scale_log2, nd, row_len, stream);
@@ -561,7 +571,6 @@ spv_status sample_inst(spv_ctx *ctx, const Inst *P, const double *betas, int32_t
     // 512 threads when the workgroups outnumber the CUs, else 1024 (measured on the
     // L = 10 and L = 20 Gaussian cubes: more sites in flight per CU when few
     // workgroups share it), and no more threads than sites.
-    const bool swar = sa_use_swar(nd, row_len);
     const bool saturated = ((reads + 3) / 4 + 1) / 2 > c->num_cus;
     int qw = sa_qw_env();
     if (qw <= 0) qw = swar ? 2 : 1;
@@ -602,6 +611,35 @@ spv_status sample_inst(spv_ctx *ctx, const Inst *P, const double *betas, int32_t
     L.wpl = (swar && wpl == 2 && qw == 2) ? 2 : 1;
     const int lanes_per_site = qw / L.wpl;
     L.threads = std::max(lanes_per_site, threads / lanes_per_site * lanes_per_site);
+    // Sites held in registers (2 to 4 classes of at most 1024 sites): the default where it
+    // applies, since it reads no records and waits for no row.  Measured against the bodies
+    // above, 1000 sweeps: N = 64, 100 / 10,000 reads 1.08 -> 0.67 / 1.86 -> 0.89 ms; Chimera
+    // N = 512, 1000 / 4000 reads 1.36 -> 0.85 / 1.85 -> 1.42; N = 1000, 1000 reads 2.22 ->
+    // 1.01; N = 1728, 5000 reads 12.1 -> 7.2; four classes, N = 125, 2000 reads 2.00 -> 1.30.
+    // Quads per workgroup: whole waves for small classes; two when the quads outnumber the
+    // CUs and the workgroup stays within 512 threads (N = 512, 10,000 reads x 2000 sweeps
+    // 5.59 ms, one quad 5.75, four 7.07).
+    const int held_qw = sa_held_env();
+    const bool shape_forced = sa_qw_env() > 0 || sa_threads_env() > 0 || sa_wpl_env() > 0 || sa_big_env();
+    if (held_qw != 0 && !shape_forced && swar && P->n_colours >= 2 && P->n_colours <= 4 &&
+        (D == 4 || D == 6 || D == 8)) {
+        int cmax = 0, counted = 0;
+        for (int k = 0; k < P->n_colours; ++k) {
+            cmax = std::max(cmax, (int)P->class_n[k]);
+            counted += P->class_n[k];
+        }
+        if (counted != n) cmax = n;  // not counted
+        int q = held_qw > 0 ? held_qw : std::max(1, 64 / cmax);
+        if (held_qw < 0 && q == 1 && (reads + 3) / 4 > c->num_cus && 2 * cmax <= 512) q = 2;
+        if (cmax * q <= 1024 && sa_held_lds_bytes(n, q) + 256 <= c->lds_max) {
+            L.held = true;
+            L.qw = qw = q;
+            L.wpl = 1;
+            L.threads = (cmax * q + 63) / 64 * 64;
+            L.global_instance = false;
+            L.big = nullptr;
+        }
+    }
     L.spin_limit = sa_spin_env();
     const int plan = sa_stream_env_off() ? 1 : sa_stream_plan(L, c->num_cus, sa_stream_env_grid());
     c->last_sa_shape[0] = L.threads;

@@ -18,29 +18,36 @@ struct Words4 {
     uint32_t w[4];
 };
 
-__device__ __forceinline__ Words4 philox(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
-                                         uint32_t k0, uint32_t k1) {
+// Rounds [first, first + N) on the counter words in place, keys (k0, k1) of round 0.
+template <int N>
+__device__ __forceinline__ void philox_rounds(uint32_t (&c)[4], int first, uint32_t k0, uint32_t k1) {
     constexpr uint32_t kMulA = 0xD2511F53u, kMulB = 0xCD9E8D57u;
     constexpr uint32_t kWeylA = 0x9E3779B9u, kWeylB = 0xBB67AE85u;
+    k0 += kWeylA * (uint32_t)first;
+    k1 += kWeylB * (uint32_t)first;
 #pragma unroll
-    for (int round = 0; round < 10; ++round) {
-        const uint64_t pa = (uint64_t)kMulA * c0;
-        const uint64_t pb = (uint64_t)kMulB * c2;
+    for (int round = 0; round < N; ++round) {
+        const uint64_t pa = (uint64_t)kMulA * c[0];
+        const uint64_t pb = (uint64_t)kMulB * c[2];
         // three-input xor in one gfx950 v_bitop3_b32 (truth table 0x96)
-        const uint32_t n0 = __builtin_amdgcn_bitop3_b32((uint32_t)(pb >> 32), c1, k0, 0x96);
-        const uint32_t n2 = __builtin_amdgcn_bitop3_b32((uint32_t)(pa >> 32), c3, k1, 0x96);
-        c1 = (uint32_t)pb;
-        c3 = (uint32_t)pa;
-        c0 = n0;
-        c2 = n2;
+        const uint32_t n0 = __builtin_amdgcn_bitop3_b32((uint32_t)(pb >> 32), c[1], k0, 0x96);
+        const uint32_t n2 = __builtin_amdgcn_bitop3_b32((uint32_t)(pa >> 32), c[3], k1, 0x96);
+        c[1] = (uint32_t)pb;
+        c[3] = (uint32_t)pa;
+        c[0] = n0;
+        c[2] = n2;
         k0 += kWeylA;
         k1 += kWeylB;
     }
+}
+
+__device__ __forceinline__ Words4 philox(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
+                                         uint32_t k0, uint32_t k1) {
+    uint32_t c[4] = {c0, c1, c2, c3};
+    philox_rounds<10>(c, 0, k0, k1);
     Words4 r;
-    r.w[0] = c0;
-    r.w[1] = c1;
-    r.w[2] = c2;
-    r.w[3] = c3;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r.w[i] = c[i];
     return r;
 }
 

@@ -228,6 +228,8 @@ struct SaLaunch {
     int qw;       // quads (4 replicas) per workgroup
     int threads;  // workgroup size
     int wpl = 1;  // byte-parallel body: quad words per lane (2 needs qw = 2)
+    bool held = false;  // byte-parallel body with every lane's sites in registers: 2 to 4 colour classes of
+                        // at most threads / qw sites, 4, 6 or 8 records a site
     int spin_limit = 1 << 22;  // streamed launch: bounded wait for a group's previous chunk
     bool global_instance = false;  // the instance stays in global memory (does not fit the LDS)
     unsigned char *big = nullptr;  // byte-parallel body with global_instance: its instance buffer
@@ -253,6 +255,7 @@ size_t sa_stream_bytes(int n, int reads, int qw);
 hipError_t launch_sa_stream(const SaLaunch &L, int plan, void *buf, hipStream_t s);
 int sa_stream_chunks_of(const SaLaunch &L, int plan);
 size_t sa_lds_bytes(int n, int D, int row_len, int qw, bool big = false);
+size_t sa_held_lds_bytes(int n, int qw);
 size_t sa_big_bytes(int n, int D);
 bool sa_use_swar(int nd, int row_len);
 

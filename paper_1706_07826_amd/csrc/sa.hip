@@ -146,6 +146,20 @@ __global__ __launch_bounds__(1024) void sa_kernel(core::SaItem a) {
     }
 }
 
+// Byte-parallel SA with every lane's sites held in registers (see SwarHeld).
+template <int DK, int NC>
+__global__ __launch_bounds__(1024) void sa_held_kernel(core::SaItem a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ int cs[kMaxColours + 1];
+    a.q0 = blockIdx.x * a.qw;
+    core::SwarLds L;
+    core::swar_big_layout(a.n, a.qw, &L, smem);
+    core::swar_load_colours(a, cs);
+    core::SwarHeld<DK, NC> held;
+    held.load(L, a, cs);
+    held.run(L, a, cs, core::SwarChunk());
+}
+
 // Streamed byte-parallel SA: resident workgroups take (group of qw quads, chunk of
 // sweeps) tasks from a counter in chunk-major order, so that the replicas are
 // spread over the whole device however their count divides into workgroups.  A
@@ -179,13 +193,17 @@ __device__ __forceinline__ uint32_t spin_word(uint32_t nib) { return ((nib * 0x0
 // Every branch of the task loop depends on wave-uniform values only (the task
 // index is read back with readfirstlane), so that no lane can be split from its
 // wave across loop iterations and barriers.
-template <int DK, int W, bool BIG = false>
-__global__ __launch_bounds__(1024) void sa_stream_kernel(StreamArgs s) {
+// NC > 0: the body with NC classes' sites held in registers (W = 1).
+template <int DK, int W, bool BIG, int NC>
+__device__ __forceinline__ void sa_stream(StreamArgs s) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int cs[kMaxColours + 1];
     __shared__ int task_s, late_s, poison_s;
     core::SwarLds L;
-    if constexpr (BIG) {
+    if constexpr (NC > 0) {
+        core::swar_big_layout(s.a.n, s.a.qw, &L, smem);
+        core::swar_load_colours(s.a, cs);
+    } else if constexpr (BIG) {
         core::swar_big_layout(s.a.n, s.a.qw, &L, smem);
         core::swar_bind_big(&L, s.a.big, s.a.n, s.a.D);
         core::swar_load_colours(s.a, cs);
@@ -255,7 +273,14 @@ __global__ __launch_bounds__(1024) void sa_stream_kernel(StreamArgs s) {
         ch.resume = k > 0 && !late;
         ch.keep = k + 1 < s.K;
         ch.poisoned = poisoned;
-        core::swar_run<DK, W, BIG>(L, it, cs, ch);  // ends with a barrier
+        if constexpr (NC > 0) {
+            // the sites are read again for every task: kept in registers over the whole
+            // loop they cost the sweeps more of them than the reads cost time
+            core::SwarHeld<DK, NC> held;
+            held.load(L, it, cs);
+            held.run(L, it, cs, ch);
+        } else
+            core::swar_run<DK, W, BIG>(L, it, cs, ch);  // ends with a barrier
         if (ch.keep) {
             const uint32_t tag = (poisoned ? kTagPoison : 0u) | (uint32_t)(k + 1);
             for (int h = tid; h < hw; h += T) {
@@ -267,6 +292,18 @@ __global__ __launch_bounds__(1024) void sa_stream_kernel(StreamArgs s) {
             }
         }
     }
+}
+
+template <int DK, int W, bool BIG = false>
+__global__ __launch_bounds__(1024) void sa_stream_kernel(StreamArgs s) {
+    sa_stream<DK, W, BIG, 0>(s);
+}
+
+// Seven waves per SIMD with two classes: what registers this costs outside the sweeps is
+// spilled there.
+template <int DK, int NC>
+__global__ __launch_bounds__(1024, NC == 2 ? 7 : 4) void sa_held_stream_kernel(StreamArgs s) {
+    sa_stream<DK, 1, false, NC>(s);
 }
 
 // Task counter and tags back to zero (no word then matches a chunk tag >= 1).
@@ -351,6 +388,12 @@ size_t sa_lds_bytes(int n, int D, int row_len, int qw, bool big) {
                : core::sa_layout(n, D, row_len, qw, nullptr, nullptr);
 }
 
+size_t sa_held_lds_bytes(int n, int qw) { return core::swar_big_lds_bytes(n, qw); }
+
+static size_t launch_lds(const SaLaunch &L) {
+    return L.held ? sa_held_lds_bytes(L.n, L.qw) : sa_lds_bytes(L.n, L.D, L.row_len, L.qw, L.global_instance);
+}
+
 size_t sa_big_bytes(int n, int D) { return core::swar_big_bytes(n, D); }
 
 static hipError_t launch_big_prep(const core::SaItem &a, hipStream_t s) {
@@ -360,6 +403,29 @@ static hipError_t launch_big_prep(const core::SaItem &a, hipStream_t s) {
     return hipGetLastError();
 }
 
+// The kernels of the held-sites body for a launch's record count (4, 6 or 8) and classes.
+using HeldFn = void (*)(core::SaItem);
+using HeldStreamFn = void (*)(StreamArgs);
+template <int DK>
+static HeldFn held_fn_of(int C) {
+    return C == 2 ? sa_held_kernel<DK, 2> : C == 3 ? sa_held_kernel<DK, 3> : C == 4 ? sa_held_kernel<DK, 4> : nullptr;
+}
+template <int DK>
+static HeldStreamFn held_stream_fn_of(int C) {
+    return C == 2   ? sa_held_stream_kernel<DK, 2>
+           : C == 3 ? sa_held_stream_kernel<DK, 3>
+           : C == 4 ? sa_held_stream_kernel<DK, 4>
+                    : nullptr;
+}
+static HeldFn held_fn(const SaLaunch &L) {
+    return L.D == 4 ? held_fn_of<4>(L.C) : L.D == 6 ? held_fn_of<6>(L.C) : L.D == 8 ? held_fn_of<8>(L.C) : nullptr;
+}
+static HeldStreamFn held_stream_fn(const SaLaunch &L) {
+    return L.D == 4   ? held_stream_fn_of<4>(L.C)
+           : L.D == 6 ? held_stream_fn_of<6>(L.C)
+           : L.D == 8 ? held_stream_fn_of<8>(L.C)
+                      : nullptr;
+}
 hipError_t launch_sa(const SaLaunch &L, hipStream_t s, size_t lds_limit) {
     core::SaItem a;
     a.image = L.image;
@@ -382,7 +448,7 @@ hipError_t launch_sa(const SaLaunch &L, hipStream_t s, size_t lds_limit) {
     a.big = L.big;
     const bool swar = sa_use_swar(L.nd, L.row_len);
     const bool big = L.global_instance;
-    const size_t lds = sa_lds_bytes(L.n, L.D, L.row_len, L.qw, big);
+    const size_t lds = launch_lds(L);
     if (lds > lds_limit || (big && swar && L.big == nullptr)) return hipErrorInvalidValue;
     const int quads = (L.reads + 3) / 4;
     const int grid = (quads + L.qw - 1) / L.qw;
@@ -418,6 +484,12 @@ hipError_t launch_sa(const SaLaunch &L, hipStream_t s, size_t lds_limit) {
             hipLaunchKernelGGL((sa_kernel<0, 0, true>), dim3(grid), dim3(L.threads), lds, s, a);
         return hipGetLastError();
     }
+    if (swar && L.held) {
+        const HeldFn f = held_fn(L);
+        if (!f) return hipErrorInvalidValue;
+        hipLaunchKernelGGL(f, dim3(grid), dim3(L.threads), lds, s, a);
+        return hipGetLastError();
+    }
     switch (sa_use_swar(L.nd, L.row_len) ? 0 : L.nd) {
         case 0:
             if (L.D == 6)
@@ -449,7 +521,6 @@ template <int DK, int W, bool BIG>
 static hipError_t stream_occupancy(int threads, size_t lds, int *per_cu) {
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, sa_stream_kernel<DK, W, BIG>, threads, lds);
 }
-
 // Chunks per group: the fewest (sweeps per chunk >= kStreamMinSweeps) whose tasks
 // fill the resident workgroups to kStreamFill, else the best filling count.  Every
 // chunk boundary moves a group's spin words through global memory once each way.
@@ -490,12 +561,15 @@ int sa_stream_plan(const SaLaunch &L, int num_cus, int force_grid) {
     const int G = (quads + L.qw - 1) / L.qw;
     const int W = (L.wpl == 2 && L.qw == 2) ? 2 : 1;
     const bool big = L.global_instance;
-    const size_t lds = sa_lds_bytes(L.n, L.D, L.row_len, L.qw, big);
+    const size_t lds = launch_lds(L);
     const int dk = (L.D == 6 || L.D == 4 || L.D == 8) ? L.D : 0;
     int per_cu = 0;
     hipError_t e;
 #define SPV_OCC(D_, W_) e = stream_occupancy<D_, W_, false>(L.threads, lds, &per_cu)
-    if (big) {
+    if (L.held) {
+        const HeldStreamFn f = held_stream_fn(L);
+        e = f ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, L.threads, lds) : hipErrorInvalidValue;
+    } else if (big) {
         if (dk == 6) {
             if (W == 2) e = stream_occupancy<6, 2, true>(L.threads, lds, &per_cu);
             else e = stream_occupancy<6, 1, true>(L.threads, lds, &per_cu);
@@ -528,7 +602,7 @@ hipError_t launch_sa_stream(const SaLaunch &L, int plan, void *buf, hipStream_t 
     const int G = (quads + L.qw - 1) / L.qw;
     const int W = (L.wpl == 2 && L.qw == 2) ? 2 : 1;
     const bool big = L.big != nullptr;
-    const size_t lds = sa_lds_bytes(L.n, L.D, L.row_len, L.qw, big);
+    const size_t lds = launch_lds(L);
     const int dk = (L.D == 6 || L.D == 4 || L.D == 8) ? L.D : 0;
     StreamArgs a;
     a.a.image = L.image;
@@ -562,6 +636,12 @@ hipError_t launch_sa_stream(const SaLaunch &L, int plan, void *buf, hipStream_t 
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int grid = std::min(resident, G * a.K);
+    if (L.held) {
+        const HeldStreamFn f = held_stream_fn(L);
+        if (!f) return hipErrorInvalidValue;
+        hipLaunchKernelGGL(f, dim3(grid), dim3(L.threads), lds, s, a);
+        return hipGetLastError();
+    }
     if (big) {
         e = launch_big_prep(a.a, s);
         if (e != hipSuccess) return e;

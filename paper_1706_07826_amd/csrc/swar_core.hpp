@@ -204,6 +204,13 @@ __device__ __forceinline__ void swar_store(uint32_t *S, uint32_t idx, uint32_t i
 typedef unsigned short swar_u16x2 __attribute__((ext_vector_type(2)));
 typedef short swar_i16x2 __attribute__((ext_vector_type(2)));
 
+// 8 P + c in both halves, as one instruction (written out, the product becomes a shift).
+__device__ __forceinline__ swar_u16x2 swar_mad8(uint32_t P, swar_u16x2 c) {
+    uint32_t r;
+    asm("v_pk_mad_u16 %0, %1, 8, %2 op_sel_hi:[1,0,1]" : "=v"(r) : "v"(P), "v"(__builtin_bit_cast(uint32_t, c)));
+    return __builtin_bit_cast(swar_u16x2, r);
+}
+
 // 4x = -4 s f for the four replicas of a word, as two pairs of int16 (replicas 0, 1 and 2, 3):
 // 4f = 4 cp + 8 P_b fits 16 bits (|f| <= x_bound <= 255), and the spin byte masks, widened to
 // 16 bits, negate it where the spin is +1.  `cp2` holds 4 cp in both halves.
@@ -213,11 +220,44 @@ __device__ __forceinline__ void swar_x16(uint32_t P, uint32_t self, uint32_t cp2
     const uint32_t mlo = __builtin_amdgcn_perm(self, self, 0x01010000u);
     const uint32_t mhi = __builtin_amdgcn_perm(self, self, 0x03030202u);
     const swar_u16x2 c = __builtin_bit_cast(swar_u16x2, cp2);
-    const swar_u16x2 flo = __builtin_bit_cast(swar_u16x2, Plo) * (unsigned short)8 + c;
-    const swar_u16x2 fhi = __builtin_bit_cast(swar_u16x2, Phi) * (unsigned short)8 + c;
+    const swar_u16x2 flo = swar_mad8(Plo, c), fhi = swar_mad8(Phi, c);
     const swar_u16x2 ml = __builtin_bit_cast(swar_u16x2, mlo), mh = __builtin_bit_cast(swar_u16x2, mhi);
     *lo = __builtin_bit_cast(swar_i16x2, (swar_u16x2)((flo ^ ml) - ml));
     *hi = __builtin_bit_cast(swar_i16x2, (swar_u16x2)((fhi ^ mh) - mh));
+}
+
+// `self` with the bytes of the accepted replicas complemented: replica e is accepted where
+// 4x = o[e] <= 0 or its word is below its threshold.  Each byte is selected in place (a
+// conditional move that writes one byte of the word and keeps the others) from the word
+// or its complement.  The first wait is the distance a vector compare into the condition
+// register needs before it is read as a mask.
+__device__ __forceinline__ uint32_t swar_flip(uint32_t self, const int32_t (&o)[4], const uint32_t (&w)[4],
+                                              const uint32_t (&th)[4]) {
+    const uint32_t inv = ~self;
+#ifdef __OPTIMIZE__
+    unsigned long long a[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        a[e] = __builtin_amdgcn_ballot_w64(o[e] <= 0) | __builtin_amdgcn_ballot_w64(w[e] < th[e]);
+    uint32_t r;
+    asm("s_mov_b64 vcc, %3\n\t"
+        "s_nop 1\n\t"
+        "v_cndmask_b32_sdwa %0, %1, %2, vcc dst_sel:BYTE_0 dst_unused:UNUSED_PAD src0_sel:BYTE_0 src1_sel:BYTE_0\n\t"
+        "s_mov_b64 vcc, %4\n\t"
+        "v_cndmask_b32_sdwa %0, %1, %2, vcc dst_sel:BYTE_1 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_1 src1_sel:BYTE_1\n\t"
+        "s_mov_b64 vcc, %5\n\t"
+        "v_cndmask_b32_sdwa %0, %1, %2, vcc dst_sel:BYTE_2 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_2 src1_sel:BYTE_2\n\t"
+        "s_mov_b64 vcc, %6\n\t"
+        "v_cndmask_b32_sdwa %0, %1, %2, vcc dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:BYTE_3 src1_sel:BYTE_3"
+        : "=&v"(r)
+        : "v"(self), "v"(inv), "s"(a[0]), "s"(a[1]), "s"(a[2]), "s"(a[3])
+        : "vcc");
+    return r;
+#else
+    uint32_t r = 0;
+    for (int e = 0; e < 4; ++e) r |= (((o[e] <= 0) | (w[e] < th[e])) ? inv : self) & (0xFFu << (8 * e));
+    return r;
+#endif
 }
 
 // A contiguous range of sweeps of one workgroup's replicas.  The whole schedule
@@ -233,6 +273,51 @@ struct SwarChunk {
 
 // Energy written for every read of a workgroup whose chunks lost their order.
 constexpr long long kSwarPoisonEnergy = INT64_MIN;
+
+// Philox start of a word: byte mask of replicas 4 quad + b, +1 where bit 31 is set.
+__device__ __forceinline__ uint32_t swar_start_word(uint32_t i, uint32_t quad, uint32_t k0, uint32_t k1) {
+    const dev::Words4 w = dev::philox(i, 0u, quad, 1u << 24, k0, k1);
+    uint32_t word = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) word |= ((w.w[e] >> 31) ? 0xFFu : 0x00u) << (8 * e);
+    return word;
+}
+
+// Caller states of the workgroup's reads into S and ~S (reads beyond the last: +1).
+__device__ __forceinline__ void swar_load_init(const SwarLds &L, const SaItem &a) {
+    const int n = a.n, qw = a.qw, T = blockDim.x;
+    const size_t inv = (size_t)n * (size_t)qw;
+    const int32_t *pos_of = a.image + kImgHeader + n;
+    unsigned char *Sb = reinterpret_cast<unsigned char *>(L.S);
+    for (int idx = threadIdx.x; idx < 4 * qw * n; idx += T) {
+        const int rl = idx / n, i = idx - rl * n;
+        const int r = 4 * a.q0 + rl;
+        unsigned char v = 0xFF;
+        if (r < a.reads) v = a.init[(size_t)r * n + i] > 0 ? 0xFF : 0x00;
+        const size_t at = ((size_t)pos_of[i] * qw + (rl >> 2)) * 4 + (rl & 3);
+        Sb[at] = v;
+        Sb[at + 4 * inv] = (unsigned char)~v;
+    }
+}
+
+// Energies (from the doubled sums in E2) and spins of the workgroup's reads, in original
+// variable order.  Ends with a barrier.
+__device__ __forceinline__ void swar_write_sample(const SwarLds &L, const SaItem &a, bool poisoned) {
+    const int n = a.n, qw = a.qw, T = blockDim.x, tid = threadIdx.x, q0 = a.q0;
+    for (int rl = tid; rl < 4 * qw; rl += T) {
+        const int r = 4 * q0 + rl;
+        if (r < a.reads) a.energies[r] = poisoned ? kSwarPoisonEnergy : ((long long)L.E2[rl]) / 2;
+    }
+    const int32_t *pos_of = a.image + kImgHeader + n;
+    const unsigned char *Sb = reinterpret_cast<const unsigned char *>(L.S);
+    for (int idx = tid; idx < 4 * qw * n; idx += T) {
+        const int rl = idx / n, i = idx - rl * n;
+        const int r = 4 * q0 + rl;
+        if (r < a.reads)
+            a.out[(size_t)r * n + i] = Sb[((size_t)pos_of[i] * qw + (rl >> 2)) * 4 + (rl & 3)] ? 1 : -1;
+    }
+    __syncthreads();
+}
 
 // W = quad words per lane: 1, or 2 when qw = 2 and a lane holds its site's whole
 // row (the neighbour addresses are then the records' addresses as they stand).
@@ -262,25 +347,11 @@ __device__ void swar_run(const SwarLds &L, const SaItem &a, const int *cs, const
     } else if (a.init == nullptr) {
         for (int p = slot; active && p < n; p += nslots)
 #pragma unroll
-            for (int b = 0; b < W; ++b) {
-                const dev::Words4 w = dev::philox(L.co[p].y, 0u, (uint32_t)(q0 + qa + b), 1u << 24, a.k0, a.k1);
-                uint32_t word = 0;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) word |= ((w.w[e] >> 31) ? 0xFFu : 0x00u) << (8 * e);
-                swar_store(L.S, (uint32_t)p * (uint32_t)qw + (uint32_t)(qa + b), inv, word);
-            }
+            for (int b = 0; b < W; ++b)
+                swar_store(L.S, (uint32_t)p * (uint32_t)qw + (uint32_t)(qa + b), inv,
+                           swar_start_word(L.co[p].y, (uint32_t)(q0 + qa + b), a.k0, a.k1));
     } else {
-        const int32_t *pos_of = a.image + kImgHeader + n;
-        unsigned char *Sb = reinterpret_cast<unsigned char *>(L.S);
-        for (int idx = tid; idx < 4 * qw * n; idx += T) {
-            const int rl = idx / n, i = idx - rl * n;
-            const int r = 4 * q0 + rl;
-            unsigned char v = 0xFF;
-            if (r < a.reads) v = a.init[(size_t)r * n + i] > 0 ? 0xFF : 0x00;
-            const size_t at = ((size_t)pos_of[i] * qw + (rl >> 2)) * 4 + (rl & 3);
-            Sb[at] = v;
-            Sb[at + 4 * inv] = (unsigned char)~v;
-        }
+        swar_load_init(L, a);
     }
     __syncthreads();
     const shadow::Pass sh = shadow::begin(inv);
@@ -397,20 +468,187 @@ __device__ void swar_run(const SwarLds &L, const SaItem &a, const int *cs, const
                 for (int e = 0; e < 4; ++e) atomicAdd(&L.E2[(qa + b) * 4 + e], (unsigned long long)e2[b][e]);
     }
     __syncthreads();
-    for (int rl = tid; rl < 4 * qw; rl += T) {
-        const int r = 4 * q0 + rl;
-        if (r < a.reads) a.energies[r] = ch.poisoned ? kSwarPoisonEnergy : ((long long)L.E2[rl]) / 2;
-    }
-    const int32_t *pos_of = a.image + kImgHeader + n;
-    const unsigned char *Sb = reinterpret_cast<const unsigned char *>(L.S);
-    for (int idx = tid; idx < 4 * qw * n; idx += T) {
-        const int rl = idx / n, i = idx - rl * n;
-        const int r = 4 * q0 + rl;
-        if (r < a.reads)
-            a.out[(size_t)r * n + i] = Sb[((size_t)pos_of[i] * qw + (rl >> 2)) * 4 + (rl & 3)] ? 1 : -1;
-    }
-    __syncthreads();
+    swar_write_sample(L, a, ch.poisoned);
 }
+
+// Body for instances of NC = 2 to 4 colour classes whose passes are at most one word per
+// lane (class size x qw <= threads; DK records a site).  A lane keeps its site of every
+// class in registers (neighbour addresses, couplings, constants), so LDS holds only the
+// acceptance rows and the spins, a word costs its six or so neighbour reads, four threshold
+// reads and 72 vector instructions, and a pass of a workgroup that has its SIMDs to itself
+// is a short chain of latencies: half of a word's random rounds run behind the neighbour
+// reads and half behind the threshold reads, and the next sweep's acceptance row is loaded
+// a sweep ahead.
+template <int DK, int NC>
+struct SwarHeld {
+    struct Mine {    // the lane's site of one class
+        uint32_t adr[DK];  // LDS addresses of its neighbours' words (S or ~S), this lane's quad
+        uint32_t jr[DK];   // |J| x 0x01010101
+        uint32_t c2;       // 4 (h - sum |J|) in both 16-bit halves
+        uint32_t ord, at;  // variable index, word index
+        bool on;
+    };
+    Mine site[NC];
+    int qa;  // quad of the workgroup
+
+    __device__ __forceinline__ void load(const SwarLds &L, const SaItem &a, const int *cs) {
+        const int n = a.n, qw = a.qw, T = blockDim.x, tid = threadIdx.x;
+        const int slot = tid / qw;
+        qa = tid - slot * qw;
+        const bool active = slot < T / qw;
+        const uint32_t inv = (uint32_t)n * (uint32_t)qw;
+        const uint32_t sa = swar_lds_addr(L.S) + 4u * (uint32_t)qa;
+        const int32_t *img = a.image;
+        const uint32_t *recs = reinterpret_cast<const uint32_t *>(img + kImgHeader + 3 * n);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            Mine &m = site[c];
+            int p = cs[c] + slot;
+            m.on = active && p < cs[c + 1];
+            p = m.on ? p : 0;
+            m.at = (uint32_t)p * (uint32_t)qw + (uint32_t)qa;
+            const int32_t h = img[kImgHeader + 2 * n + p];
+            m.ord = (uint32_t)img[kImgHeader + p];
+            int32_t sum = 0;
+#pragma unroll
+            for (int k = 0; k < DK; ++k) {
+                const uint32_t r = recs[(size_t)p * DK + k];
+                const int32_t J = (int32_t)(int16_t)(r & 0xffffu), A = J < 0 ? -J : J;
+                m.adr[k] = sa + 4u * ((r >> 16) * (uint32_t)qw + (J < 0 ? inv : 0u));
+#ifdef __OPTIMIZE__
+                asm volatile("" : "+v"(m.adr[k]));  // a value of its own: else every read adds the LDS base again
+#endif
+                m.jr[k] = (uint32_t)A * 0x01010101u;
+                sum += A;
+            }
+            const uint32_t c16 = (uint32_t)(4 * (h - sum)) & 0xffffu;
+            m.c2 = c16 | (c16 << 16);
+        }
+    }
+
+    // Per byte, the sum of |J| over the neighbours agreeing with sign(J).
+    __device__ __forceinline__ static uint32_t agree(const Mine &m, const uint32_t (&w)[DK]) {
+        uint32_t P = 0;
+#pragma unroll
+        for (int k = 0; k < DK; ++k) P += w[k] & m.jr[k];
+        return P;
+    }
+    __device__ __forceinline__ static void words(const Mine &m, uint32_t (&w)[DK]) {
+#pragma unroll
+        for (int k = 0; k < DK; ++k) w[k] = swar_ld32(m.adr[k]);
+    }
+
+    // One chunk of the schedule (see swar_run); starts and ends with a barrier.
+    __device__ __forceinline__ void run(const SwarLds &L, const SaItem &a, const int *cs, const SwarChunk &ch) {
+        const int n = a.n, qw = a.qw, T = blockDim.x, tid = threadIdx.x, q0 = a.q0;
+        const uint32_t inv = (uint32_t)n * (uint32_t)qw, quad = (uint32_t)(q0 + qa);
+        const int ls0 = ch.ls0, lsend = ch.count < 0 ? a.sweeps : ls0 + ch.count;
+        for (int k = tid; k < 2 * kSwarTabWords; k += T) {
+            const int i = k % kSwarTabWords - kSwarTabHalf;
+            L.tab[k] = (i >= 0 && k < kSwarTabWords && i < a.row_len && ls0 < lsend)
+                           ? a.tables[(size_t)ls0 * a.row_len + i]
+                           : 0xFFFFFFFFu;
+        }
+        for (int k = tid; k < 4 * qw; k += T) L.E2[k] = 0ull;
+        if (ch.resume) {
+            // spin words already in LDS
+        } else if (a.init == nullptr) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+                if (site[c].on)
+                    swar_store(L.S, site[c].at, inv, swar_start_word(site[c].ord, quad, a.k0, a.k1));
+        } else {
+            swar_load_init(L, a);
+        }
+        __syncthreads();
+        const shadow::Pass sh = shadow::begin(inv);
+        const uint32_t s_addr = swar_lds_addr(L.S);
+        auto shadow_pass = [&](int c, bool before) {
+            const Mine &m = site[c];
+            if (before) {
+                if (m.on) shadow::mark(sh, m.at);
+                shadow::barrier();
+                for (int k = 0; m.on && k < DK; ++k) {
+                    if (m.jr[k] == 0u) continue;  // padding or J = 0: the value read is unused
+                    uint32_t w = (m.adr[k] - s_addr) >> 2;
+                    if (w >= inv) w -= inv;
+                    shadow::check(sh, w);
+                }
+                shadow::count_pass(sh);
+            } else {
+                if (m.on) shadow::unmark(sh, m.at);
+                shadow::barrier();
+            }
+        };
+        auto pass = [&](const Mine &m, const char *tz, uint32_t t) __attribute__((always_inline)) {
+            if (!m.on) return;
+            const uint32_t self = L.S[m.at];
+            uint32_t w[DK];
+            words(m, w);
+            uint32_t rnd[4] = {m.ord, t, quad, 2u << 24};
+            __builtin_amdgcn_sched_barrier(0);
+            dev::philox_rounds<5>(rnd, 0, a.k0, a.k1);
+            __builtin_amdgcn_sched_barrier(0);
+            swar_i16x2 xlo, xhi;  // 4x
+            swar_x16(agree(m, w), self, m.c2, &xlo, &xhi);
+            const int32_t o[4] = {xlo.x, xlo.y, xhi.x, xhi.y};
+            uint32_t th[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) th[e] = *reinterpret_cast<const uint32_t *>(tz + o[e]);
+            __builtin_amdgcn_sched_barrier(0);
+            dev::philox_rounds<5>(rnd, 5, a.k0, a.k1);
+            __builtin_amdgcn_sched_barrier(0);
+            const uint32_t next = swar_flip(self, o, rnd, th);
+            swar_store(L.S, m.at, inv, next);
+        };
+        for (int ls = ls0; ls < lsend; ++ls) {
+            const uint32_t t = a.sweep_offset + (uint32_t)ls;
+            const int cur = (ls - ls0) & 1;
+            const char *tz = reinterpret_cast<const char *>(L.tab + cur * kSwarTabWords + kSwarTabHalf);
+            uint32_t *tnext = L.tab + (1 - cur) * kSwarTabWords + kSwarTabHalf;
+            const int next_len = ls + 1 < lsend ? a.row_len : 0;
+            uint32_t row[kRowRegs];
+            row_load(a.tables + (size_t)(ls + 1) * a.row_len, tnext, next_len, row);
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                if constexpr (shadow::kOn) shadow_pass(c, true);
+                pass(site[c], tz, t);
+                if (c + 1 == NC) row_store(tnext, next_len, row);
+                __syncthreads();
+                if constexpr (shadow::kOn) shadow_pass(c, false);
+            }
+        }
+        if (ch.keep) {
+            __syncthreads();
+            return;
+        }
+        // 2E = sum over sites of s (h + f), f = h - sum |J| + 2 P
+        long long e2[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const Mine &m = site[c];
+            if (!m.on) continue;
+            uint32_t w[DK];
+            words(m, w);
+            const uint32_t P = agree(m, w), self = L.S[m.at];
+            const int32_t h = a.image[kImgHeader + 2 * n + (int)((m.at - (uint32_t)qa) / (uint32_t)qw)];
+            const int32_t cp = ((int32_t)(int16_t)(m.c2 & 0xffffu)) / 4;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int32_t v = h + cp + 2 * (int32_t)((P >> (8 * e)) & 0xffu);
+                e2[e] += ((self >> (8 * e)) & 0xffu) ? v : -v;
+            }
+        }
+        bool any = false;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) any |= site[c].on;
+        if (any)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) atomicAdd(&L.E2[qa * 4 + e], (unsigned long long)e2[e]);
+        __syncthreads();
+        swar_write_sample(L, a, ch.poisoned);
+    }
+};
 
 // q = x / d and r = x - q d for 0 <= x < 2^20 and 1 <= d < 2^16: the float quotient
 // through v_rcp_f32 is within 1 of the true one (relative error below 2^-21), so one
@@ -452,11 +690,8 @@ __device__ void swar_run_pairs(const SwarLds &L, const SaItem &a, const int *cs,
         swar_divmod(v, n, k, p);
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
-            const dev::Words4 w = dev::philox(L.co[p].y, 0u, (uint32_t)(q0 + 2 * k + b), 1u << 24, a.k0, a.k1);
-            uint32_t word = 0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) word |= ((w.w[e] >> 31) ? 0xFFu : 0x00u) << (8 * e);
-            swar_store(L.S, (uint32_t)k * region + 2u * (uint32_t)p + (uint32_t)b, inv, word);
+            swar_store(L.S, (uint32_t)k * region + 2u * (uint32_t)p + (uint32_t)b, inv,
+                       swar_start_word(L.co[p].y, (uint32_t)(q0 + 2 * k + b), a.k0, a.k1));
         }
     }
     __syncthreads();
