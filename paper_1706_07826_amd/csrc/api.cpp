@@ -613,12 +613,12 @@ spv_status sample_inst(spv_ctx *ctx, const Inst *P, const double *betas, int32_t
     L.threads = std::max(lanes_per_site, threads / lanes_per_site * lanes_per_site);
     // Sites held in registers (2 to 4 classes of at most 1024 sites): the default where it
     // applies, since it reads no records and waits for no row.  Measured against the bodies
-    // above, 1000 sweeps: N = 64, 100 / 10,000 reads 1.08 -> 0.67 / 1.86 -> 0.89 ms; Chimera
-    // N = 512, 1000 / 4000 reads 1.36 -> 0.85 / 1.85 -> 1.42; N = 1000, 1000 reads 2.22 ->
-    // 1.01; N = 1728, 5000 reads 12.1 -> 7.2; four classes, N = 125, 2000 reads 2.00 -> 1.30.
+    // above, 1000 sweeps: N = 64, 100 / 10,000 reads 1.08 -> 0.67 / 1.86 -> 0.87 ms; Chimera
+    // N = 512, 1000 / 4000 reads 1.36 -> 0.85 / 1.85 -> 1.39; N = 1000, 1000 reads 2.22 ->
+    // 1.01; N = 1728, 5000 reads 12.1 -> 5.2; four classes, N = 125, 2000 reads 2.00 -> 1.27.
     // Quads per workgroup: whole waves for small classes; two when the quads outnumber the
-    // CUs and the workgroup stays within 512 threads (N = 512, 10,000 reads x 2000 sweeps
-    // 5.59 ms, one quad 5.75, four 7.07).
+    // CUs and the workgroup stays within 512 threads (N = 216, 10,000 reads: 1.66 ms, one
+    // quad 1.84; N = 512: 2.8 either way, four 3.5).
     const int held_qw = sa_held_env();
     const bool shape_forced = sa_qw_env() > 0 || sa_threads_env() > 0 || sa_wpl_env() > 0 || sa_big_env();
     if (held_qw != 0 && !shape_forced && swar && P->n_colours >= 2 && P->n_colours <= 4 &&

@@ -219,7 +219,66 @@ __global__ __launch_bounds__(1024) void batch_sa_paired_kernel(BatchArgs a) {
     }
 }
 
+// Held-sites body: an item is (instance, first quad, quads), every class pass of it at
+// most one word per lane; see SwarHeld.  At two classes the registers of eight waves per
+// SIMD hold the sweeps' state, so a CU runs two workgroups of 1024 lanes.
+template <int DK, int NC>
+__global__ __launch_bounds__(1024, NC > 2 ? 4 : 8) void batch_sa_held_kernel(BatchArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ int cs[kMaxColours + 1];
+    __shared__ int item_s;
+    for (;;) {
+        if (threadIdx.x == 0) item_s = atomicAdd(a.counter, 1);
+        __syncthreads();
+        const int item = __builtin_amdgcn_readfirstlane(item_s);
+        __syncthreads();
+        if (item >= a.n_items) break;
+        const BatchInst in = a.insts[a.items[3 * item]];
+        core::SaItem it;
+        it.image = a.images + in.image_off;
+        it.tables = a.tables;
+        it.init = nullptr;
+        it.out = in.out;
+        it.energies = in.energies;
+        it.n = in.n;
+        it.D = in.D;
+        it.C = in.C;
+        it.row_len = a.row_len;
+        it.sweeps = a.sweeps;
+        it.reads = in.reads;
+        it.q0 = a.items[3 * item + 1];
+        it.qw = a.items[3 * item + 2];
+        it.sweep_offset = a.sweep_offset;
+        it.k0 = (uint32_t)in.seed;
+        it.k1 = (uint32_t)(in.seed >> 32);
+        core::SwarLds L;
+        core::swar_big_layout(it.n, it.qw, &L, smem);
+        core::swar_load_colours(it, cs);
+        core::SwarHeld<DK, NC> held;
+        held.load(L, it, cs);
+        held.run(L, it, cs, core::SwarChunk());  // ends with a barrier
+    }
+}
+
+using BatchFn = void (*)(BatchArgs);
+template <int DK>
+BatchFn held_fn_of(int C) {
+    return C == 2   ? batch_sa_held_kernel<DK, 2>
+           : C == 3 ? batch_sa_held_kernel<DK, 3>
+           : C == 4 ? batch_sa_held_kernel<DK, 4>
+                    : nullptr;
+}
+BatchFn held_fn(int dk, int C) {
+    return dk == 4 ? held_fn_of<4>(C) : dk == 6 ? held_fn_of<6>(C) : dk == 8 ? held_fn_of<8>(C) : nullptr;
+}
+
 }  // namespace
+
+hipError_t batch_held_resident(int dk, int C, int threads, size_t lds, int *per_cu) {
+    const BatchFn f = held_fn(dk, C);
+    if (!f) return hipErrorInvalidValue;
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, f, threads, lds);
+}
 
 hipError_t launch_batch_prep(const BatchInst *insts, int B, int n_max, int32_t *images, hipStream_t s) {
     if (B <= 0) return hipSuccess;
@@ -259,6 +318,12 @@ hipError_t launch_batch_sa(const BatchLaunch &L, hipStream_t s) {
     a.sweep_offset = L.sweep_offset;
     a.pairs_qw = L.pairs_qw;
     a.kmax = L.kmax;
+    if (L.held) {
+        const BatchFn f = held_fn(L.dk, L.c_max);
+        if (!f) return hipErrorInvalidValue;
+        hipLaunchKernelGGL(f, dim3(L.grid), dim3(L.threads), L.held_lds, s, a);
+        return hipGetLastError();
+    }
     if (L.paired) {
         const size_t plds = batch_paired_lds_bytes(L.n_max, L.dk, L.row_len, L.pairs_qw, L.kmax);
         if (L.dk == 6)

@@ -33,10 +33,14 @@ namespace {
 struct Shape {
     int threads, qw, wgs_per_cu;
     bool paired = false;  // the paired body (copies of 2 quads per item, chosen per instance)
+    bool held = false;    // the held-sites body (quads per item chosen per instance)
 };
 
 struct Plan {
     int B = 0, n_max = 0, D_max = 1, nd = 1, row_len = 1, scale = 0, dk = 0;
+    int c_min = kMaxColours, c_max = 0;  // fewest and most colour classes of an instance
+    int cls_max = 0;                     // largest class (n where not counted)
+    long long lanes = 0;          // words of every instance's largest class over its quads
     long long image_words = 0, total_quads = 0;
     std::vector<BatchInst> insts;
     std::vector<std::vector<int>> classes;  // class sizes per instance (empty: not counted)
@@ -111,6 +115,36 @@ bool make_pair_items(const Plan &pl, int threads, size_t lds_wg, PairPlan *pp) {
     return pp->lds + 256 <= lds_wg;
 }
 
+// The held-sites body's item list and LDS: per instance the quads whose largest class
+// fills the workgroup's lanes.  False when some class exceeds the workgroup.
+bool make_held_items(const Plan &pl, int threads, size_t lds_max, std::vector<int32_t> *items, size_t *lds) {
+    if (pl.cls_max > threads) return false;
+    std::vector<int> order(pl.B);
+    std::iota(order.begin(), order.end(), 0);
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return pl.insts[a].n > pl.insts[b].n; });
+    items->clear();
+    *lds = sa_held_lds_bytes(1, 1);
+    for (int b : order) {
+        const BatchInst &in = pl.insts[b];
+        const int quads = (in.reads + 3) / 4;
+        if (quads == 0 || in.n <= 0) continue;
+        int cls = 1;
+        for (int v : pl.classes[b]) cls = std::max(cls, v);
+        if (pl.classes[b].empty()) cls = in.n;
+        const int cap = std::min(quads, threads / cls), n_it = (quads + cap - 1) / cap;
+        const int base = quads / n_it, extra = quads % n_it;
+        for (int j = 0, first = 0; j < n_it; ++j) {
+            const int q = base + (j < extra ? 1 : 0);
+            items->push_back(b);
+            items->push_back(first);
+            items->push_back(q);
+            *lds = std::max(*lds, sa_held_lds_bytes(in.n, q));
+            first += q;
+        }
+    }
+    return *lds + 256 <= lds_max;
+}
+
 size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 // Quads per item of instance b: at least the base shape, more for small
@@ -161,7 +195,8 @@ Layout layout_for(const Plan &pl, size_t n_items) {
 }
 
 spv_status enqueue(Ctx *c, const Plan &pl, const Layout &ly, size_t n_items, const Shape &sh,
-                   int sweeps, uint32_t sweep_offset, hipStream_t s, const PairPlan *pp = nullptr) {
+                   int sweeps, uint32_t sweep_offset, hipStream_t s, const PairPlan *pp = nullptr,
+                   size_t held_lds = 0) {
     unsigned char *dev = static_cast<unsigned char *>(c->batch.p);
     hipError_t e = hipMemcpyAsync(dev, c->batch_host, ly.host, hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return hip_check(c, e, "batch descriptor upload");
@@ -191,6 +226,11 @@ spv_status enqueue(Ctx *c, const Plan &pl, const Layout &ly, size_t n_items, con
         L.pairs_qw = pp->pairs_qw;
         L.kmax = pp->kmax;
         L.qw = 2;
+    }
+    if (sh.held) {
+        L.held = true;
+        L.c_max = pl.c_max;
+        L.held_lds = held_lds;
     }
     return hip_check(c, launch_batch_sa(L, s), "batch launch");
 }
@@ -283,6 +323,12 @@ spv_status sample_batch_inst(spv_ctx *ctx, int32_t B, const Inst *problems, cons
         pl.D_max = std::max(pl.D_max, in.D);
         pl.total_quads += (reads[b] + 3) / 4;
         x_max = std::max(x_max, P->x_bound);
+        int cls = P->n;
+        if (!pl.classes[b].empty()) cls = *std::max_element(pl.classes[b].begin(), pl.classes[b].end());
+        pl.c_min = std::min(pl.c_min, in.C);
+        pl.c_max = std::max(pl.c_max, in.C);
+        pl.cls_max = std::max(pl.cls_max, cls);
+        pl.lanes += (long long)cls * ((reads[b] + 3) / 4);
     }
     pl.scale = problems[0].scale_log2;
     pl.nd = digits_for(x_max);
@@ -291,6 +337,7 @@ spv_status sample_batch_inst(spv_ctx *ctx, int32_t B, const Inst *problems, cons
     // The byte-parallel body has straight-line variants for 4, 6 and 8 records per
     // site, the general body for kSiteRecs: pad every image of the batch to the largest degree (zero-coupling records).
     const bool swar = sa_use_swar(pl.nd, pl.row_len);
+    if (swar && (pl.D_max == 3 || pl.D_max == 5 || pl.D_max == 7)) ++pl.D_max;  // (LDS blocks of the same size)
     if (swar ? (pl.D_max == 4 || pl.D_max == 6 || pl.D_max == 8) : pl.D_max == kSiteRecs) {
         pl.dk = pl.D_max;
         pl.image_words = 0;
@@ -313,6 +360,19 @@ spv_status sample_batch_inst(spv_ctx *ctx, int32_t B, const Inst *problems, cons
     const size_t lds_cu = c->lds_max;  // LDS of one CU (the largest workgroup allocation)
     Shape sh{256, 2, 4};
     if (paired_ok) sh = Shape{1024, 2, 1, true};
+    // The held-sites body where every class fits a workgroup.  A batch that does not fill
+    // the device takes the narrowest workgroups, spread over more CUs (8 instances of 500 to
+    // 1000 variables, 50 reads: 0.97 ms, 1024 threads 1.42, the paired body 6.57); one that
+    // does takes 512 threads, or 1024 when classes beyond 256 would leave waves of them idle
+    // (256 instances of 50 to 1000, 500 reads x 500 sweeps: 11.6 ms, 512 threads 12.4, the
+    // paired body 17.0; 128 of 30 to 300: 2.6, 2.4 and 5.0).
+    const bool held_ok = paired_ok && pl.c_min == pl.c_max && pl.c_max >= 2 && pl.c_max <= 4 && pl.cls_max >= 1 &&
+                         pl.cls_max <= 1024 && sa_held_env() != 0;
+    if (held_ok) {
+        const int narrow = (pl.cls_max + 63) / 64 * 64;
+        const bool fills = pl.lanes >= 64ll * 32 * c->num_cus;
+        sh = Shape{!fills ? narrow : pl.cls_max > 256 ? 1024 : 512, 1, 1, false, true};
+    }
     const std::vector<long long> tkey = {pl.n_max, pl.D_max, pl.nd, B, pl.total_quads / 64};
     bool have = false;
     if (opts && opts->threads > 0 && (flags & SPV_BATCH_PAIRED)) {
@@ -327,12 +387,21 @@ spv_status sample_batch_inst(spv_ctx *ctx, int32_t B, const Inst *problems, cons
     if (!have)
         for (auto &t : c->tuned)
             if (t.key == tkey) {
-                sh = Shape{t.threads, t.qw, t.wgs_per_cu, t.paired};
+                sh = Shape{t.threads, t.qw, t.wgs_per_cu, t.paired, t.held};
                 have = true;
             }
     // Items, layout and (paired body) per-instance copies of a shape.
     PairPlan pp;
-    auto items_of = [&](const Shape &x, std::vector<int32_t> *items) -> bool {
+    size_t held_lds = 0;
+    auto items_of = [&](Shape &x, std::vector<int32_t> *items) -> bool {
+        if (x.held) {
+            int per_cu = 0;
+            if (!make_held_items(pl, x.threads, c->lds_max, items, &held_lds) ||
+                batch_held_resident(pl.dk, pl.c_max, x.threads, held_lds, &per_cu) != hipSuccess || per_cu < 1)
+                return false;
+            x.wgs_per_cu = per_cu;
+            return true;
+        }
         if (x.paired) {
             if (!make_pair_items(pl, x.threads, lds_cu / (size_t)x.wgs_per_cu, &pp)) return false;
             *items = pp.items;
@@ -347,21 +416,22 @@ spv_status sample_batch_inst(spv_ctx *ctx, int32_t B, const Inst *problems, cons
         static const Shape cand[] = {{64, 2, 16},        {128, 2, 8},         {128, 4, 8},         {256, 1, 4},
                                      {256, 2, 4},        {512, 1, 2},         {512, 2, 2},         {512, 4, 2},
                                      {1024, 2, 1},       {1024, 4, 1},        {1024, 8, 1},        {1024, 2, 1, true},
-                                     {512, 2, 2, true},  {512, 2, 1, true},   {256, 2, 4, true},   {256, 2, 2, true}};
+                                     {512, 2, 2, true},  {512, 2, 1, true},   {256, 2, 4, true},   {256, 2, 2, true},
+                                     {256, 1, 1, false, true}, {512, 1, 1, false, true}, {1024, 1, 1, false, true}};
         const int tsweeps = std::min(sweeps, 24);
         hipEvent_t e0, e1;
         if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
             return set_err(c, SPV_EDEVICE, "event create");
         float best = 1e30f;
         Shape bs = sh;
-        for (const Shape &cs : cand) {
-            if (cs.paired && !paired_ok) continue;
+        for (Shape cs : cand) {
+            if ((cs.paired && !paired_ok) || (cs.held && !held_ok)) continue;
             std::vector<int32_t> items;
             if (!items_of(cs, &items)) continue;
             const Layout ly = layout_for(pl, items.size() / 3);
             if ((st = ensure_batch_buf(c, ly.total)) || (st = stage(c, pl, items, ly))) break;
             (void)hipEventRecord(e0, stream);
-            st = enqueue(c, pl, ly, items.size() / 3, cs, tsweeps, 0, stream, &pp);
+            st = enqueue(c, pl, ly, items.size() / 3, cs, tsweeps, 0, stream, &pp, held_lds);
             (void)hipEventRecord(e1, stream);
             (void)hipEventRecord(c->batch_done, stream);
             if (st) break;
@@ -380,7 +450,7 @@ spv_status sample_batch_inst(spv_ctx *ctx, int32_t B, const Inst *problems, cons
         if (st) return st;
         sh = bs;
         tuned_ms = best;
-        c->tuned.push_back({tkey, sh.threads, sh.qw, sh.wgs_per_cu, best, sh.paired});
+        c->tuned.push_back({tkey, sh.threads, sh.qw, sh.wgs_per_cu, best, sh.paired, sh.held});
     }
     if (sh.threads < 64 || sh.threads > 1024 || sh.threads % 64 || sh.qw < 1 || sh.qw > sh.threads ||
         sh.wgs_per_cu < 1 || sh.wgs_per_cu > 32)
@@ -388,14 +458,16 @@ spv_status sample_batch_inst(spv_ctx *ctx, int32_t B, const Inst *problems, cons
                        sh.qw, sh.wgs_per_cu);
     std::vector<int32_t> items;
     if (!items_of(sh, &items)) {
-        if (!sh.paired || have)
+        if ((!sh.paired && !sh.held) || have)
             return set_err(c, SPV_ECAPACITY, "largest instance (n=%d) needs more LDS than a workgroup has", pl.n_max);
-        sh = Shape{256, 2, 4, false};  // default paired shape does not fit: the one-word body
-        if (!items_of(sh, &items))
+        // a default shape that does not fit gives way to the next: paired, then one word per lane
+        if (sh.held) sh = Shape{1024, 2, 1, true};
+        if (!sh.paired || !items_of(sh, &items)) sh = Shape{256, 2, 4, false};
+        if (!sh.paired && !items_of(sh, &items))
             return set_err(c, SPV_ECAPACITY, "largest instance (n=%d) needs more LDS than a workgroup has", pl.n_max);
     }
     c->last_shape[0] = sh.threads;
-    c->last_shape[1] = sh.paired ? 0 : sh.qw;
+    c->last_shape[1] = sh.paired || sh.held ? 0 : sh.qw;
     c->last_shape[2] = sh.wgs_per_cu;
     c->last_tuned_ms = tuned_ms;
 
@@ -406,8 +478,8 @@ spv_status sample_batch_inst(spv_ctx *ctx, int32_t B, const Inst *problems, cons
     if (n_items == 0) return SPV_OK;
     if (flags & SPV_BATCH_GRAPH) {
         const std::vector<long long> key = {B, (long long)n_items, pl.n_max, pl.D_max, pl.nd, pl.row_len,
-                                            sweeps, sh.threads, sh.qw, sh.wgs_per_cu, sh.paired ? 1 : 0,
-                                            pp.pairs_qw, pp.kmax,
+                                            sweeps, sh.threads, sh.qw, sh.wgs_per_cu, sh.held ? 2 : sh.paired ? 1 : 0,
+                                            sh.held ? pl.c_max : pp.pairs_qw, sh.held ? (long long)held_lds : pp.kmax,
                                             (long long)(uintptr_t)c->batch.p,
                                             (long long)(uintptr_t)c->batch_host,
                                             (long long)(uintptr_t)c->tables.p, (long long)(uintptr_t)stream};
@@ -423,7 +495,7 @@ spv_status sample_batch_inst(spv_ctx *ctx, int32_t B, const Inst *problems, cons
             hipGraph_t graph = nullptr;
             hipError_t e = hipStreamBeginCapture(c->capture_stream, hipStreamCaptureModeThreadLocal);
             if (e != hipSuccess) return hip_check(c, e, "begin capture");
-            st = enqueue(c, pl, ly, n_items, sh, sweeps, 0, c->capture_stream, &pp);
+            st = enqueue(c, pl, ly, n_items, sh, sweeps, 0, c->capture_stream, &pp, held_lds);
             e = hipStreamEndCapture(c->capture_stream, &graph);
             if (st) {
                 if (graph) (void)hipGraphDestroy(graph);
@@ -437,7 +509,7 @@ spv_status sample_batch_inst(spv_ctx *ctx, int32_t B, const Inst *problems, cons
         hipError_t e = hipGraphLaunch(exec, stream);
         if (e != hipSuccess) return hip_check(c, e, "graph launch");
     } else {
-        if ((st = enqueue(c, pl, ly, n_items, sh, sweeps, 0, stream, &pp))) return st;
+        if ((st = enqueue(c, pl, ly, n_items, sh, sweeps, 0, stream, &pp, held_lds))) return st;
     }
     return hip_check(c, hipEventRecord(c->batch_done, stream), "event record");
 }

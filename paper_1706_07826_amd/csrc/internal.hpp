@@ -113,7 +113,7 @@ struct Ctx {
         std::vector<long long> key;
         int threads, qw, wgs_per_cu;
         float ms;
-        bool paired;
+        bool paired, held;
     };
     std::vector<TuneEntry> tuned;
     int last_shape[3] = {0, 0, 0};
@@ -255,6 +255,7 @@ size_t sa_stream_bytes(int n, int reads, int qw);
 hipError_t launch_sa_stream(const SaLaunch &L, int plan, void *buf, hipStream_t s);
 int sa_stream_chunks_of(const SaLaunch &L, int plan);
 size_t sa_lds_bytes(int n, int D, int row_len, int qw, bool big = false);
+int sa_held_env();
 size_t sa_held_lds_bytes(int n, int qw);
 size_t sa_big_bytes(int n, int D);
 bool sa_use_swar(int nd, int row_len);
@@ -315,7 +316,12 @@ struct BatchLaunch {
     bool paired = false;  // paired body (items are instance, first quad, copies of 2 quads)
     int pairs_qw = 0;     // paired body: spin area of 2 n_max pairs_qw words
     int kmax = 0;         // paired body: most copies of an item
+    bool held = false;    // held-sites body (items are instance, first quad, quads)
+    int c_max = 0;        // held-sites body: colour classes of every instance
+    size_t held_lds = 0;  // held-sites body: LDS of the largest item
 };
+// Workgroups per CU of the held-sites body.
+hipError_t batch_held_resident(int dk, int C, int threads, size_t lds, int *per_cu);
 // Small instances get up to this many quads per work item (energy accumulators are sized for it).
 constexpr int kBatchMaxItemQuads = 16;
 size_t batch_lds_bytes(int n_max, int D_max, int row_len, int qw, int nd);

@@ -148,7 +148,7 @@ __global__ __launch_bounds__(1024) void sa_kernel(core::SaItem a) {
 
 // Byte-parallel SA with every lane's sites held in registers (see SwarHeld).
 template <int DK, int NC>
-__global__ __launch_bounds__(1024) void sa_held_kernel(core::SaItem a) {
+__global__ __launch_bounds__(1024, NC > 2 ? 4 : 8) void sa_held_kernel(core::SaItem a) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int cs[kMaxColours + 1];
     a.q0 = blockIdx.x * a.qw;
@@ -190,20 +190,99 @@ __device__ __forceinline__ uint32_t spin_nibble(uint32_t w) {
 }
 __device__ __forceinline__ uint32_t spin_word(uint32_t nib) { return ((nib * 0x00204081u) & 0x01010101u) * 0xFFu; }
 
-// Every branch of the task loop depends on wave-uniform values only (the task
+// Every branch of a task loop depends on wave-uniform values only (the task
 // index is read back with readfirstlane), so that no lane can be split from its
 // wave across loop iterations and barriers.
-// NC > 0: the body with NC classes' sites held in registers (W = 1).
-template <int DK, int W, bool BIG, int NC>
-__device__ __forceinline__ void sa_stream(StreamArgs s) {
+struct StreamShared {
+    int task, late, poison;
+};
+
+// The next task's index, into LDS.  Ends with a barrier.
+__device__ __forceinline__ int stream_pop(const StreamArgs &s, StreamShared *sh) {
+    if (__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) == 0) {
+        // one increment per workgroup: lane 0 adds 1, the others 0
+        const int v = __hip_atomic_fetch_add(s.counter, threadIdx.x == 0 ? 1 : 0, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+        if (threadIdx.x == 0) {
+            sh->task = v;
+            sh->late = 0;
+            sh->poison = 0;
+        }
+    }
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(sh->task);
+}
+
+// Spin words of group g after k chunks into S and ~S, waiting (bounded) for each.
+__device__ __forceinline__ void stream_resume(const StreamArgs &s, const core::SwarLds &L, int g, int k,
+                                              StreamShared *sh) {
+    const int words = s.a.n * s.a.qw, hw = (words + 3) / 4, T = blockDim.x;
+    const uint32_t *st = s.state + (size_t)g * (size_t)hw;
+    // every word must carry this launch's tag for k chunks done
+    const uint32_t want = (uint32_t)k;
+    bool late = false, poison = false;
+    for (int h = threadIdx.x; h < hw; h += T) {
+        uint32_t v = 0;
+        for (int spins = 0;; ++spins) {
+            v = __hip_atomic_load(st + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (((v >> 16) & ~kTagPoison) == want) break;
+            if (spins >= s.spin_limit) {
+                late = true;
+                break;
+            }
+            __builtin_amdgcn_s_sleep(2);
+        }
+        poison |= ((v >> 16) & kTagPoison) != 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int w = 4 * h + q;
+            if (w < words) {
+                const uint32_t word = spin_word((v >> (4 * q)) & 0xFu);
+                L.S[w] = word;
+                L.S[w + words] = ~word;
+            }
+        }
+    }
+    if (late) sh->late = 1;
+    if (poison) sh->poison = 1;
+}
+
+// Task tau's share of the schedule, after its resume and a barrier.
+__device__ __forceinline__ core::SwarChunk stream_chunk(const StreamArgs &s, int k, const StreamShared *sh) {
+    const bool late = __builtin_amdgcn_readfirstlane(sh->late) != 0;
+    core::SwarChunk ch;
+    ch.ls0 = k * s.Lc;
+    ch.count = min(s.Lc, s.a.sweeps - ch.ls0);
+    // An abandoned wait restarts the group from its initial state: words that may
+    // still be in flight are not used.
+    ch.resume = k > 0 && !late;
+    ch.keep = k + 1 < s.K;
+    ch.poisoned = late || __builtin_amdgcn_readfirstlane(sh->poison) != 0;
+    return ch;
+}
+
+// Spin words of group g after chunk k to its next task.
+__device__ __forceinline__ void stream_handoff(const StreamArgs &s, const core::SwarLds &L, int g, int k,
+                                               bool poisoned) {
+    const int words = s.a.n * s.a.qw, hw = (words + 3) / 4, T = blockDim.x;
+    uint32_t *st = s.state + (size_t)g * (size_t)hw;
+    const uint32_t tag = (poisoned ? kTagPoison : 0u) | (uint32_t)(k + 1);
+    for (int h = threadIdx.x; h < hw; h += T) {
+        uint32_t pay = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (4 * h + q < words) pay |= spin_nibble(L.S[4 * h + q]) << (4 * q);
+        __hip_atomic_store(st + h, (tag << 16) | pay, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+template <int DK, int W, bool BIG = false>
+__global__ __launch_bounds__(1024) void sa_stream_kernel(StreamArgs s) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int cs[kMaxColours + 1];
-    __shared__ int task_s, late_s, poison_s;
+    __shared__ StreamShared sh;
     core::SwarLds L;
-    if constexpr (NC > 0) {
-        core::swar_big_layout(s.a.n, s.a.qw, &L, smem);
-        core::swar_load_colours(s.a, cs);
-    } else if constexpr (BIG) {
+    if constexpr (BIG) {
         core::swar_big_layout(s.a.n, s.a.qw, &L, smem);
         core::swar_bind_big(&L, s.a.big, s.a.n, s.a.D);
         core::swar_load_colours(s.a, cs);
@@ -211,99 +290,81 @@ __device__ __forceinline__ void sa_stream(StreamArgs s) {
         core::swar_layout(s.a.n, s.a.D, s.a.row_len, s.a.qw, &L, smem);
         core::swar_load_instance(L, s.a, cs);
     }
-    const int ntask = s.G * s.K, T = blockDim.x, tid = threadIdx.x;
-    const int words = s.a.n * s.a.qw, hw = (words + 3) / 4;
-    const uint32_t inv = (uint32_t)words;
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     for (;;) {
-        if (wave == 0) {
-            // one increment per workgroup: lane 0 adds 1, the others 0
-            const int v = __hip_atomic_fetch_add(s.counter, threadIdx.x == 0 ? 1 : 0, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT);
-            if (threadIdx.x == 0) {
-                task_s = v;
-                late_s = 0;
-                poison_s = 0;
-            }
-        }
-        __syncthreads();
-        const int tau = __builtin_amdgcn_readfirstlane(task_s);
-        if (tau >= ntask) break;
+        const int tau = stream_pop(s, &sh);
+        if (tau >= s.G * s.K) break;
         const int g = tau % s.G, k = tau / s.G;
-        uint32_t *st = s.state + (size_t)g * (size_t)hw;
-        if (k > 0) {
-            // resume: every word must carry this launch's tag for k chunks done
-            const uint32_t want = (uint32_t)k;
-            bool late = false, poison = false;
-            for (int h = tid; h < hw; h += T) {
-                uint32_t v = 0;
-                for (int spins = 0;; ++spins) {
-                    v = __hip_atomic_load(st + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if (((v >> 16) & ~kTagPoison) == want) break;
-                    if (spins >= s.spin_limit) {
-                        late = true;
-                        break;
-                    }
-                    __builtin_amdgcn_s_sleep(2);
-                }
-                poison |= ((v >> 16) & kTagPoison) != 0;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int w = 4 * h + q;
-                    if (w < words) {
-                        const uint32_t word = spin_word((v >> (4 * q)) & 0xFu);
-                        L.S[w] = word;
-                        L.S[w + inv] = ~word;
-                    }
-                }
-            }
-            if (late) late_s = 1;
-            if (poison) poison_s = 1;
-        }
+        if (k > 0) stream_resume(s, L, g, k, &sh);
         __syncthreads();
-        const bool poisoned = (__builtin_amdgcn_readfirstlane(late_s) | __builtin_amdgcn_readfirstlane(poison_s)) != 0;
-        const bool late = __builtin_amdgcn_readfirstlane(late_s) != 0;
+        const core::SwarChunk ch = stream_chunk(s, k, &sh);
         core::SaItem it = s.a;
         it.q0 = g * s.a.qw;
-        core::SwarChunk ch;
-        ch.ls0 = k * s.Lc;
-        ch.count = min(s.Lc, s.a.sweeps - ch.ls0);
-        // An abandoned wait restarts the group from its initial state: words that may
-        // still be in flight are not used.
-        ch.resume = k > 0 && !late;
-        ch.keep = k + 1 < s.K;
-        ch.poisoned = poisoned;
-        if constexpr (NC > 0) {
-            // the sites are read again for every task: kept in registers over the whole
-            // loop they cost the sweeps more of them than the reads cost time
-            core::SwarHeld<DK, NC> held;
-            held.load(L, it, cs);
-            held.run(L, it, cs, ch);
-        } else
-            core::swar_run<DK, W, BIG>(L, it, cs, ch);  // ends with a barrier
-        if (ch.keep) {
-            const uint32_t tag = (poisoned ? kTagPoison : 0u) | (uint32_t)(k + 1);
-            for (int h = tid; h < hw; h += T) {
-                uint32_t pay = 0;
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    if (4 * h + q < words) pay |= spin_nibble(L.S[4 * h + q]) << (4 * q);
-                __hip_atomic_store(st + h, (tag << 16) | pay, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
+        core::swar_run<DK, W, BIG>(L, it, cs, ch);  // ends with a barrier
+        if (ch.keep) stream_handoff(s, L, g, k, ch.poisoned);
     }
 }
 
-template <int DK, int W, bool BIG = false>
-__global__ __launch_bounds__(1024) void sa_stream_kernel(StreamArgs s) {
-    sa_stream<DK, W, BIG, 0>(s);
+// The launch's arguments read again from where the kernel received them: a phase that
+// takes them from here does not keep them in scalar registers through the phases before.
+__device__ __forceinline__ StreamArgs stream_args() {
+#ifdef __HIP_DEVICE_COMPILE__
+    auto p = (const __attribute__((address_space(4))) StreamArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+#ifdef __OPTIMIZE__
+    asm volatile("" : "+s"(p));
+#endif
+    return *p;
+#else
+    return StreamArgs();
+#endif
 }
 
-// Seven waves per SIMD with two classes: what registers this costs outside the sweeps is
-// spilled there.
+// The same with every lane's sites in registers (see SwarHeld).  Registers for eight
+// waves per SIMD at two classes: the sites are read again
+// for every task and each phase takes the arguments anew, so that little else is live in
+// the sweeps (spilled scalars cost them twelve more vector instructions a word).
 template <int DK, int NC>
-__global__ __launch_bounds__(1024, NC == 2 ? 7 : 4) void sa_held_stream_kernel(StreamArgs s) {
-    sa_stream<DK, 1, false, NC>(s);
+__global__ __launch_bounds__(1024, NC > 2 ? 4 : 8) void sa_held_stream_kernel(StreamArgs) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ int cs[kMaxColours + 1];
+    __shared__ StreamShared sh;
+    auto layout = [&](const StreamArgs &s) __attribute__((always_inline)) {
+        core::SwarLds L;
+        core::swar_big_layout(s.a.n, s.a.qw, &L, smem);
+        return L;
+    };
+    core::swar_load_colours(stream_args().a, cs);
+    for (;;) {
+        {
+            const StreamArgs s = stream_args();
+            const int tau = stream_pop(s, &sh);
+            if (tau >= s.G * s.K) break;
+            if (tau >= s.G) stream_resume(s, layout(s), tau % s.G, tau / s.G, &sh);
+            __syncthreads();
+        }
+        core::SwarHeld<DK, NC> held;
+        {
+            const StreamArgs s = stream_args();
+            const int tau = __builtin_amdgcn_readfirstlane(sh.task);
+            core::SaItem it = s.a;
+            it.q0 = (tau % s.G) * s.a.qw;
+            const core::SwarLds L = layout(s);
+            held.load(L, it, cs);
+            held.sweeps(L, it, stream_chunk(s, tau / s.G, &sh));
+        }
+        {
+            const StreamArgs s = stream_args();
+            const int tau = __builtin_amdgcn_readfirstlane(sh.task), g = tau % s.G, k = tau / s.G;
+            const core::SwarChunk ch = stream_chunk(s, k, &sh);
+            const core::SwarLds L = layout(s);
+            core::SaItem it = s.a;
+            it.q0 = g * s.a.qw;
+            if (ch.keep)
+                stream_handoff(s, L, g, k, ch.poisoned);
+            else
+                held.finish(L, it, ch.poisoned);
+            __syncthreads();  // the flags are read before the next task resets them
+        }
+    }
 }
 
 // Task counter and tags back to zero (no word then matches a chunk tag >= 1).
@@ -585,6 +646,11 @@ int sa_stream_plan(const SaLaunch &L, int num_cus, int force_grid) {
 #undef SPV_OCC
     const int resident = per_cu * num_cus;
     if (e != hipSuccess || resident <= 0 || G <= resident) return 1;
+    // Held sites: a last round that is half empty or less runs about as fast in one launch,
+    // its workgroups having the CUs almost to themselves (1250 workgroups on 1024 resident,
+    // N = 1000, 500 sweeps: 1.43 ms, streamed 1.58; on 512 resident, N = 1728: 3.39, streamed
+    // 2.62).
+    if (L.held && 2 * G < 3 * resident) return 1;
     const char *kv = getenv("SPVAR_SA_CHUNKS");  // tuning: a fixed chunk count
     const int K = kv && atoi(kv) > 0 ? std::min(255, atoi(kv)) : stream_chunks(G, L.sweeps, resident);
     return K <= 1 ? 1 : (K | (resident << 8));

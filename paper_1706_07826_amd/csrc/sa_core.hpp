@@ -235,22 +235,23 @@ __device__ __forceinline__ uint32_t metropolis_mask(const int32_t x[4], const ui
     return mask;
 }
 
-// The next sweep's acceptance row is loaded at the start of a sweep into kRowRegs
-// registers a thread and stored to its LDS buffer before the sweep's last barrier, so
-// that no sweep waits for the load (what a narrow workgroup cannot hold goes straight
-// to LDS).  len = 0: no next sweep.
+// The next sweep's acceptance row is loaded at the start of a sweep into N registers a
+// thread and stored to its LDS buffer before the sweep's last barrier, so that no sweep
+// waits for the load (what a narrow workgroup cannot hold goes straight to LDS).
+// len = 0: no next sweep.
 constexpr int kRowRegs = 2;
-__device__ __forceinline__ void row_load(const uint32_t *__restrict__ src, uint32_t *dst, int len,
-                                         uint32_t (&reg)[kRowRegs]) {
+template <int N>
+__device__ __forceinline__ void row_load(const uint32_t *__restrict__ src, uint32_t *dst, int len, uint32_t (&reg)[N]) {
     const int T = blockDim.x, tid = threadIdx.x;
 #pragma unroll
-    for (int u = 0; u < kRowRegs; ++u) reg[u] = tid + u * T < len ? src[tid + u * T] : 0u;
-    for (int k = tid + kRowRegs * T; k < len; k += T) dst[k] = src[k];
+    for (int u = 0; u < N; ++u) reg[u] = tid + u * T < len ? src[tid + u * T] : 0u;
+    for (int k = tid + N * T; k < len; k += T) dst[k] = src[k];
 }
-__device__ __forceinline__ void row_store(uint32_t *dst, int len, const uint32_t (&reg)[kRowRegs]) {
+template <int N>
+__device__ __forceinline__ void row_store(uint32_t *dst, int len, const uint32_t (&reg)[N]) {
     const int T = blockDim.x, tid = threadIdx.x;
 #pragma unroll
-    for (int u = 0; u < kRowRegs; ++u)
+    for (int u = 0; u < N; ++u)
         if (tid + u * T < len) dst[tid + u * T] = reg[u];
 }
 

@@ -479,6 +479,10 @@ __device__ void swar_run(const SwarLds &L, const SaItem &a, const int *cs, const
 // is a short chain of latencies: half of a word's random rounds run behind the neighbour
 // reads and half behind the threshold reads, and the next sweep's acceptance row is loaded
 // a sweep ahead.
+// Measured at Chimera 8 x 8, 10,000 reads x 2000 sweeps: 5.5 ms against 6.5 for the body
+// with records in LDS, the vector units busy 0.93 of the time at a clock the load brings
+// down to about 2 GHz.  Two quads per lane (8-byte accesses, half the barriers) was
+// slower there, 5.8 ms: its registers leave five waves per SIMD instead of eight.
 template <int DK, int NC>
 struct SwarHeld {
     struct Mine {    // the lane's site of one class
@@ -526,6 +530,10 @@ struct SwarHeld {
         }
     }
 
+    __device__ __forceinline__ static void words(const Mine &m, uint32_t (&w)[DK]) {
+#pragma unroll
+        for (int k = 0; k < DK; ++k) w[k] = swar_ld32(m.adr[k]);
+    }
     // Per byte, the sum of |J| over the neighbours agreeing with sign(J).
     __device__ __forceinline__ static uint32_t agree(const Mine &m, const uint32_t (&w)[DK]) {
         uint32_t P = 0;
@@ -533,13 +541,15 @@ struct SwarHeld {
         for (int k = 0; k < DK; ++k) P += w[k] & m.jr[k];
         return P;
     }
-    __device__ __forceinline__ static void words(const Mine &m, uint32_t (&w)[DK]) {
-#pragma unroll
-        for (int k = 0; k < DK; ++k) w[k] = swar_ld32(m.adr[k]);
+
+    // One chunk of the schedule (see swar_run).
+    __device__ __forceinline__ void run(const SwarLds &L, const SaItem &a, const int *cs, const SwarChunk &ch) {
+        sweeps(L, a, ch);
+        if (!ch.keep) finish(L, a, ch.poisoned);
     }
 
-    // One chunk of the schedule (see swar_run); starts and ends with a barrier.
-    __device__ __forceinline__ void run(const SwarLds &L, const SaItem &a, const int *cs, const SwarChunk &ch) {
+    // The chunk's tables, its start state unless resumed, and its sweeps.  Ends with a barrier.
+    __device__ __forceinline__ void sweeps(const SwarLds &L, const SaItem &a, const SwarChunk &ch) {
         const int n = a.n, qw = a.qw, T = blockDim.x, tid = threadIdx.x, q0 = a.q0;
         const uint32_t inv = (uint32_t)n * (uint32_t)qw, quad = (uint32_t)(q0 + qa);
         const int ls0 = ch.ls0, lsend = ch.count < 0 ? a.sweeps : ls0 + ch.count;
@@ -555,8 +565,7 @@ struct SwarHeld {
         } else if (a.init == nullptr) {
 #pragma unroll
             for (int c = 0; c < NC; ++c)
-                if (site[c].on)
-                    swar_store(L.S, site[c].at, inv, swar_start_word(site[c].ord, quad, a.k0, a.k1));
+                if (site[c].on) swar_store(L.S, site[c].at, inv, swar_start_word(site[c].ord, quad, a.k0, a.k1));
         } else {
             swar_load_init(L, a);
         }
@@ -583,23 +592,20 @@ struct SwarHeld {
         auto pass = [&](const Mine &m, const char *tz, uint32_t t) __attribute__((always_inline)) {
             if (!m.on) return;
             const uint32_t self = L.S[m.at];
-            uint32_t w[DK];
+            uint32_t w[DK], rnd[4] = {m.ord, t, quad, 2u << 24}, th[4];
             words(m, w);
-            uint32_t rnd[4] = {m.ord, t, quad, 2u << 24};
             __builtin_amdgcn_sched_barrier(0);
             dev::philox_rounds<5>(rnd, 0, a.k0, a.k1);
             __builtin_amdgcn_sched_barrier(0);
             swar_i16x2 xlo, xhi;  // 4x
             swar_x16(agree(m, w), self, m.c2, &xlo, &xhi);
             const int32_t o[4] = {xlo.x, xlo.y, xhi.x, xhi.y};
-            uint32_t th[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) th[e] = *reinterpret_cast<const uint32_t *>(tz + o[e]);
             __builtin_amdgcn_sched_barrier(0);
             dev::philox_rounds<5>(rnd, 5, a.k0, a.k1);
             __builtin_amdgcn_sched_barrier(0);
-            const uint32_t next = swar_flip(self, o, rnd, th);
-            swar_store(L.S, m.at, inv, next);
+            swar_store(L.S, m.at, inv, swar_flip(self, o, rnd, th));
         };
         for (int ls = ls0; ls < lsend; ++ls) {
             const uint32_t t = a.sweep_offset + (uint32_t)ls;
@@ -607,7 +613,7 @@ struct SwarHeld {
             const char *tz = reinterpret_cast<const char *>(L.tab + cur * kSwarTabWords + kSwarTabHalf);
             uint32_t *tnext = L.tab + (1 - cur) * kSwarTabWords + kSwarTabHalf;
             const int next_len = ls + 1 < lsend ? a.row_len : 0;
-            uint32_t row[kRowRegs];
+            uint32_t row[1];
             row_load(a.tables + (size_t)(ls + 1) * a.row_len, tnext, next_len, row);
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
@@ -618,10 +624,11 @@ struct SwarHeld {
                 if constexpr (shadow::kOn) shadow_pass(c, false);
             }
         }
-        if (ch.keep) {
-            __syncthreads();
-            return;
-        }
+    }
+
+    // Energies and spins of the workgroup's reads.  Ends with a barrier.
+    __device__ __forceinline__ void finish(const SwarLds &L, const SaItem &a, bool poisoned) const {
+        const int n = a.n, qw = a.qw;
         // 2E = sum over sites of s (h + f), f = h - sum |J| + 2 P
         long long e2[4] = {0, 0, 0, 0};
 #pragma unroll
@@ -646,7 +653,7 @@ struct SwarHeld {
 #pragma unroll
             for (int e = 0; e < 4; ++e) atomicAdd(&L.E2[qa * 4 + e], (unsigned long long)e2[e]);
         __syncthreads();
-        swar_write_sample(L, a, ch.poisoned);
+        swar_write_sample(L, a, poisoned);
     }
 };
 

@@ -68,3 +68,32 @@ def test_held(spv, ctx, monkeypatch, name, sizes, d, j, h, reads, env, init):
                            init_spins=torch.as_tensor(S0).cuda() if init else None)
     osp, oE = oracle.sa_sample(inst, betas, reads=reads, seed=17, sweep_offset=9 if init else 0, init=S0, threads=8)
     assert np.array_equal(sp.cpu().numpy(), osp) and np.array_equal(E.cpu().numpy(), oE)
+
+
+BATCHES = [
+    ("two_classes", [[40, 40], [9, 8], [129, 64], [300, 257], [1, 1]], 3, [23, 400, 9, 30, 3]),
+    ("degree5_padded", [[30, 30], [64, 64]], 5, [50, 700]),
+    ("degree8", [[30, 30], [20, 31]], 8, [50, 70]),
+    ("three_classes", [[20, 20, 20], [33, 31, 35]], 2, [41, 17]),
+    ("four_classes", [[20, 20, 20, 20], [65, 12, 9, 64]], 2, [41, 17]),
+    ("mixed_class_counts", [[20, 20], [12, 12, 12]], 3, [41, 17]),
+    ("fills_device_wide", [[300, 300], [40, 40]], 4, [8200, 900]),
+    ("fills_device_narrow", [[60, 60], [40, 40]], 4, [40100, 900]),
+]
+
+
+@pytest.mark.parametrize("name,shapes,d,reads", BATCHES, ids=[c[0] for c in BATCHES])
+def test_held_batch(spv, ctx, name, shapes, d, reads):
+    insts = [_layers(sz, min(d, min(sz)), 6, 50 + b, 4) for b, sz in enumerate(shapes)]
+    betas = si.linear_betas(0.05, 3.0, 11)
+    seeds = [70 + b for b in range(len(insts))]
+    print(f"[held] batch {name}", flush=True)
+    probs = [spv.Problem.from_instance(i) for i in insts]
+    for graph in (False, True, True):
+        sp, E = spv.spv_sample_batch(ctx, probs, betas, reads, seeds, graph=graph)
+        for b, inst in enumerate(insts):
+            s_b, e_b = sp[b].cpu().numpy(), E[b].cpu().numpy()
+            assert np.array_equal(e_b, oracle.energy(inst, s_b)), b
+            for lo, hi in {(0, min(40, reads[b])), (max(0, reads[b] - 40), reads[b])}:
+                osp, oE = oracle.sa_sample(inst, betas, seed=seeds[b], r_begin=lo, r_end=hi)
+                assert np.array_equal(s_b[lo:hi], osp) and np.array_equal(e_b[lo:hi], oE), (b, lo)
