@@ -383,14 +383,90 @@ __global__ __launch_bounds__(256) void big_prep_kernel(core::SaItem a) {
 }
 
 // Energies of arbitrary states: one workgroup per 64 rows... one thread per (row, variable).
+// Energies of given rows.  2E = sum_i s_i (2 h_i + sum_j J_ij s_j).
+// A workgroup stages NR rows in LDS by position, one int16 lane per row (any int8 value
+// is exact there), so a neighbour is one LDS read of all its rows and two neighbours
+// cost a row one v_perm_b32 and one v_dot2_i32_i16 (|sum| <= 64 * 2^15 * 2^7 < 2^29).
+// What it replaces gathered every neighbour's byte from global memory through the
+// position map, a row per workgroup: L = 10 cube, 10^4 rows, 96 -> 16 us; L = 20, 5000
+// rows, 444 -> 135 us a call.  Bound by each workgroup's reading of the n D records
+// through the vector cache.  8 rows a workgroup halve those reads, but leave half the
+// workgroups, and measured the same at n = 512 and 1000 and slower at 8000 (158 us).
+constexpr int kEnergyRows = 4;
+
+__global__ __launch_bounds__(1024) void energy_rows_kernel(const int32_t *__restrict__ image, int n, int D,
+                                                           const int8_t *__restrict__ spins, int R,
+                                                           long long *__restrict__ E) {
+    constexpr int NR = kEnergyRows;
+    extern __shared__ __align__(16) uint32_t row_lds[];
+    __shared__ long long part[1024 / 64][NR];
+    struct alignas(2 * NR) Rows {
+        uint32_t w[NR / 2];
+    };
+    Rows *sp = reinterpret_cast<Rows *>(row_lds);
+    const int tid = threadIdx.x, T = blockDim.x;
+    const int r0 = blockIdx.x * NR, nr = min(NR, R - r0);
+    const int32_t *pos_of = image + kImgHeader + n;
+    const int32_t *hpos = pos_of + n;
+    const uint32_t *nbr = reinterpret_cast<const uint32_t *>(hpos + n);
+    const int8_t *s = spins + (size_t)r0 * n;
+    for (int i = tid; i < n; i += T) {
+        int v[NR];
+#pragma unroll
+        for (int u = 0; u < NR; ++u) v[u] = u < nr ? s[(size_t)u * n + i] : 0;
+        Rows x;
+#pragma unroll
+        for (int u = 0; u < NR / 2; ++u) x.w[u] = ((uint32_t)v[2 * u] & 0xFFFFu) | ((uint32_t)v[2 * u + 1] << 16);
+        sp[pos_of[i]] = x;
+    }
+    __syncthreads();
+    long long acc_h[NR] = {}, acc_f[NR] = {};
+    for (int p = tid; p < n; p += T) {
+        const uint32_t *rec = nbr + (size_t)p * D;
+        int32_t F[NR] = {};
+        auto pair = [&](uint32_t a, uint32_t b) {
+            const dev::i16x2 j = __builtin_bit_cast(dev::i16x2, dev::j_pair(a, b));
+            const Rows x = sp[a >> 16], y = sp[b >> 16];
+#pragma unroll
+            for (int u = 0; u < NR; ++u) {
+                const uint32_t w = __builtin_amdgcn_perm(y.w[u / 2], x.w[u / 2], u & 1 ? 0x07060302u : 0x05040100u);
+                F[u] = __builtin_amdgcn_sdot2(__builtin_bit_cast(dev::i16x2, w), j, F[u], false);
+            }
+        };
+        int k = 0;
+        for (; k + 2 <= D; k += 2) pair(rec[k], rec[k + 1]);
+        if (k < D) pair(rec[k], 0u);
+        const int h = hpos[p];
+        const Rows own = sp[p];
+#pragma unroll
+        for (int u = 0; u < NR; ++u) {
+            const int su = (int)(int16_t)(u & 1 ? own.w[u / 2] >> 16 : own.w[u / 2]);
+            acc_h[u] += (long long)su * h;
+            acc_f[u] += (long long)su * F[u];
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < NR; ++u) {
+        long long a = 2 * acc_h[u] + acc_f[u];
+        for (int d = 32; d >= 1; d >>= 1) a += __shfl_down(a, d, 64);
+        if ((tid & 63) == 0) part[tid >> 6][u] = a;
+    }
+    __syncthreads();
+    if (tid < nr) {
+        long long tot = 0;
+        for (int w = 0; w < (T >> 6); ++w) tot += part[w][tid];
+        E[r0 + tid] = tot / 2;
+    }
+}
+
+// The same for problems whose rows do not fit the LDS: a row per workgroup, every
+// neighbour gathered from global memory.
 __global__ __launch_bounds__(256) void energy_kernel(const int32_t *__restrict__ image, int n,
                                                      int D, const int8_t *__restrict__ spins,
                                                      int R, long long *__restrict__ E) {
-    // 2E = sum_i s_i (2 h_i + sum_j J_ij s_j); each workgroup handles one row.
     const int r = blockIdx.x;
     if (r >= R) return;
     const int32_t *order = image + kImgHeader;
-    const int32_t *pos_of = order + n;
     const int32_t *hpos = order + 2 * n;
     const uint32_t *nbr = reinterpret_cast<const uint32_t *>(order + 3 * n);
     const int8_t *s = spins + (size_t)r * n;
@@ -405,7 +481,6 @@ __global__ __launch_bounds__(256) void energy_kernel(const int32_t *__restrict__
         }
         acc += (long long)s[i] * f;
     }
-    (void)pos_of;
     __shared__ long long part[256 / 64];
     for (int d = 32; d >= 1; d >>= 1) acc += __shfl_down(acc, d, 64);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = acc;
@@ -730,11 +805,22 @@ hipError_t launch_sa_stream(const SaLaunch &L, int plan, void *buf, hipStream_t 
     return hipGetLastError();
 }
 
+// LDS of the rows of one workgroup: to n = 16384.  Few sites take small workgroups (more
+// of them on a CU: n = 64, 10^4 rows, 44 us a call with 256 threads, 60 with 1024), many
+// sites large ones, which share the one copy of the rows (n = 8000, 5000 rows: 158 us
+// with 1024, 304 with 256).
+constexpr size_t kEnergyLds = 128 * 1024;
+
 hipError_t launch_energy(const int32_t *image, int n, int D, const int8_t *spins, int R,
                          int64_t *E, hipStream_t s) {
     if (R <= 0) return hipSuccess;
-    hipLaunchKernelGGL(energy_kernel, dim3(R), dim3(256), 0, s, image, n, D, spins, R,
-                       reinterpret_cast<long long *>(E));
+    long long *e = reinterpret_cast<long long *>(E);
+    const size_t lds = (size_t)n * 2 * kEnergyRows;
+    if (lds > kEnergyLds)
+        hipLaunchKernelGGL(energy_kernel, dim3(R), dim3(256), 0, s, image, n, D, spins, R, e);
+    else
+        hipLaunchKernelGGL(energy_rows_kernel, dim3((unsigned)((R + kEnergyRows - 1) / kEnergyRows)),
+                           dim3(n <= 1024 ? 256 : n <= 4096 ? 512 : 1024), lds, s, image, n, D, spins, R, e);
     return hipGetLastError();
 }
 
