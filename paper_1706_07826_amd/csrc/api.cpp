@@ -787,7 +787,24 @@ spv_status spv_sample_last_shape(const spv_ctx *ctx, int32_t *threads, int32_t *
 
 namespace spv {
 
-// Argument checks and launch parameters shared by both persistence entry points;
+// Checks shared by the components' entry points and the multi-start driver.
+spv_status check_components(Ctx *c, const spv_problem *P) {
+    if (components_lds_bytes(P->n) + 256 > c->lds_max)
+        return set_err(c, SPV_ECAPACITY, "spv_components: n=%d exceeds one workgroup's LDS", P->n);
+    return SPV_OK;
+}
+
+spv_status check_merge(Ctx *c, const MergeLaunch &L) {
+    if (L.C < 1 || L.C > L.P->n) return set_err(c, SPV_EINVAL, "spv_merge_components: n_comp=%d", L.C);
+    if (!L.comp || !L.S || !L.merged || !L.merged_E)
+        return set_err(c, SPV_EINVAL, "spv_merge_components: NULL buffer");
+    if ((size_t)L.C * (size_t)L.R > (size_t)1 << 31)
+        return set_err(c, SPV_ECAPACITY, "spv_merge_components: n_comp x R too large");
+    return SPV_OK;
+}
+
+// Argument checks and launch parameters shared by both persistence entry points
+// and the multi-start driver;
 // *scratch_bytes receives the scratch the launch needs.
 spv_status persist_prepare(Ctx *c, const spv_problem *P, const int8_t *samples, const int64_t *energies, int32_t R,
                            double elite_frac, double threshold, int32_t gauge, const spv_fix_out *out, FixLaunch *L,
@@ -1192,8 +1209,7 @@ spv_status spv_components(spv_ctx *ctx, const spv_problem *P, int32_t *comp, int
     if (!n_comp || (P->n > 0 && !comp)) return set_err(c, SPV_EINVAL, "spv_components: NULL output");
     *n_comp = 0;
     if (P->n == 0) return SPV_OK;
-    if (components_lds_bytes(P->n) + 256 > c->lds_max)
-        return set_err(c, SPV_ECAPACITY, "spv_components: n=%d exceeds one workgroup's LDS", P->n);
+    if ((st = check_components(c, P))) return st;
     if ((st = ensure(c, c->merge, 256))) return st;
     int32_t *dcount = static_cast<int32_t *>(c->merge.p);
     hipError_t e = launch_components(P, comp, dcount, stream);
@@ -1219,15 +1235,11 @@ spv_status spv_merge_components(spv_ctx *ctx, const spv_problem *P, const int32_
         if (!merged_E) return set_err(c, SPV_EINVAL, "spv_merge_components: NULL merged_E");
         return hip_check(c, hipMemsetAsync(merged_E, 0, 8ull * R, stream), "memset");
     }
-    if (n_comp < 1 || n_comp > P->n) return set_err(c, SPV_EINVAL, "spv_merge_components: n_comp=%d", n_comp);
-    if (!comp || !samples || !merged || !merged_E)
-        return set_err(c, SPV_EINVAL, "spv_merge_components: NULL buffer");
-    if ((size_t)n_comp * (size_t)R > (size_t)1 << 31)
-        return set_err(c, SPV_ECAPACITY, "spv_merge_components: n_comp x R too large");
+    MergeLaunch L{P, comp, n_comp, samples, R, merged, merged_E, part_E, nullptr};
+    if ((st = check_merge(c, L))) return st;
     if ((st = ensure(c, c->merge, 256 + merge_scratch_bytes(n_comp, R)))) return st;
-    void *scratch = static_cast<unsigned char *>(c->merge.p) + 256;
-    return hip_check(c, launch_merge(P, comp, n_comp, samples, R, merged, merged_E, part_E, scratch, stream),
-                     "merge launch");
+    L.scratch = static_cast<unsigned char *>(c->merge.p) + 256;
+    return hip_check(c, launch_merge(L, stream), "merge launch");
 }
 
 spv_status spv_colour(spv_ctx *ctx, const spv_problem *P0, uint64_t seed, uint8_t *colour, int32_t *n_colours,

@@ -23,10 +23,25 @@ namespace spv {
 
 namespace {
 
-__global__ __launch_bounds__(1024) void comp_kernel(const int32_t *__restrict__ row_ptr,
-                                                    const int32_t *__restrict__ col,
-                                                    const int32_t *__restrict__ J, int n, int nnz,
-                                                    int32_t *__restrict__ comp, int32_t *__restrict__ count) {
+// One problem's components and recombination: for one problem by value, for several
+// (blockIdx.z) from an array.  The kernels are latency-bound on a few workgroups, so
+// several problems' cost little more than one's: 20 problems of n ~ 270, 500 rows each,
+// 1.8 ms one after the other (each with a host read-back of its component count), 0.1 ms
+// together.
+struct MergeJob {
+    const int32_t *row_ptr, *col, *J, *h;
+    int n, nnz, C, R;
+    int32_t *comp, *count;
+    const int8_t *S;
+    long long *keyA, *keyB;
+    int32_t *idxA, *idxB, *inv;
+    long long *part_E, *merged_E;  // part_E: the sorted partial energies
+    int8_t *merged;
+};
+
+__device__ __forceinline__ void components(const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
+                                           const int32_t *__restrict__ J, int n, int nnz,
+                                           int32_t *__restrict__ comp, int32_t *__restrict__ count) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int scan_tmp[1024 / 64 + 1];
     __shared__ int base;
@@ -66,16 +81,14 @@ __global__ __launch_bounds__(1024) void comp_kernel(const int32_t *__restrict__ 
 // Partial energies, component-major: pe[c * R + r] = E_c(r).
 constexpr int kPeLdsComps = 8192;
 
-__global__ __launch_bounds__(256) void partial_energy_kernel(const int32_t *__restrict__ row_ptr,
-                                                             const int32_t *__restrict__ col,
-                                                             const int32_t *__restrict__ J,
-                                                             const int32_t *__restrict__ h, int n,
-                                                             const int32_t *__restrict__ comp, int C,
-                                                             const int8_t *__restrict__ S, int R,
-                                                             long long *__restrict__ pe) {
+__device__ __forceinline__ void partial_energy(const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
+                                               const int32_t *__restrict__ J, const int32_t *__restrict__ h, int n,
+                                               const int32_t *__restrict__ comp, int C,
+                                               const int8_t *__restrict__ S, int R, long long *__restrict__ pe) {
     extern __shared__ __align__(16) unsigned char smem[];
     long long *acc = reinterpret_cast<long long *>(smem);  // [C] when C <= kPeLdsComps
     const int r = blockIdx.x, tid = threadIdx.x, T = blockDim.x;
+    if (r >= R) return;
     const bool lds = C <= kPeLdsComps;
     if (lds)
         for (int c = tid; c < C; c += T) acc[c] = 0;
@@ -99,7 +112,7 @@ __global__ __launch_bounds__(256) void partial_energy_kernel(const int32_t *__re
         for (int c = tid; c < C; c += T) pe[(size_t)c * R + r] = acc[c];
 }
 
-__global__ void fill_i64_kernel(long long *p, size_t count) {
+__device__ __forceinline__ void zero_i64(long long *p, size_t count) {
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < count; i += (size_t)gridDim.x * blockDim.x)
         p[i] = 0;
 }
@@ -110,17 +123,15 @@ __global__ void fill_i64_kernel(long long *p, size_t count) {
 // (digit, thread, position) order keeps equal keys in row order.
 constexpr int kSortThreads = 1024;
 
-__global__ __launch_bounds__(kSortThreads) void component_sort_kernel(long long *__restrict__ keyA,
-                                                                      long long *__restrict__ keyB,
-                                                                      int32_t *__restrict__ idxA,
-                                                                      int32_t *__restrict__ idxB, int R,
-                                                                      int32_t *__restrict__ inv,
-                                                                      long long *__restrict__ part_E) {
+__device__ __forceinline__ void component_sort(long long *__restrict__ keyA, long long *__restrict__ keyB,
+                                               int32_t *__restrict__ idxA, int32_t *__restrict__ idxB, int C, int R,
+                                               int32_t *__restrict__ inv, long long *__restrict__ part_E) {
     extern __shared__ __align__(16) unsigned char smem[];
     int *cnt = reinterpret_cast<int *>(smem);  // [16][T]
     __shared__ int scan_tmp[kSortThreads / 64 + 1];
     __shared__ long long red_min[kSortThreads / 64], red_max[kSortThreads / 64];
     const int c = blockIdx.x, tid = threadIdx.x, T = blockDim.x, lane = dev::lane_id(), wid = tid >> 6;
+    if (c >= C) return;
     long long *ka = keyA + (size_t)c * R, *kb = keyB + (size_t)c * R;
     int32_t *ia = idxA + (size_t)c * R, *ib = idxB + (size_t)c * R;
     // range of the keys
@@ -192,12 +203,13 @@ __global__ __launch_bounds__(kSortThreads) void component_sort_kernel(long long 
     }
     for (int k = tid; k < R; k += T) {
         inv[(size_t)c * R + k] = ia[k];
-        if (part_E) part_E[(size_t)c * R + k] = ka[k] + mn;
+        part_E[(size_t)c * R + k] = ka[k] + mn;
     }
 }
 
-__global__ void merge_rows_kernel(const int8_t *__restrict__ S, int n, int R, const int32_t *__restrict__ comp,
-                                  const int32_t *__restrict__ inv, int8_t *__restrict__ merged) {
+__device__ __forceinline__ void merge_rows(const int8_t *__restrict__ S, int n, int R,
+                                           const int32_t *__restrict__ comp, const int32_t *__restrict__ inv,
+                                           int8_t *__restrict__ merged) {
     const size_t total = (size_t)R * n;
     for (size_t x = blockIdx.x * (size_t)blockDim.x + threadIdx.x; x < total; x += (size_t)gridDim.x * blockDim.x) {
         const int k = (int)(x / n), i = (int)(x - (size_t)k * n);
@@ -206,8 +218,8 @@ __global__ void merge_rows_kernel(const int8_t *__restrict__ S, int n, int R, co
     }
 }
 
-__global__ void merge_energy_kernel(const long long *__restrict__ sorted_E, int C, int R,
-                                    long long *__restrict__ merged_E) {
+__device__ __forceinline__ void merge_energy(const long long *__restrict__ sorted_E, int C, int R,
+                                             long long *__restrict__ merged_E) {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= R) return;
     long long e = 0;
@@ -215,13 +227,114 @@ __global__ void merge_energy_kernel(const long long *__restrict__ sorted_E, int 
     merged_E[k] = e;
 }
 
+struct CompStep {
+    static constexpr int kThreads = 1024;
+    static __device__ __forceinline__ void run(const MergeJob &j) {
+        components(j.row_ptr, j.col, j.J, j.n, j.nnz, j.comp, j.count);
+    }
+};
+struct ZeroStep {  // partial energies accumulated in memory start from zero
+    static constexpr int kThreads = 256;
+    static __device__ __forceinline__ void run(const MergeJob &j) {
+        if (j.C > kPeLdsComps) zero_i64(j.keyA, (size_t)j.C * j.R);
+    }
+};
+struct PartialEnergyStep {
+    static constexpr int kThreads = 256;
+    static __device__ __forceinline__ void run(const MergeJob &j) {
+        partial_energy(j.row_ptr, j.col, j.J, j.h, j.n, j.comp, j.C, j.S, j.R, j.keyA);
+    }
+};
+struct SortStep {
+    static constexpr int kThreads = kSortThreads;
+    static __device__ __forceinline__ void run(const MergeJob &j) {
+        component_sort(j.keyA, j.keyB, j.idxA, j.idxB, j.C, j.R, j.inv, j.part_E);
+    }
+};
+struct MergeRowsStep {
+    static constexpr int kThreads = 256;
+    static __device__ __forceinline__ void run(const MergeJob &j) {
+        merge_rows(j.S, j.n, j.R, j.comp, j.inv, j.merged);
+    }
+};
+struct MergeEnergyStep {
+    static constexpr int kThreads = 256;
+    static __device__ __forceinline__ void run(const MergeJob &j) { merge_energy(j.part_E, j.C, j.R, j.merged_E); }
+};
+
+template <class Step>
+__global__ __launch_bounds__(Step::kThreads) void merge_kernel(const MergeJob job) {
+    Step::run(job);
+}
+
+template <class Step>
+__global__ __launch_bounds__(Step::kThreads) void merge_many_kernel(const MergeJob *__restrict__ jobs) {
+    const MergeJob job = jobs[blockIdx.z];
+    Step::run(job);
+}
+
+MergeJob components_job(const spv_problem *P, int32_t *comp, int32_t *count) {
+    MergeJob j{};
+    j.row_ptr = P->row_ptr;
+    j.col = P->col;
+    j.J = P->J;
+    j.h = P->h;
+    j.n = P->n;
+    j.nnz = P->nnz;
+    j.comp = comp;
+    j.count = count;
+    return j;
+}
+
+MergeJob merge_job(const MergeLaunch &L) {
+    MergeJob j = components_job(L.P, const_cast<int32_t *>(L.comp), nullptr);
+    const size_t cr = (size_t)L.C * L.R;
+    j.C = L.C;
+    j.R = L.R;
+    j.S = L.S;
+    j.keyA = static_cast<long long *>(L.scratch);
+    j.keyB = j.keyA + cr;
+    j.idxA = reinterpret_cast<int32_t *>(j.keyB + cr);
+    j.idxB = j.idxA + cr;
+    j.inv = j.idxB + cr;
+    long long *own = reinterpret_cast<long long *>(reinterpret_cast<unsigned char *>(L.scratch) + cr * 16 +
+                                                   ((cr * 12 + 7) & ~(size_t)7));
+    j.part_E = L.part_E ? reinterpret_cast<long long *>(L.part_E) : own;
+    j.merged_E = reinterpret_cast<long long *>(L.merged_E);
+    j.merged = L.merged;
+    return j;
+}
+
+// The steps of `count` recombinations, each through go(step, grid, lds); the extents are the largest.
+template <class Go>
+hipError_t merge_steps(const MergeLaunch *L, int count, Go go) {
+    int C = 0, R = 0, C_lds = 0;
+    size_t rows = 0, mem = 0;
+    for (int k = 0; k < count; ++k) {
+        C = std::max(C, L[k].C);
+        R = std::max(R, L[k].R);
+        rows = std::max(rows, (size_t)L[k].R * L[k].P->n);
+        if (L[k].C <= kPeLdsComps)
+            C_lds = std::max(C_lds, L[k].C);
+        else
+            mem = std::max(mem, (size_t)L[k].C * L[k].R);
+    }
+    if (R <= 0 || C <= 0) return hipSuccess;
+    if (mem) go(ZeroStep{}, dim3((unsigned)std::min<size_t>((mem + 255) / 256, 4096), 1, count), 0);
+    go(PartialEnergyStep{}, dim3(R, 1, count), (size_t)C_lds * 8);
+    go(SortStep{}, dim3(C, 1, count), (size_t)16 * kSortThreads * 4);
+    if (rows) go(MergeRowsStep{}, dim3((unsigned)std::min<size_t>((rows + 255) / 256, 16384), 1, count), 0);
+    go(MergeEnergyStep{}, dim3((R + 255) / 256, 1, count), 0);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 size_t components_lds_bytes(int n) { return ((size_t)((n + 1) & ~1)) * 2 + 16; }
 
 hipError_t launch_components(const spv_problem *P, int32_t *comp, int32_t *count, hipStream_t s) {
-    hipLaunchKernelGGL(comp_kernel, dim3(1), dim3(1024), components_lds_bytes(P->n), s, P->row_ptr, P->col, P->J,
-                       P->n, P->nnz, comp, count);
+    hipLaunchKernelGGL(merge_kernel<CompStep>, dim3(1), dim3(CompStep::kThreads), components_lds_bytes(P->n), s,
+                       components_job(P, comp, count));
     return hipGetLastError();
 }
 
@@ -233,33 +346,36 @@ size_t merge_scratch_bytes(int C, int R) {
     return cr * (8 + 8) + ((cr * 12 + 7) & ~(size_t)7) + cr * 8 + 256;
 }
 
-hipError_t launch_merge(const spv_problem *P, const int32_t *comp, int C, const int8_t *S, int R, int8_t *merged,
-                        int64_t *merged_E, int64_t *part_E, void *scratch, hipStream_t s) {
-    if (R <= 0 || C <= 0) return hipSuccess;
-    const size_t cr = (size_t)C * R;
-    long long *keyA = static_cast<long long *>(scratch);
-    long long *keyB = keyA + cr;
-    int32_t *idxA = reinterpret_cast<int32_t *>(keyB + cr);
-    int32_t *idxB = idxA + cr;
-    int32_t *inv = idxB + cr;
-    long long *own_sorted = reinterpret_cast<long long *>(reinterpret_cast<unsigned char *>(scratch) + cr * 16 +
-                                                          ((cr * 12 + 7) & ~(size_t)7));
-    long long *sortedE = part_E ? reinterpret_cast<long long *>(part_E) : own_sorted;
-    const bool lds = C <= kPeLdsComps;
-    if (!lds)
-        hipLaunchKernelGGL(fill_i64_kernel, dim3((unsigned)std::min<size_t>((cr + 255) / 256, 4096)), dim3(256), 0, s,
-                           keyA, cr);
-    hipLaunchKernelGGL(partial_energy_kernel, dim3(R), dim3(256), lds ? (size_t)C * 8 : 0, s, P->row_ptr, P->col,
-                       P->J, P->h, P->n, comp, C, S, R, keyA);
-    hipLaunchKernelGGL(component_sort_kernel, dim3(C), dim3(kSortThreads), (size_t)16 * kSortThreads * 4, s, keyA,
-                       keyB, idxA, idxB, R, inv, sortedE);
-    const size_t total = (size_t)R * P->n;
-    if (total)
-        hipLaunchKernelGGL(merge_rows_kernel, dim3((unsigned)std::min<size_t>((total + 255) / 256, 16384)), dim3(256),
-                           0, s, S, P->n, R, comp, inv, merged);
-    hipLaunchKernelGGL(merge_energy_kernel, dim3((R + 255) / 256), dim3(256), 0, s, sortedE, C, R,
-                       reinterpret_cast<long long *>(merged_E));
+hipError_t launch_merge(const MergeLaunch &L, hipStream_t s) {
+    if (L.R <= 0 || L.C <= 0) return hipSuccess;
+    const MergeJob job = merge_job(L);
+    return merge_steps(&L, 1, [&](auto step, dim3 grid, size_t lds) {
+        using Step = decltype(step);
+        hipLaunchKernelGGL(merge_kernel<Step>, grid, dim3(Step::kThreads), lds, s, job);
+    });
+}
+
+size_t merge_job_bytes() { return sizeof(MergeJob); }
+
+void write_components_job(void *jobs, int k, const spv_problem *P, int32_t *comp, int32_t *count) {
+    static_cast<MergeJob *>(jobs)[k] = components_job(P, comp, count);
+}
+
+void write_merge_job(void *jobs, int k, const MergeLaunch &L) { static_cast<MergeJob *>(jobs)[k] = merge_job(L); }
+
+hipError_t launch_components_many(int n_max, int count, const void *jobs, hipStream_t s) {
+    if (count <= 0) return hipSuccess;
+    hipLaunchKernelGGL(merge_many_kernel<CompStep>, dim3(1, 1, count), dim3(CompStep::kThreads),
+                       components_lds_bytes(n_max), s, static_cast<const MergeJob *>(jobs));
     return hipGetLastError();
+}
+
+hipError_t launch_merge_many(const MergeLaunch *L, int count, const void *jobs, hipStream_t s) {
+    return merge_steps(L, count, [&](auto step, dim3 grid, size_t lds) {
+        using Step = decltype(step);
+        hipLaunchKernelGGL(merge_many_kernel<Step>, grid, dim3(Step::kThreads), lds, s,
+                           static_cast<const MergeJob *>(jobs));
+    });
 }
 
 }  // namespace spv

@@ -286,6 +286,13 @@ hipError_t launch_compose(int n_cur, const uint8_t *fm_round, const int8_t *fv_r
                           hipStream_t s);
 hipError_t launch_iota(int n, int32_t *a, uint8_t *fm, int8_t *fv, hipStream_t s);
 hipError_t launch_persist_fix(const FixLaunch &L, hipStream_t s);
+// Several problems in the same launches (descriptors as for launch_merge_many).
+spv_status persist_prepare(Ctx *c, const spv_problem *P, const int8_t *samples, const int64_t *energies, int32_t R,
+                           double elite_frac, double threshold, int32_t gauge, const spv_fix_out *out, FixLaunch *L,
+                           size_t *scratch_bytes);
+size_t fix_job_bytes();
+void write_fix_job(void *jobs, int k, const FixLaunch &L);
+hipError_t launch_persist_fix_many(const FixLaunch *L, int count, const void *jobs, hipStream_t s);
 hipError_t launch_top_gather(const int8_t *ts, const int64_t *te, const int32_t *cnt, const int32_t *off,
                              int lists, int n, int8_t *S, int64_t *E, hipStream_t s);
 
@@ -420,8 +427,26 @@ hipError_t launch_ptx(const PtxLaunch &L, hipStream_t s);
 size_t components_lds_bytes(int n);
 hipError_t launch_components(const spv_problem *P, int32_t *comp, int32_t *count, hipStream_t s);
 size_t merge_scratch_bytes(int C, int R);
-hipError_t launch_merge(const spv_problem *P, const int32_t *comp, int C, const int8_t *S, int R, int8_t *merged,
-                        int64_t *merged_E, int64_t *part_E, void *scratch, hipStream_t s);
+struct MergeLaunch {
+    const spv_problem *P;
+    const int32_t *comp;
+    int C;
+    const int8_t *S;
+    int R;
+    int8_t *merged;
+    int64_t *merged_E, *part_E;  // part_E may be null
+    void *scratch;
+};
+hipError_t launch_merge(const MergeLaunch &L, hipStream_t s);
+spv_status check_components(Ctx *c, const spv_problem *P);
+spv_status check_merge(Ctx *c, const MergeLaunch &L);
+// Several problems in the same launches: descriptors written to host memory (job k of
+// *_job_bytes() each), which the caller copies to the device `jobs` the launches read.
+size_t merge_job_bytes();
+void write_components_job(void *jobs, int k, const spv_problem *P, int32_t *comp, int32_t *count);
+void write_merge_job(void *jobs, int k, const MergeLaunch &L);
+hipError_t launch_components_many(int n_max, int count, const void *jobs, hipStream_t s);
+hipError_t launch_merge_many(const MergeLaunch *L, int count, const void *jobs, hipStream_t s);
 
 // Multi-start driver helpers (multistart.hip).
 // Per-start values of the current stage (device arrays in the driver's working set).

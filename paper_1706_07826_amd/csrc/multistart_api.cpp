@@ -3,10 +3,11 @@
 // stages side by side: every sampling stage is one launch over all starts (the
 // first samples the shared problem as one job; later stages sample each start's
 // own modified problem: SA in one batched launch, SQA a launch per start), and
-// every reduction stage (the correlation step, the SPVAR step of Algorithm 1,
-// the optional tree step) runs per start on the device.  The host reads back
-// the per-start sizes after each reduction; the best recorded state is found
-// and lifted to the full problem on the device.
+// every reduction stage (the correlation step, the SPVAR step of Algorithm 1)
+// and the recombination are one set of launches over all starts; the optional
+// tree step runs per start.  The host reads back the per-start sizes after each
+// reduction; the best recorded state is found and lifted to the full problem on
+// the device.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -22,6 +23,16 @@ namespace {
 
 constexpr int kMaxStarts = 4096;
 constexpr int kStageCorr = 0, kStageFix = 1, kStageTree = 2, kStageSolve = 3;
+
+// Scratch of the starts whose reductions or recombinations run in the same launches:
+// starts beyond it follow in further launches over the same scratch.  256 MB holds
+// hundreds of starts of a few hundred variables.
+// (SPVAR_MS_TOGETHER_KB: a test's limit.)
+size_t together(size_t per, int count) {
+    size_t limit = (size_t)256 << 20;
+    if (const char *v = getenv("SPVAR_MS_TOGETHER_KB")) limit = (size_t)std::max(0, atoi(v)) << 10;
+    return std::min<size_t>(count, std::max<size_t>(1, limit / per));
+}
 
 inline size_t al(size_t b) { return (b + 255) & ~(size_t)255; }
 
@@ -209,16 +220,23 @@ spv_status spv_multistart(spv_ctx *ctx, const spv_problem *P0, const spv_multist
     const size_t o_merge = p;
     if (merge) p += al((size_t)S * Rs * nn);
     const size_t o_comp = p;
-    p += al(4 * nn);
+    if (merge) p += al(4 * nn) * S;
+    const size_t o_count = p;
+    p += al(4ull * S);
+    const size_t o_info = p;
+    p += al(64ull * S);
+    const size_t job_bytes = al((size_t)S * std::max(fix_job_bytes(), merge_job_bytes()));
+    const size_t o_jobs = p;
+    p += job_bytes;
     const size_t o_sb = p;
     p += 2 * al(8ull * S) + al(64);
     const size_t o_lift = p;
     p += 2 * al(nn);
     if ((st = ensure(c, c->ms, p))) return st;
     // Pinned staging: per-start values (off, ncur, n_prev, n_next), level infos,
-    // start bests, the best position, pivots.  The values are rewritten only
-    // after a stream synchronisation, so no copy from them is still in flight.
-    const size_t hb = par_bytes + al(64ull * S) + al(8ull * S) + al(64) + al(4ull * S);
+    // start bests, the best position, pivots, component counts, job descriptors.  The values
+    // are rewritten only after a stream synchronisation, so no copy from them is still in flight.
+    const size_t hb = par_bytes + al(64ull * S) + al(8ull * S) + al(64) + 2 * al(4ull * S) + job_bytes;
     if (c->ms_host_bytes < hb) {
         if (c->ms_host) (void)hipHostFree(c->ms_host);
         c->ms_host = nullptr;
@@ -237,6 +255,10 @@ spv_status spv_multistart(spv_ctx *ctx, const spv_problem *P0, const spv_multist
     int64_t *h_sb = reinterpret_cast<int64_t *>(hbase + par_bytes + al(64ull * S));
     int64_t *h_best = reinterpret_cast<int64_t *>(hbase + par_bytes + al(64ull * S) + al(8ull * S));
     int32_t *h_piv = reinterpret_cast<int32_t *>(hbase + par_bytes + al(64ull * S) + al(8ull * S) + al(64));
+    int32_t *h_count = reinterpret_cast<int32_t *>(reinterpret_cast<unsigned char *>(h_piv) + al(4ull * S));
+    void *h_jobs = reinterpret_cast<unsigned char *>(h_count) + al(4ull * S);
+    void *d_jobs = base + o_jobs;
+    auto upload_jobs = [&](size_t bytes) { return hipMemcpyAsync(d_jobs, h_jobs, bytes, hipMemcpyHostToDevice, stream); };
     MsStageParams dprm;
     dprm.off = reinterpret_cast<const long long *>(base + o_par);
     dprm.ncur = reinterpret_cast<const int *>(base + o_par + al(8ull * S));
@@ -353,15 +375,45 @@ spv_status spv_multistart(spv_ctx *ctx, const spv_problem *P0, const spv_multist
             if (kind == kStageSolve && merge) {
                 // recombination over each modified problem's components (Sec. II.C)
                 int8_t *msp = reinterpret_cast<int8_t *>(base + o_merge);
-                int32_t *comp = reinterpret_cast<int32_t *>(base + o_comp);
+                int32_t *d_count = reinterpret_cast<int32_t *>(base + o_count);
+                auto comp_of = [&](int s) { return reinterpret_cast<int32_t *>(base + o_comp + (size_t)s * al(4 * nn)); };
+                std::vector<int> live;
+                int n_max = 0;
                 for (int s = 0; s < S; ++s) {
                     if (cur[s].n == 0) continue;
-                    int32_t nc = 0;
-                    if ((st = spv_components(ctx, &cur[s], comp, &nc, stream))) return st;
-                    if ((st = spv_merge_components(ctx, &cur[s], comp, nc, start_rows(ks, s), R,
-                                                   msp + (size_t)s * R * nn, rec + (size_t)s * R, nullptr, stream)))
-                        return st;
-                    info[(size_t)s * 8 + 5] = nc;
+                    if ((st = check_components(c, &cur[s]))) return st;
+                    write_components_job(h_jobs, (int)live.size(), &cur[s], comp_of(s), d_count + s);
+                    live.push_back(s);
+                    n_max = std::max(n_max, cur[s].n);
+                }
+                const int count = (int)live.size();
+                if (count > 0) {
+                    if ((e = upload_jobs(count * merge_job_bytes())) == hipSuccess &&
+                        (e = launch_components_many(n_max, count, d_jobs, stream)) == hipSuccess &&
+                        (e = hipMemcpyAsync(h_count, d_count, 4ull * S, hipMemcpyDeviceToHost, stream)) == hipSuccess)
+                        e = hipStreamSynchronize(stream);
+                    if (e != hipSuccess) return hip_check(c, e, "multistart components");
+                    std::vector<MergeLaunch> L(count);
+                    size_t per = 0;
+                    for (int k = 0; k < count; ++k) {
+                        const int s = live[k];
+                        L[k] = MergeLaunch{&cur[s], comp_of(s), h_count[s], start_rows(ks, s), R,
+                                           msp + (size_t)s * R * nn, rec + (size_t)s * R, nullptr, nullptr};
+                        if ((st = check_merge(c, L[k]))) return st;
+                        info[(size_t)s * 8 + 5] = h_count[s];
+                        per = std::max(per, al(merge_scratch_bytes(L[k].C, R)));
+                    }
+                    const int chunk = (int)together(per, count);
+                    if ((st = ensure(c, c->merge, chunk * per))) return st;
+                    for (int k = 0; k < count; ++k) {
+                        L[k].scratch = static_cast<unsigned char *>(c->merge.p) + (size_t)(k % chunk) * per;
+                        write_merge_job(h_jobs, k, L[k]);
+                    }
+                    e = upload_jobs(count * merge_job_bytes());
+                    for (int k = 0; k < count && e == hipSuccess; k += chunk)
+                        e = launch_merge_many(&L[k], std::min(chunk, count - k),
+                                              static_cast<unsigned char *>(d_jobs) + k * merge_job_bytes(), stream);
+                    if (e != hipSuccess) return hip_check(c, e, "multistart merge");
                 }
                 rows_of[ks] = msp;
                 packed[ks] = 0;
@@ -378,7 +430,11 @@ spv_status spv_multistart(spv_ctx *ctx, const spv_problem *P0, const spv_multist
             if (kind == kStageSolve) break;
         }
         // The reduction of this stage, per start (a start whose problem is empty skips it).
+        // Persistence of all starts runs in the same launches.
         bool any = false;
+        std::vector<FixLaunch> fix;
+        std::vector<spv_fix_out> fix_out(S);
+        size_t per = 0;
         for (int s = 0; s < S; ++s) {
             if (cur[s].n == 0) continue;
             any = true;
@@ -386,18 +442,40 @@ spv_status spv_multistart(spv_ctx *ctx, const spv_problem *P0, const spv_multist
             if (kind == kStageTree) {
                 const spv_tree_out t = tree_out_of(L, lo);
                 if ((st = spv_tree_reduce(ctx, &cur[s], &t, stream))) return st;
+                e = hipMemcpyAsync(h_info + (size_t)s * 8, L + lo.info, 64, hipMemcpyDeviceToHost, stream);
+                if (e != hipSuccess) return hip_check(c, e, "multistart level info");
             } else {
                 const bool corr = kind == kStageCorr;
                 const int64_t *E = (corr ? out->corr_E : out->fixing_E) + (size_t)s * R_of[ks - 1];
-                const spv_fix_out fo = fix_out_of(L, lo);
-                if ((st = spv_persist_fix(ctx, &cur[s], start_rows(ks - 1, s), E, R_of[ks - 1],
+                fix_out[s] = fix_out_of(L, lo);
+                fix_out[s].info = reinterpret_cast<int64_t *>(base + o_info) + (size_t)s * 8;
+                FixLaunch F;
+                size_t bytes = 0;
+                if ((st = persist_prepare(c, &cur[s], start_rows(ks - 1, s), E, R_of[ks - 1],
                                           corr ? prm->corr_elite_frac : prm->elite_frac,
-                                          corr ? prm->corr_threshold : prm->threshold, corr ? 1 : prm->gauge, &fo,
-                                          stream)))
+                                          corr ? prm->corr_threshold : prm->threshold, corr ? 1 : prm->gauge,
+                                          &fix_out[s], &F, &bytes)))
                     return st;
+                per = std::max(per, al(bytes));
+                fix.push_back(F);
             }
-            e = hipMemcpyAsync(h_info + (size_t)s * 8, L + lo.info, 64, hipMemcpyDeviceToHost, stream);
-            if (e != hipSuccess) return hip_check(c, e, "multistart level info");
+        }
+        if (!fix.empty()) {
+            const int count = (int)fix.size();
+            const int chunk = (int)together(per, count);
+            if ((st = ensure(c, c->scratch, chunk * per))) return st;
+            for (int k = 0; k < count; ++k) {
+                fix[k].scratch = static_cast<unsigned char *>(c->scratch.p) + (size_t)(k % chunk) * per;
+                fix[k].scratch_bytes = per;
+                write_fix_job(h_jobs, k, fix[k]);
+            }
+            e = upload_jobs(count * fix_job_bytes());
+            for (int k = 0; k < count && e == hipSuccess; k += chunk)
+                e = launch_persist_fix_many(&fix[k], std::min(chunk, count - k),
+                                            static_cast<unsigned char *>(d_jobs) + k * fix_job_bytes(), stream);
+            if (e == hipSuccess)
+                e = hipMemcpyAsync(h_info, base + o_info, 64ull * S, hipMemcpyDeviceToHost, stream);
+            if (e != hipSuccess) return hip_check(c, e, "multistart persistence");
         }
         if (!any) {
             ++nl;

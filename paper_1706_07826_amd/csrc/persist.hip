@@ -19,6 +19,7 @@
 //                     folds fixed neighbours into h', reduces the offset.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "device.hpp"
@@ -125,8 +126,7 @@ __device__ __forceinline__ unsigned long long order_key(long long e) {
 constexpr int kEliteWaves = 1024 / 64;
 
 template <int KR>
-__global__ __launch_bounds__(1024) void elite_kernel(const long long *__restrict__ E, int R, int m,
-                                                     FixScratch f) {
+__device__ __forceinline__ void elite(const long long *__restrict__ E, int R, int m, const FixScratch &f) {
     __shared__ __align__(16) unsigned int hist[kEliteWaves][256];
     __shared__ unsigned long long kmin_w[kEliteWaves], kmax_w[kEliteWaves];
     __shared__ unsigned long long prefix_s;
@@ -285,14 +285,16 @@ __global__ __launch_bounds__(1024) void elite_kernel(const long long *__restrict
 }
 
 // 2. Column bitmaps: word w of variable i = ballot over elite rows 64w..64w+63 of s = +1.
-__global__ __launch_bounds__(64) void bitmap_kernel(const int8_t *__restrict__ S, int n, int m,
-                                                    FixScratch f, int cols_per_block, int clear) {
-    const int w = blockIdx.x;
+constexpr int kBitmapCols = 64;  // a multiple of 4 (the 4-column reads)
+
+__device__ __forceinline__ void bitmap(const int8_t *__restrict__ S, int n, int m, const FixScratch &f, bool clear) {
+    const int w = blockIdx.x, groups = (n + kBitmapCols - 1) / kBitmapCols;
+    if (w >= f.W || (int)blockIdx.y >= groups) return;
     const int lane = threadIdx.x;
     // the gauge's hash table for the next kernel: keys and counts zero, minima at the top
     // (TS words of keys, TS / 2 of counts; TS < 4 n, so a workgroup clears a few words)
     if (clear)
-        for (int k = (blockIdx.y * gridDim.x + w) * 64 + lane; k < f.TS + f.TS / 2; k += 64 * gridDim.x * gridDim.y) {
+        for (int k = (blockIdx.y * f.W + w) * 64 + lane; k < f.TS + f.TS / 2; k += 64 * f.W * groups) {
             f.tkey[k] = 0ull;
             if (k < f.TS) f.tmin[k] = 0x7FFFFFFF;
         }
@@ -300,12 +302,12 @@ __global__ __launch_bounds__(64) void bitmap_kernel(const int8_t *__restrict__ S
     const bool valid = e < m;
     const int row = valid ? f.elite[e] : 0;
     const int8_t *srow = S + (size_t)row * n;
-    const int i0 = blockIdx.y * cols_per_block;
-    const int i1 = min(n, i0 + cols_per_block);
+    const int i0 = blockIdx.y * kBitmapCols;
+    const int i1 = min(n, i0 + kBitmapCols);
     bool bad = false;
     int i = i0;
     // rows read 4 columns at a time when every row starts on a 4-byte boundary
-    // (cols_per_block is a multiple of 4, so i0 keeps that alignment)
+    // (i0 is a multiple of 4, so it keeps that alignment)
     if ((n & 3) == 0 && (reinterpret_cast<uintptr_t>(S) & 3) == 0) {
         for (; i + 4 <= i1; i += 4) {
             const uint32_t v4 = valid ? *reinterpret_cast<const uint32_t *>(srow + i) : 0x01010101u;
@@ -344,7 +346,7 @@ __device__ __forceinline__ unsigned long long mix64(unsigned long long z) {
 }
 
 // 3a. Hash canonical columns into the open-addressing table.
-__global__ __launch_bounds__(256) void gauge_hash_kernel(int n, int m, FixScratch f) {
+__device__ __forceinline__ void gauge_hash(int n, int m, const FixScratch &f) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const unsigned long long *bi = f.bits + (size_t)i * f.W;
@@ -365,7 +367,7 @@ __global__ __launch_bounds__(256) void gauge_hash_kernel(int n, int m, FixScratc
 }
 
 // 3b. Largest class -> pivot (-1: no gauge); verify the pivot class exactly.  The whole
-// workgroup of fix_reduce_kernel calls it.
+// workgroup of the reduction calls it.
 __device__ __forceinline__ int gauge_pivot(const int32_t *__restrict__ h, int n, int m, int mode,
                                            const FixScratch &f) {
     __shared__ unsigned long long best[1024 / 64];
@@ -456,7 +458,7 @@ struct ReduceArgs {
 };
 
 // 4. Fix and reduce (one workgroup; phases separated by barriers).
-__global__ __launch_bounds__(1024) void fix_reduce_kernel(ReduceArgs a, FixScratch f) {
+__device__ __forceinline__ void fix_reduce(const ReduceArgs &a, const FixScratch &f) {
     __shared__ int tmp[1024 / 64 + 1];
     __shared__ long long part[1024 / 64];
     __shared__ int range_bad;
@@ -558,6 +560,49 @@ __global__ __launch_bounds__(1024) void fix_reduce_kernel(ReduceArgs a, FixScrat
     }
 }
 
+// One problem's persistence, and its steps as they are launched: for one problem by
+// value, for several (blockIdx.z) from an array.  A problem's steps are latency-bound on
+// a few workgroups, so several problems' cost little more than one's: 20 problems of
+// n = 512, 500 rows each, 480 us one after the other, 28 us together.
+struct FixJob {
+    const long long *E;
+    const int8_t *S;
+    int R;
+    ReduceArgs a;
+    FixScratch f;
+};
+
+template <int KR>
+struct EliteStep {
+    static constexpr int kThreads = 1024;
+    static __device__ __forceinline__ void run(const FixJob &j) { elite<KR>(j.E, j.R, j.a.m, j.f); }
+};
+struct BitmapStep {
+    static constexpr int kThreads = 64;
+    static __device__ __forceinline__ void run(const FixJob &j) {
+        bitmap(j.S, j.a.n, j.a.m, j.f, j.a.gauge_mode != 0);
+    }
+};
+struct GaugeHashStep {
+    static constexpr int kThreads = 256;
+    static __device__ __forceinline__ void run(const FixJob &j) { gauge_hash(j.a.n, j.a.m, j.f); }
+};
+struct FixReduceStep {
+    static constexpr int kThreads = 1024;
+    static __device__ __forceinline__ void run(const FixJob &j) { fix_reduce(j.a, j.f); }
+};
+
+template <class Step>
+__global__ __launch_bounds__(Step::kThreads) void fix_kernel(const FixJob job) {
+    Step::run(job);
+}
+
+template <class Step>
+__global__ __launch_bounds__(Step::kThreads) void fix_many_kernel(const FixJob *__restrict__ jobs) {
+    const FixJob job = jobs[blockIdx.z];
+    Step::run(job);
+}
+
 // Iterated rounds: fold a round's fixes into original indices and compose the
 // reduced -> original map.
 __global__ void compose_kernel(int n_cur, const uint8_t *__restrict__ fm_round,
@@ -633,34 +678,22 @@ size_t fix_scratch_bytes(int n, int R, int m) {
            2 * align8((size_t)n * 4) + 64;
 }
 
-hipError_t launch_persist_fix(const FixLaunch &L, hipStream_t s) {
+namespace {
+
+FixJob fix_job(const FixLaunch &L) {
     const spv_problem *P = L.P;
-    const int n = P->n;
-    FixScratch f = carve(L.scratch, n, L.R, L.m);
-    // rows held per lane: as few as hold R (all KR slots are worked through)
-    auto elite = L.R <= 1024 ? elite_kernel<1> : L.R <= 4096 ? elite_kernel<4> : L.R <= 16384 ? elite_kernel<16>
-                                                                                             : elite_kernel<0>;
-    hipLaunchKernelGGL(elite, dim3(1), dim3(1024), 0, s, reinterpret_cast<const long long *>(L.energies), L.R, L.m,
-                       f);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const int cols = 64;  // a multiple of 4 (the kernel's 4-column reads)
-    if (n > 0) {
-        hipLaunchKernelGGL(bitmap_kernel, dim3(f.W, (n + cols - 1) / cols), dim3(64), 0, s,
-                           L.samples, n, L.m, f, cols, L.gauge_mode != 0 ? 1 : 0);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    if (L.gauge_mode != 0 && n > 0) {
-        hipLaunchKernelGGL(gauge_hash_kernel, dim3((n + 255) / 256), dim3(256), 0, s, n, L.m, f);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    ReduceArgs a;
+    FixJob j;
+    j.E = reinterpret_cast<const long long *>(L.energies);
+    j.S = L.samples;
+    j.R = L.R;
+    j.f = carve(L.scratch, P->n, L.R, L.m);
+    ReduceArgs &a = j.a;
     a.row_ptr = P->row_ptr;
     a.col = P->col;
     a.J = P->J;
     a.h = P->h;
     a.colour = P->colour;
-    a.n = n;
+    a.n = P->n;
     a.nnz = P->nnz;
     a.m = L.m;
     a.kmin = L.kmin;
@@ -674,8 +707,63 @@ hipError_t launch_persist_fix(const FixLaunch &L, hipStream_t s) {
     a.colour_o = L.out->colour;
     a.orig_o = L.out->orig_index;
     a.info = reinterpret_cast<long long *>(L.out->info);
-    hipLaunchKernelGGL(fix_reduce_kernel, dim3(1), dim3(1024), 0, s, a, f);
+    return j;
+}
+
+// The steps of `count` problems (the extents are the largest of them), each through go(step, grid).
+template <class Go>
+hipError_t fix_steps(int n, int R, int W, bool gauge, int count, Go go) {
+    // rows held per lane: as few as hold R (all KR slots are worked through)
+    if (R <= 1024)
+        go(EliteStep<1>{}, dim3(1, 1, count));
+    else if (R <= 4096)
+        go(EliteStep<4>{}, dim3(1, 1, count));
+    else if (R <= 16384)
+        go(EliteStep<16>{}, dim3(1, 1, count));
+    else
+        go(EliteStep<0>{}, dim3(1, 1, count));
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (n > 0) {
+        go(BitmapStep{}, dim3(W, (n + kBitmapCols - 1) / kBitmapCols, count));
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        if (gauge) {
+            go(GaugeHashStep{}, dim3((n + 255) / 256, 1, count));
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+        }
+    }
+    go(FixReduceStep{}, dim3(1, 1, count));
     return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_persist_fix(const FixLaunch &L, hipStream_t s) {
+    const FixJob job = fix_job(L);
+    return fix_steps(L.P->n, L.R, job.f.W, L.gauge_mode != 0, 1, [&](auto step, dim3 grid) {
+        using Step = decltype(step);
+        hipLaunchKernelGGL(fix_kernel<Step>, grid, dim3(Step::kThreads), 0, s, job);
+    });
+}
+
+size_t fix_job_bytes() { return sizeof(FixJob); }
+
+void write_fix_job(void *jobs, int k, const FixLaunch &L) { static_cast<FixJob *>(jobs)[k] = fix_job(L); }
+
+hipError_t launch_persist_fix_many(const FixLaunch *L, int count, const void *jobs, hipStream_t s) {
+    if (count <= 0) return hipSuccess;
+    int n = 0, R = 0, W = 0;
+    bool gauge = false;
+    for (int k = 0; k < count; ++k) {
+        n = std::max(n, L[k].P->n);
+        R = std::max(R, L[k].R);
+        W = std::max(W, (L[k].m + 63) / 64);
+        gauge |= L[k].gauge_mode != 0;
+    }
+    return fix_steps(n, R, W, gauge, count, [&](auto step, dim3 grid) {
+        using Step = decltype(step);
+        hipLaunchKernelGGL(fix_many_kernel<Step>, grid, dim3(Step::kThreads), 0, s, static_cast<const FixJob *>(jobs));
+    });
 }
 
 }  // namespace spv
