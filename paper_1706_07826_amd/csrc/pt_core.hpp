@@ -66,28 +66,51 @@ __device__ __forceinline__ uint32_t metropolis_mask4(const int32_t x[4], const u
     return mask;
 }
 
-// Replica-exchange decision (digit test of D with the tables of dbeta_k).  The
-// thresholds of every nonzero digit are fetched together, then compared.
+// Replica-exchange decision (digit test of D with the tables of dbeta_k), in three
+// steps: the thresholds of every nonzero digit are fetched together, the random words
+// drawn, then compared.
+struct SwapTest {
+    uint32_t d[7], th[7];
+    bool never;  // D beyond the tables
+};
+
+__device__ __forceinline__ SwapTest swap_load(long long D, const uint32_t *__restrict__ T, int nd) {
+    SwapTest s;
+    s.never = D > 0 && nd < 7 && (D >> (kDigitBits * nd)) != 0;
+    const bool draw = D > 0 && !s.never;
+#pragma unroll
+    for (int j = 0; j < 7; ++j) {
+        s.d[j] = draw && j < nd ? (uint32_t)((D >> (kDigitBits * j)) & (kDigitSize - 1)) : 0u;
+        s.th[j] = s.d[j] ? T[j * kDigitSize + s.d[j]] : 0u;
+    }
+    return s;
+}
+
+__device__ __forceinline__ void swap_draw(int nd, uint32_t k, uint32_t t, uint32_t c, uint32_t k0, uint32_t k1,
+                                          dev::Words4 &w0, dev::Words4 &w1) {
+    w0 = dev::philox(k, t, c, 3u << 24, k0, k1);
+    w1 = w0;
+    if (nd > 4) w1 = dev::philox(k, t, c, (3u << 24) | 1u, k0, k1);
+}
+
+__device__ __forceinline__ bool swap_accept(const SwapTest &s, const dev::Words4 &w0, const dev::Words4 &w1) {
+    bool ok = !s.never;
+#pragma unroll
+    for (int j = 0; j < 7; ++j) {
+        const uint32_t w = j < 4 ? w0.w[j] : w1.w[j - 4];
+        if (s.d[j]) ok = ok && (w < s.th[j]);
+    }
+    return ok;
+}
+
 __device__ inline bool swap_test(long long D, const uint32_t *__restrict__ T, int nd, uint32_t k, uint32_t t,
                                  uint32_t c, uint32_t k0, uint32_t k1) {
     if (D <= 0) return true;
     if (nd < 7 && (D >> (kDigitBits * nd)) != 0) return false;
-    uint32_t d[7], th[7];
-#pragma unroll
-    for (int j = 0; j < 7; ++j) {
-        d[j] = j < nd ? (uint32_t)((D >> (kDigitBits * j)) & (kDigitSize - 1)) : 0u;
-        th[j] = d[j] ? T[j * kDigitSize + d[j]] : 0u;
-    }
-    dev::Words4 w0 = dev::philox(k, t, c, 3u << 24, k0, k1);
-    dev::Words4 w1 = w0;
-    if (nd > 4) w1 = dev::philox(k, t, c, (3u << 24) | 1u, k0, k1);
-    bool ok = true;
-#pragma unroll
-    for (int j = 0; j < 7; ++j) {
-        const uint32_t w = j < 4 ? w0.w[j] : w1.w[j - 4];
-        if (d[j]) ok = ok && (w < th[j]);
-    }
-    return ok;
+    const SwapTest s = swap_load(D, T, nd);
+    dev::Words4 w0, w1;
+    swap_draw(nd, k, t, c, k0, k1, w0, w1);
+    return swap_accept(s, w0, w1);
 }
 
 // Neighbour records are fetched this many at a time when their count is only known at

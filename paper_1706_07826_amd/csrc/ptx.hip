@@ -89,7 +89,7 @@ struct PtxLds {
     int32_t *Lins;      // [chains*m] entry a list's offer replaces this sweep (-1: none)
     long long *Lmax;    // [chains*m] a full list's largest energy (LLONG_MAX: not known)
     int32_t *snd;       // [m + 1] digit counts of the swap tables of pairs s0-1 .. s0+m-1
-    int32_t *acc;       // [chains*m] accepted in-group pairs: their replicas' byte offsets
+    int32_t *acc;       // [nq <= chains*m] per word: bytes that take their successor (bits 0-3), predecessor (4-7)
     int32_t *cin;       // [2*chains] accepted boundary pairs (side, chain)
     uint16_t *parent;          // [pairs][n rounded to even] union-find forests over positions
     unsigned long long *dmask; // [pairs][ceil(n / 64)] disagreement masks in variable order
@@ -169,7 +169,7 @@ __global__ void xw_zero_kernel(uint32_t *w, size_t count) {
 
 // a byte in LDS, addressed with 32-bit offsets
 typedef __attribute__((address_space(3))) const unsigned char lds_u8;
-typedef __attribute__((address_space(3))) unsigned char lds_mu8;
+typedef __attribute__((address_space(3))) uint32_t lds_mu32;
 
 // What a launch's groups do between exchanges, fixed at compile time for the common
 // shapes: one kernel with every body in it held 128 registers and spilled 132 bytes (216
@@ -183,6 +183,46 @@ enum PtxMove {
     kMovePacked,  // the same, both chains' bytes of the group's slot in one word per site
     kMoveAny      // up to kIcmBatch pairs at a time (or none, or one), decided at run time
 };
+
+template <int CTRL>
+__device__ __forceinline__ int32_t row_move(int32_t v) {
+    return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xF, 0xF, false);
+}
+
+// v summed over the rows 0 and 1, 2 and 3 (lane by lane), and over the two halves: a swap
+// of a register with its copy leaves one operand of the sum in each.
+__device__ __forceinline__ int32_t add_row_pairs(int32_t v) {
+    const auto r = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
+    return (int32_t)(r[0] + r[1]);
+}
+__device__ __forceinline__ int32_t add_halves(int32_t v) {
+    const auto r = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
+    return (int32_t)(r[0] + r[1]);
+}
+
+// Every lane of a row of 16 gets the row's entry ordered last by (energy, stamp): a
+// butterfly of DPP moves (quads by two permutations, then the two mirrors).
+__device__ __forceinline__ void last_of_16(long long &e, int32_t &w, int32_t &i) {
+    auto step = [&](auto move) __attribute__((always_inline)) {
+        const long long oe = (long long)(((unsigned long long)(uint32_t)move((int32_t)(e >> 32)) << 32) |
+                                         (uint32_t)move((int32_t)e));
+        const int32_t ow = move(w), oi = move(i);
+        if (oe > e || (oe == e && ow > w)) {
+            e = oe;
+            w = ow;
+            i = oi;
+        }
+    };
+    step([](int32_t v) { return row_move<0xB1>(v); });
+    step([](int32_t v) { return row_move<0x4E>(v); });
+    step([](int32_t v) { return row_move<0x141>(v); });
+    step([](int32_t v) { return row_move<0x140>(v); });
+}
+
+__device__ __forceinline__ unsigned long long read_first(unsigned long long v) {
+    return ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) |
+           (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+}
 
 // ND threshold digits; BIG: instance read from the global image; DK: records per
 // site fixed at compile time (0: D at run time).
@@ -221,7 +261,17 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
     auto *const L_ubuf = Lay.ubuf;
     auto *const L_ubj = Lay.ubj;
     auto *const L_es = Lay.esite;
-    const int tid = threadIdx.x, T = blockDim.x, lane = dev::lane_id(), wid = tid >> 6, nw = T >> 6;
+    int tid = threadIdx.x, lane = dev::lane_id(), wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int T = blockDim.x, nw = T >> 6;
+    // Thread, lane and wavefront as new values for each phase of a sweep: what a phase
+    // derives from them (addresses above all) is not kept in registers, and spilled,
+    // across the others.
+    auto phase = [&]() __attribute__((always_inline)) {
+#ifdef __OPTIMIZE__
+        asm volatile("" : "+v"(tid), "+v"(lane));
+#endif
+        wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    };
     const int run = blockIdx.x / G, g = blockIdx.x - run * G;
     const int s0 = g * a.m, mg = min(a.m, K - s0);
     // byte of its quad word that holds the group's first slot of a chain; with K a
@@ -261,7 +311,19 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
         const int ch = l / mg, o = l - ch * mg + boff_of(ch);
         return Sb + ((size_t)p * nq + ch * qpc + (o >> 2)) * 4 + (o & 3);
     };
-    // a replica's bytes lie pst apart: loops over positions take sbyte(l, 0) once
+    // its byte at position 0 (chain ch, slot s0 + o); a replica's bytes lie pst apart
+    auto sbase = [=](int ch, int o) __attribute__((always_inline)) -> unsigned char * {
+        if (pk) return Sb + ch;
+        const int b = o + boff_of(ch);
+        return Sb + (ch * qpc + (b >> 2)) * 4 + (b & 3);
+    };
+    // x = chain * per + rest, by subtraction (few chains; a division by a run-time value
+    // costs some forty instructions, in phases where every instruction is waited for)
+    auto chain_of = [](int &x, int per) __attribute__((always_inline)) -> int {
+        int ch = 0;
+        for (; x >= per; x -= per) ++ch;
+        return ch;
+    };
     const uint32_t pst = (uint32_t)nq * 4u;
 
     if (tid <= a.C) cs[tid] = img[3 + tid];
@@ -417,6 +479,7 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
     };
 
     for (int ls = 0; ls < a.sweeps; ++ls) {
+        phase();
         const uint32_t t = a.sweep_offset + (uint32_t)ls;
         // 1. Metropolis on the group's replicas (costs and their sums scaled by 2^SH).
         constexpr int SH = core::field_shift<ND>;
@@ -599,7 +662,38 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
         }
 #pragma unroll
         for (int b = 0; b < 4; ++b) dE[b] = 2 * (dE[b] >> SH);  // a flip changes E by 2 x
-        if (pow2) {
+        if (pow2 && (ND == 1 || (ND == 2 && n < 8192))) {
+            // |sum over the sites| < n 512^ND < 2^31: summed over the wavefront in 32 bits by
+            // DPP moves and lane swaps.  (The 64-bit shuffles below are 40 LDS operations a
+            // wavefront: 5000 of 28000 clocks of a sweep of the L = 10 cube, 8 slots a group.)
+            int32_t s4[4];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) s4[b] = (int32_t)(dE[b] >> 1);
+            if (nq <= 1)
+#pragma unroll
+                for (int b = 0; b < 4; ++b) s4[b] += row_move<0xB1>(s4[b]);
+            if (nq <= 2)
+#pragma unroll
+                for (int b = 0; b < 4; ++b) s4[b] += row_move<0x4E>(s4[b]);
+            if (nq <= 4)
+#pragma unroll
+                for (int b = 0; b < 4; ++b) s4[b] += row_move<0x124>(s4[b]);
+            if (nq <= 8)
+#pragma unroll
+                for (int b = 0; b < 4; ++b) s4[b] += row_move<0x128>(s4[b]);
+            if (nq <= 16)
+#pragma unroll
+                for (int b = 0; b < 4; ++b) s4[b] = add_row_pairs(s4[b]);
+            if (nq <= 32)
+#pragma unroll
+                for (int b = 0; b < 4; ++b) s4[b] = add_halves(s4[b]);
+            if (active && lane < nq)
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+                    if (s4[b])
+                        atomicAdd(reinterpret_cast<unsigned long long *>(&L_E[loc[b]]),
+                                  (unsigned long long)(2ll * s4[b]));
+        } else if (pow2) {
 #pragma unroll
             for (int b = 0; b < 4; ++b)
                 for (int off = nq; off < 64; off <<= 1) dE[b] += __shfl_xor(dE[b], off, 64);
@@ -614,9 +708,11 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
         }
         if (tid == 0) nacc = 0;
         if (tid < 2 * chains) L_cin[tid] = 0;
+        for (int w = tid; w < nq; w += T) L_acc[w] = 0;
         __syncthreads();
 
         // 2. Replica exchange.
+        phase();
         // This sweep's pairs (k, k+1) have k of parity par: nin of them lie inside the
         // group from slot kin on; lo_act / hi_act: the pair across the lower / upper
         // boundary is one of them.  Each boundary pair comes every other sweep, so
@@ -650,7 +746,7 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
                 if (side == 0 ? !lo_act : !hi_act) continue;
                 for (int ch = 0; ch < chains; ++ch) {
                     const int l = ch * mg + (side ? mg - 1 : 0);
-                    const unsigned char *rb = sbyte(l, 0);
+                    const unsigned char *rb = sbase(ch, side ? mg - 1 : 0);
                     uint32_t *dst = msg(g, side, ch);
                     const unsigned long long El = (unsigned long long)L_E[l];
                     for (int w = tid; w < xmsg; w += T) {
@@ -665,91 +761,88 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
                     }
                 }
             }
-            __syncthreads();
         }
-        {
-            const int per = nin + (edge ? 2 : 0);      // + the straddling pairs
-            if (tid < chains * per) {
-                const int ch = tid / per, e = tid - ch * per;
-                const uint32_t cctr = (uint32_t)(run * chains + ch);
-                if (e < nin) {
-                    const int k = kin + 2 * e;
-                    const int la = ch * mg + (k - s0);
-                    const long long Dd = L_E[la] - L_E[la + 1];
-                    if (swap_test(Dd, a.stab + (size_t)k * 7 * kDigitSize, L_snd[k - s0 + 1], (uint32_t)k, t, cctr, a.k0,
-                                  a.k1)) {
-                        const long long x = L_E[la];
-                        L_E[la] = L_E[la + 1];
-                        L_E[la + 1] = x;
-                        // the pair's byte offsets of its two replicas (at position 0)
-                        const int ix = atomicAdd(&nacc, 1);
-                        L_acc[2 * ix] = (int)(sbyte(la, 0) - Sb);
-                        L_acc[2 * ix + 1] = (int)(sbyte(la + 1, 0) - Sb);
-                    }
-                } else if ((e == nin && lo_act) || (e == nin + 1 && hi_act)) {
-                    // the pair straddling a group boundary: (s0 - 1, s0) against the lower
-                    // neighbour's last slot, (s0 + mg - 1, s0 + mg) against the upper one's first
-                    const int side = e - nin;
-                    const uint32_t *m = msg(side == 0 ? g - 1 : g + 1, side == 0 ? 1 : 0, ch);
-                    // the four energy words are loaded together (one round trip when the
-                    // message is there); a word without the expected tag is waited for
-                    uint32_t ew[4];
+        // The pairs' decisions, a thread each.  What does not need a neighbour's energy (an
+        // in-group pair's thresholds, every pair's random words) is done before the wait.
+        const int per = nin + (edge ? 2 : 0);      // + the straddling pairs
+        int pe = tid;
+        const int pch = tid < chains * per ? chain_of(pe, per) : 0;
+        const bool inner = pe < nin, lower = pe == nin;
+        const bool decides = tid < chains * per && (inner || (lower ? lo_act : hi_act));
+        const int pk0 = inner ? kin + 2 * pe : lower ? s0 - 1 : s0 + mg - 1;  // the pair (k, k + 1)
+        const int pl = pch * mg + (inner ? pk0 - s0 : lower ? 0 : mg - 1);     // its own (lower) replica
+        ptc::SwapTest test;
+        dev::Words4 w0, w1;
+        const uint32_t *stab = a.stab + (size_t)(decides ? pk0 : 0) * 7 * kDigitSize;
+        int pnd = 0;
+        if (decides) {
+            pnd = L_snd[pk0 - s0 + 1];
+            if (inner) test = ptc::swap_load(L_E[pl] - L_E[pl + 1], stab, pnd);
+            ptc::swap_draw(pnd, (uint32_t)pk0, t, (uint32_t)(run * chains + pch), a.k0, a.k1, w0, w1);
+        }
+        if (edge) __syncthreads();
+        if (decides && inner) {
+            if (ptc::swap_accept(test, w0, w1)) {
+                const long long x = L_E[pl];
+                L_E[pl] = L_E[pl + 1];
+                L_E[pl + 1] = x;
+                // the pair's replicas are neighbouring bytes of a site's words: the lower one
+                // takes its successor (bit 0..3), the upper its predecessor (bit 4..7)
+                const int o = (int)(sbase(pch, pk0 - s0) - Sb);
+                nacc = 1;
+                atomicOr(&L_acc[o >> 2], 1 << (o & 3));
+                atomicOr(&L_acc[(o + 1) >> 2], 16 << ((o + 1) & 3));
+            }
+        } else if (decides) {
+            // the pair straddling a group boundary: (s0 - 1, s0) against the lower
+            // neighbour's last slot, (s0 + mg - 1, s0 + mg) against the upper one's first
+            const uint32_t *m = msg(lower ? g - 1 : g + 1, lower ? 1 : 0, pch);
+            // the four energy words are loaded together (one round trip when the
+            // message is there); a word without the expected tag is waited for
+            uint32_t ew[4];
 #pragma unroll
-                    for (int w = 0; w < 4; ++w) ew[w] = __hip_atomic_load(m + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    unsigned long long eu = 0;
-                    bool ok = true;
+            for (int w = 0; w < 4; ++w) ew[w] = __hip_atomic_load(m + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            unsigned long long eu = 0;
+            bool ok = true;
 #pragma unroll
-                    for (int w = 0; w < 4; ++w) {
-                        const int v = (ew[w] & 0xFFFF0000u) == tag ? (int)(ew[w] & 0xFFFFu) : recv(m + w);
-                        ok = ok && v >= 0;
-                        eu |= (unsigned long long)(v < 0 ? 0 : v) << (16 * w);
-                    }
-                    if (!ok) {
-                        stop = 1;
-                    } else {
-                        const long long En = (long long)eu;
-                        const int lo = ch * mg + (side == 0 ? 0 : mg - 1);
-                        const int k = side == 0 ? s0 - 1 : s0 + mg - 1;
-                        const long long Dd = side == 0 ? En - L_E[lo] : L_E[lo] - En;
-                        if (swap_test(Dd, a.stab + (size_t)k * 7 * kDigitSize, L_snd[k - s0 + 1], (uint32_t)k, t, cctr,
-                                      a.k0, a.k1)) {
-                            L_E[lo] = En;
-                            L_cin[side * chains + ch] = 1;
-                        }
-                    }
+            for (int w = 0; w < 4; ++w) {
+                const int v = (ew[w] & 0xFFFF0000u) == tag ? (int)(ew[w] & 0xFFFFu) : recv(m + w);
+                ok = ok && v >= 0;
+                eu |= (unsigned long long)(v < 0 ? 0 : v) << (16 * w);
+            }
+            if (!ok) {
+                stop = 1;
+            } else {
+                const long long En = (long long)eu;
+                test = ptc::swap_load(lower ? En - L_E[pl] : L_E[pl] - En, stab, pnd);
+                if (ptc::swap_accept(test, w0, w1)) {
+                    L_E[pl] = En;
+                    L_cin[(lower ? 0 : chains) + pch] = 1;
                 }
             }
         }
         __syncthreads();
         if (stop) break;
         {
-            // accepted pairs swap their bytes four pairs at a time, every load before
-            // the stores (the pairs' replicas are distinct)
-            const int na = nacc;
-            for (int pr0 = 0; pr0 < na; pr0 += 4) {
-                const int nb = min(4, na - pr0);
-                uint32_t oa[4], ob[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int pr = pr0 + min(u, nb - 1);
-                    oa[u] = (uint32_t)L_acc[2 * pr];
-                    ob[u] = (uint32_t)L_acc[2 * pr + 1];
-                }
-                lds_mu8 *const S3 = (lds_mu8 *)Sb;
+            // accepted pairs swap their bytes word by word, a site's words by one thread
+            // (a byte moves by one place, within its word or to the next one)
+            if (nacc) {
+                lds_mu32 *const S3 = (lds_mu32 *)L_S;
                 for (int p = tid; p < n; p += T) {
-                    const uint32_t o = (uint32_t)p * pst;
-                    unsigned char x[4], y[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        x[u] = S3[oa[u] + o];
-                        y[u] = S3[ob[u] + o];
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u)
-                        if (u < nb) {
-                            S3[oa[u] + o] = y[u];
-                            S3[ob[u] + o] = x[u];
+                    const uint32_t o = (uint32_t)p * (uint32_t)nq;
+                    uint32_t prev = 0, cur = S3[o];
+                    for (int w = 0; w < nq; ++w) {
+                        const uint32_t next = w + 1 < nq ? S3[o + w + 1] : 0u;
+                        const uint32_t m = (uint32_t)L_acc[w];
+                        if (m) {
+                            const uint32_t up = (((m & 15u) * 0x00204081u) & 0x01010101u) * 255u;
+                            const uint32_t dn = ((((m >> 4) & 15u) * 0x00204081u) & 0x01010101u) * 255u;
+                            S3[o + w] = (cur & ~(up | dn)) | (((cur >> 8) | (next << 24)) & up) |
+                                        (((cur << 8) | (prev >> 24)) & dn);
                         }
+                        prev = cur;
+                        cur = next;
+                    }
                 }
             }
             if (edge) {
@@ -759,9 +852,9 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
                 const int nwd = xmsg - 4;
                 for (int sc = 0; sc < 2 * chains; ++sc) {
                     if (!L_cin[sc]) continue;
-                    const int side = sc / chains, ch = sc - side * chains;
+                    const int side = sc >= chains ? 1 : 0, ch = sc - side * chains;
                     const uint32_t *src = msg(side == 0 ? g - 1 : g + 1, side == 0 ? 1 : 0, ch) + 4;
-                    unsigned char *rb = sbyte(ch * mg + (side ? mg - 1 : 0), 0);
+                    unsigned char *rb = sbase(ch, side ? mg - 1 : 0);
                     for (int w0 = tid; w0 < nwd; w0 += kCopyBatch * T) {
                         uint32_t v[kCopyBatch];
 #pragma unroll
@@ -789,6 +882,7 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
             if (stop) break;
         }
 
+        phase();
         // 3. Houdayer cluster moves between chains 0 and 1 at the group's slots, up to
         // kIcmBatch slot pairs at a time with the whole workgroup: each cluster is the
         // connected component of its seed in the graph of J != 0 edges between sites
@@ -1171,23 +1265,36 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
         // 4. Top-10 lists of the group's colder slots: a wavefront per list decides the
         // offer (candidate test, duplicate check, victim entry) and updates the list;
         // the inserted state is stored by that wavefront, or for long states (where one
-        // wavefront's copy outlasts a barrier) by the whole workgroup afterwards.
+        // wavefront's copy outlasts a barrier) by the whole workgroup afterwards.  While a
+        // run still descends every second offer is an insertion (0.56 per list and sweep in
+        // the first 300 sweeps of the L = 10 cube, 0.29 over 1000).
+        phase();
         const int kc = max(K - half, s0), ncold = max(0, s0 + mg - kc);
         const bool wide_copy = n >= 2048;
+        // a replica's bytes at positions 4 w .. 4 w + 3 (from its byte at position 0 on)
+        auto four = [=](const lds_u8 *rb, int w) __attribute__((always_inline)) -> uint32_t {
+            const uint32_t o = 4u * (uint32_t)w * pst;
+            return (uint32_t)rb[o] | ((uint32_t)rb[o + pst] << 8) | ((uint32_t)rb[o + 2 * pst] << 16) |
+                   ((uint32_t)rb[o + 3 * pst] << 24);
+        };
         // replica l's state into dst by threads first, first + step, ...
-        auto store_state = [&](int l, int8_t *dst, int first, int step) __attribute__((always_inline)) {
+        auto store_state = [&](int ch, int k, int8_t *dst, int first, int step) __attribute__((always_inline)) {
             if (pk && (n & 3) == 0) {
                 // chain l's byte of four consecutive sites' words per thread, one word store
-                const int sh = 8 * l;
+                const int sh = 8 * ch;
                 for (int w = first; w < (n >> 2); w += step) {
                     const uint4 v = *reinterpret_cast<const uint4 *>(L_S + 4 * w);
                     *reinterpret_cast<uint32_t *>(dst + 4 * w) =
                         ((v.x >> sh) & 0xFFu) | (((v.y >> sh) & 0xFFu) << 8) | (((v.z >> sh) & 0xFFu) << 16) |
                         (((v.w >> sh) & 0xFFu) << 24);
                 }
+            } else if ((n & 3) == 0) {
+                const lds_u8 *rb = (const lds_u8 *)sbase(ch, k - s0);
+#pragma unroll 4
+                for (int w = first; w < (n >> 2); w += step) *reinterpret_cast<uint32_t *>(dst + 4 * w) = four(rb, w);
             } else {
                 // 32-bit LDS offsets stepped by addition (no 64-bit address arithmetic)
-                const lds_u8 *rb = (const lds_u8 *)sbyte(l, 0);
+                const lds_u8 *rb = (const lds_u8 *)sbase(ch, k - s0);
                 const uint32_t ostep = (uint32_t)step * pst;
                 uint32_t o = (uint32_t)first * pst;
                 for (uint32_t p = (uint32_t)first; p < (uint32_t)n; p += (uint32_t)step, o += ostep)
@@ -1195,7 +1302,9 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
             }
         };
         for (int li = wid; li < chains * ncold; li += nw) {
-            const int ch = li / ncold, k = kc + (li - ch * ncold);
+            int k = li;
+            const int ch = chain_of(k, ncold);
+            k += kc;
             const int l = ch * mg + (k - s0);
             const int gl = ch * half + (k - (K - half));
             const long long Ec = L_E[l];
@@ -1210,42 +1319,51 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
             int32_t *LW = L_Lwhen + (size_t)l * 10;
             int8_t *base = a.tops + ((size_t)run * Ls + gl) * 10 * n;
             int victim = -1;
-            // lane e holds entry e: one butterfly over 16 lanes gives the entry ordered
-            // last by (energy, insertion stamp), the worst one and a full list's victim
-            // (stamps are distinct, so the order is strict)
+            // lane e holds entry e; a full list's victim is the entry ordered last by
+            // (energy, insertion stamp) (stamps are distinct, so the order is strict), known
+            // from the insertion before (L_Lmax, and its place in the rank storage)
             const bool held = lane < cnt;
-            const long long le = held ? LE[lane] : (long long)0x8000000000000000ll;
-            const int32_t lw = held ? LW[lane] : (int32_t)0x80000000;
-            long long bk = le;
-            int32_t bw = lw, bi = lane;
-#pragma unroll
-            for (int off = 8; off >= 1; off >>= 1) {
-                const long long ok = __shfl_xor(bk, off, 64);
-                const int32_t ow = __shfl_xor(bw, off, 64), oi = __shfl_xor(bi, off, 64);
-                if (ok > bk || (ok == bk && ow > bw)) {
-                    bk = ok;
-                    bw = ow;
-                    bi = oi;
-                }
-            }
-            const long long worst = __shfl(bk, 0, 64);
-            const bool cand = cnt < 10 || Ec < worst;
+            long long le = held ? LE[lane] : (long long)0x8000000000000000ll;
+            int32_t lw = held ? LW[lane] : (int32_t)0x80000000;
+            long long worst = L_Lmax[l];
+            int32_t worst_at = L_Lord[(size_t)l * 10];
+            auto rank_last = [&]() __attribute__((always_inline)) {
+                worst = le;
+                int32_t w = lw;
+                worst_at = lane;
+                last_of_16(worst, w, worst_at);
+            };
+            const bool known = worst != 0x7FFFFFFFFFFFFFFFll;
+            if (cnt == 10 && !known) rank_last();
+            const bool cand = cnt < 10 || Ec < (long long)read_first((unsigned long long)worst);
             if (cand) {
-                const lds_u8 *rb = (const lds_u8 *)sbyte(l, 0);
+                const lds_u8 *rb = (const lds_u8 *)sbase(ch, k - s0);
                 bool dup = false;
                 // entries of equal energy get a full comparison of their states
                 for (unsigned long long eq = __ballot(held && le == Ec); eq && !dup; eq &= eq - 1) {
                     const int8_t *ent = base + (size_t)(__ffsll((long long)eq) - 1) * n;
                     bool diff = false;
-                    uint32_t o = (uint32_t)lane * pst;
-                    for (uint32_t p = (uint32_t)lane; p < (uint32_t)n; p += 64u, o += 64u * pst)
-                        diff |= ent[p] != (int8_t)rb[o];
+                    if ((n & 3) == 0) {
+#pragma unroll 4
+                        for (int w = lane; w < (n >> 2); w += 64)
+                            diff |= *reinterpret_cast<const uint32_t *>(ent + 4 * w) != four(rb, w);
+                    } else {
+                        uint32_t o = (uint32_t)lane * pst;
+                        for (uint32_t p = (uint32_t)lane; p < (uint32_t)n; p += 64u, o += 64u * pst)
+                            diff |= ent[p] != (int8_t)rb[o];
+                    }
                     dup = !__any(diff);
                 }
                 if (!dup) {
-                    victim = __builtin_amdgcn_readfirstlane(cnt < 10 ? cnt : __shfl(bi, 0, 64));
-                    if (!wide_copy) store_state(l, base + (size_t)victim * n, lane, 64);
+                    victim = cnt < 10 ? cnt : __builtin_amdgcn_readfirstlane(worst_at);
+                    if (!wide_copy) store_state(ch, k, base + (size_t)victim * n, lane, 64);
                 }
+            }
+            const int now = victim >= 0 && cnt < 10 ? cnt + 1 : cnt;
+            if (victim >= 0 && now == 10) {
+                le = lane == victim ? Ec : le;
+                lw = lane == victim ? ls : lw;
+                rank_last();
             }
             __builtin_amdgcn_wave_barrier();
             if (lane == 0) {
@@ -1253,10 +1371,10 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
                 if (victim >= 0) {
                     LE[victim] = Ec;
                     LW[victim] = ls;
-                    if (cnt < 10) L_Lcnt[l] = cnt + 1;
+                    L_Lcnt[l] = now;
                 }
-                // the largest energy stays known while the entries do not change
-                L_Lmax[l] = victim < 0 && cnt == 10 ? worst : 0x7FFFFFFFFFFFFFFFll;
+                L_Lmax[l] = now < 10 ? 0x7FFFFFFFFFFFFFFFll : worst;
+                L_Lord[(size_t)l * 10] = worst_at;
             }
             __builtin_amdgcn_wave_barrier();
         }
@@ -1265,10 +1383,11 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
             for (int li = 0; li < chains * ncold; ++li) {
                 const int victim = L_Lins[li];
                 if (victim < 0) continue;
-                const int ch = li / ncold, k = kc + (li - ch * ncold);
-                const int l = ch * mg + (k - s0);
+                int k = li;
+                const int ch = chain_of(k, ncold);
+                k += kc;
                 const int gl = ch * half + (k - (K - half));
-                store_state(l, a.tops + (((size_t)run * Ls + gl) * 10 + victim) * n, tid, T);
+                store_state(ch, k, a.tops + (((size_t)run * Ls + gl) * 10 + victim) * n, tid, T);
             }
         }
         __syncthreads();
