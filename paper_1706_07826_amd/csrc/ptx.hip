@@ -170,6 +170,8 @@ __global__ void xw_zero_kernel(uint32_t *w, size_t count) {
 // a byte in LDS, addressed with 32-bit offsets
 typedef __attribute__((address_space(3))) const unsigned char lds_u8;
 typedef __attribute__((address_space(3))) uint32_t lds_mu32;
+typedef __attribute__((address_space(1))) uint32_t glb_u32;
+typedef __attribute__((address_space(1))) int32_t glb_i32;
 
 // What a launch's groups do between exchanges, fixed at compile time for the common
 // shapes: one kernel with every body in it held 128 registers and spilled 132 bytes (216
@@ -289,8 +291,12 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
     const bool pk = MV == kMoveAny ? ptx_packed(BIG, a.m, chains) : MV == kMovePacked;
     const int nq = pk ? 1 : chains * qpc, nl = chains * mg;
     const int32_t *img = a.image;
-    const uint32_t *gnbr = reinterpret_cast<const uint32_t *>(img + kImgHeader + 3 * n);
-    const int32_t *gord = img + kImgHeader, *gpos = img + kImgHeader + n, *ghpos = img + kImgHeader + 2 * n;
+    // (global address space spelled out: past the opaque copies below the compiler no longer
+    // knows it, and a flat load counts as an LDS operation too, so that every wait for an LDS
+    // read would wait for the records fetched ahead)
+    const glb_i32 *gpos = (const glb_i32 *)(img + kImgHeader + n), *gord = (const glb_i32 *)(img + kImgHeader),
+                  *ghpos = (const glb_i32 *)(img + kImgHeader + 2 * n);
+    const glb_u32 *gnbr = (const glb_u32 *)(img + kImgHeader + 3 * n);
 #ifdef __OPTIMIZE__
     // Kept as values of their own: otherwise each use rebuilds them from the whole
     // argument block, which comes back from spill lanes sixteen registers at a time.
@@ -1055,10 +1061,10 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
                     cnt -= m;
                     __builtin_amdgcn_wave_barrier();
                 };
-                // Every edge is taken from its smaller end, and the last colour class (the
-                // highest positions; no edge joins two sites of one class) has none: the
-                // scan stops where that class begins.
-                const int scan_end = a.C > 0 ? min(n, cs[a.C - 1]) : 0;
+                // Every edge is taken from its larger end, and the first colour class (the
+                // lowest positions; no edge joins two sites of one class) has none: the
+                // scan starts where that class ends.
+                const int scan_begin = a.C > 0 ? cs[1] : n;
                 auto scan_site = [&](int p, auto rec) __attribute__((always_inline)) {
                     uint32_t dp = 0, ap = 0;
                     if (esum) {
@@ -1073,25 +1079,53 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
                         uint32_t rr[KB];
 #pragma unroll
                         for (int uu = 0; uu < KB; ++uu) rr[uu] = (need && k0 + uu < Dn) ? rec(k0 + uu, p) : 0u;
-                        // the pairs each edge joins, every neighbour's words read before the joins
+                        // the pairs each edge joins, every neighbour's words read before the
+                        // joins (an absent edge reads the site's own)
                         uint32_t fb[KB];
+                        if (esum) {
+                            uint32_t au[KB], du[KB];
 #pragma unroll
-                        for (int uu = 0; uu < KB; ++uu) {
-                            const int u = (int)(rr[uu] >> 16);
-                            const bool edge_ok = k0 + uu < Dn && (rr[uu] & 0xffffu) != 0u && u > p;
-                            if (esum) {
-                                uint32_t au = 0, du = 0;
-                                if (edge_ok) pair_bytes(u, au, du);
-                                fb[uu] = dp & du;
-                                if (edge_ok && ((dp ^ du) & 1u)) {
+                            for (int uu = 0; uu < KB; ++uu)
+                                pair_bytes(min((int)(rr[uu] >> 16), n - 1), au[uu], du[uu]);
+#pragma unroll
+                            for (int uu = 0; uu < KB; ++uu) {
+                                const int u = (int)(rr[uu] >> 16);
+                                const bool edge_ok = k0 + uu < Dn && (rr[uu] & 0xffffu) != 0u && u < p;
+                                fb[uu] = edge_ok ? dp & du[uu] : 0u;
+                                if (edge_ok && ((dp ^ du[uu]) & 1u)) {
                                     // an edge with one disagreeing end: its term goes to that end
                                     const int32_t Jv = (int32_t)(int16_t)(rr[uu] & 0xffffu);
-                                    const int32_t prod = Jv * (int32_t)(int8_t)(ap & 0xFFu) * (int32_t)(int8_t)(au & 0xFFu);
+                                    const int32_t prod =
+                                        Jv * (int32_t)(int8_t)(ap & 0xFFu) * (int32_t)(int8_t)(au[uu] & 0xFFu);
                                     atomicAdd(&L_es[(dp & 1u) ? p : u], prod);
                                 }
-                            } else {
+                            }
+                        } else {
+#pragma unroll
+                            for (int uu = 0; uu < KB; ++uu) {
+                                const int u = (int)(rr[uu] >> 16);
+                                const bool edge_ok = k0 + uu < Dn && (rr[uu] & 0xffffu) != 0u && u < p;
                                 fb[uu] = edge_ok ? (dp & dis_bits(u)) : 0u;
                             }
+                        }
+                        // a site that is still its own root is hooked under its first
+                        // disagreeing neighbour at once (a smaller one; whatever tree that is
+                        // in): one join in three of a site of six neighbours goes, and the
+                        // others find shallow trees
+#pragma unroll
+                        for (int j = 0; j < kBatch; ++j) {
+                            if (j >= nb) break;
+                            uint32_t first = KB, to = 0;
+#pragma unroll
+                            for (int uu = KB - 1; uu >= 0; --uu)
+                                if ((fb[uu] >> j) & 1u) {
+                                    first = uu;
+                                    to = rr[uu] >> 16;
+                                }
+                            if (first < KB && ptc::cas16(L_parent + (size_t)j * n16 + p, (uint32_t)p, to))
+#pragma unroll
+                                for (int uu = 0; uu < KB; ++uu)
+                                    if (first == (uint32_t)uu) fb[uu] &= ~(1u << j);
                         }
 #pragma unroll
                         for (int uu = 0; uu < KB; ++uu) {
@@ -1121,17 +1155,17 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
 #pragma unroll
                         for (int u = 0; u < DK; ++u) rn[u] = pp < n ? gnbr[(size_t)pp * DK + u] : 0u;
                     };
-                    int p0 = wid * 64;
-                    if (p0 < scan_end) fetch(p0 + lane);
-                    for (; p0 < scan_end; p0 += nw * 64) {
+                    int p0 = scan_begin + wid * 64;
+                    if (p0 < n) fetch(p0 + lane);
+                    for (; p0 < n; p0 += nw * 64) {
                         uint32_t rr[DK];
 #pragma unroll
                         for (int u = 0; u < DK; ++u) rr[u] = rn[u];
-                        if (p0 + nw * 64 < scan_end) fetch(p0 + nw * 64 + lane);
+                        if (p0 + nw * 64 < n) fetch(p0 + nw * 64 + lane);
                         scan_site(p0 + lane, [&](int k, int) __attribute__((always_inline)) { return rr[k]; });
                     }
                 } else {
-                    for (int p0 = wid * 64; p0 < scan_end; p0 += nw * 64) scan_site(p0 + lane, NBR);
+                    for (int p0 = scan_begin + wid * 64; p0 < n; p0 += nw * 64) scan_site(p0 + lane, NBR);
                 }
                 if (cnt > 0) run_joins(cnt);
             }
