@@ -459,8 +459,8 @@ __global__ __launch_bounds__(1024) void energy_rows_kernel(const int32_t *__rest
     }
 }
 
-// The same for problems whose rows do not fit the LDS: a row per workgroup, every
-// neighbour gathered from global memory.
+// The same for few rows of few sites, and for problems whose rows do not fit the LDS: a
+// row per workgroup, every neighbour gathered from global memory.
 __global__ __launch_bounds__(256) void energy_kernel(const int32_t *__restrict__ image, int n,
                                                      int D, const int8_t *__restrict__ spins,
                                                      int R, long long *__restrict__ E) {
@@ -816,7 +816,10 @@ hipError_t launch_energy(const int32_t *image, int n, int D, const int8_t *spins
     if (R <= 0) return hipSuccess;
     long long *e = reinterpret_cast<long long *>(E);
     const size_t lds = (size_t)n * 2 * kEnergyRows;
-    if (lds > kEnergyLds)
+    // Few rows of few sites: a row per workgroup has every gather in flight at once (n = 125,
+    // 137 rows: 36.8 against 37.1 us a call; n = 288, 1000 rows: 42.0 and 42.6; n = 512, 4000
+    // rows: 51.5 and 43.8).
+    if (lds > kEnergyLds || (n <= 512 && R <= 1024))
         hipLaunchKernelGGL(energy_kernel, dim3(R), dim3(256), 0, s, image, n, D, spins, R, e);
     else
         hipLaunchKernelGGL(energy_rows_kernel, dim3((unsigned)((R + kEnergyRows - 1) / kEnergyRows)),

@@ -9,7 +9,8 @@ import spvar_inputs as si
 
 pytestmark = pytest.mark.gpu
 
-CASES = ([(n, R, 6) for n, R in [(1, 1), (2, 3), (63, 4), (257, 5), (1024, 4095), (1025, 4096), (1000, 4099)]] +
+CASES = ([(n, R, 6) for n, R in [(1, 1), (2, 3), (63, 4), (257, 5), (1024, 4095), (1025, 4096), (1000, 4099),
+                                    (512, 1024), (512, 1025), (513, 1024)]] +
          [(4096, 9, 5), (4097, 9, 5), (8192, 4097, 3), (8193, 4097, 3), (16384, 6, 3), (16385, 6, 3),
           (130, 8193, 1), (300, 4100, 64), (200, 7, 63)])
 
