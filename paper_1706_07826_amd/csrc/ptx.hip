@@ -40,6 +40,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "device.hpp"
 #include "internal.hpp"
@@ -294,9 +295,11 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
     // (global address space spelled out: past the opaque copies below the compiler no longer
     // knows it, and a flat load counts as an LDS operation too, so that every wait for an LDS
     // read would wait for the records fetched ahead)
-    const glb_i32 *gpos = (const glb_i32 *)(img + kImgHeader + n), *gord = (const glb_i32 *)(img + kImgHeader),
-                  *ghpos = (const glb_i32 *)(img + kImgHeader + 2 * n);
-    const glb_u32 *gnbr = (const glb_u32 *)(img + kImgHeader + 3 * n);
+    using ImgI = std::conditional_t<BIG, const glb_i32, const int32_t>;
+    using ImgU = std::conditional_t<BIG, const glb_u32, const uint32_t>;
+    ImgI *gpos = (ImgI *)(img + kImgHeader + n), *gord = (ImgI *)(img + kImgHeader),
+         *ghpos = (ImgI *)(img + kImgHeader + 2 * n);
+    ImgU *gnbr = (ImgU *)(img + kImgHeader + 3 * n);
 #ifdef __OPTIMIZE__
     // Kept as values of their own: otherwise each use rebuilds them from the whole
     // argument block, which comes back from spill lanes sixteen registers at a time.
