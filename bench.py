@@ -43,14 +43,27 @@ SA_PROFILE_SOURCES = ["paper_1706_07826_amd/csrc/sa.hip", "paper_1706_07826_amd/
                       "paper_1706_07826_amd/csrc/sa_core.hpp", "paper_1706_07826_amd/csrc/device.hpp"]
 
 
-def sa_lds_bytes_per_update(D, words_per_lane):
+def sa_lds_bytes_per_update(D, words_per_lane, held=False):
     """LDS bytes a byte-parallel SA update moves (read + flip write), from its access
     pattern: per lane and site visit, the D neighbour records (8 B each), the neighbour
     spin words, the lane's own words, the site constants (8 B), one threshold word per
-    replica (4 B) and the flipped words with their complements; W quad words per lane."""
+    replica (4 B) and the flipped words with their complements; W quad words per lane.
+    held: records and site constants lie in registers (one quad word per lane)."""
     W = words_per_lane
+    if held:
+        return (4 * D + 4 + 16 + 8) / 4.0
     per_visit = 8 * D + 4 * W * D + 4 * W + 8 + 16 * W + 8 * W
     return per_visit / (4.0 * W)
+
+
+def held_body(insts, max_degree):
+    """Whether SA takes the body that holds a lane's sites in registers (2 to 4 colour classes, the
+    same number in every instance, none above 1024 variables, 3 to 8 records per site)."""
+    import numpy as np
+    classes = {i.n_colours for i in insts}
+    largest = max(int(np.bincount(i.colour).max()) for i in insts)
+    return (len(classes) == 1 and 2 <= min(classes) <= 4 and largest <= 1024 and 3 <= max_degree <= 8
+            and os.environ.get("SPVAR_SA_HELD", "") != "0")
 
 
 def pt_lds_bytes_per_update(D, digits, records_in_lds):
@@ -263,6 +276,8 @@ def part_chimera8_sa(args, line=True):
     dk = max_degree if max_degree in (4, 6, 8) else 0
     if not byte_parallel:
         kernel = "sa_kernel<1>"
+    elif held_body([inst], max_degree) and not shape["global_instance"]:
+        kernel = f"sa_held{'_stream' if shape['chunks'] > 1 else ''}_kernel<{2 * ((max_degree + 1) // 2)}, {inst.n_colours}>"
     elif shape["chunks"] > 1:
         big = "true" if shape["global_instance"] else "false"
         kernel = f"sa_stream_kernel<{dk}, {shape['words_per_lane']}, {big}>"
@@ -278,7 +293,8 @@ def part_chimera8_sa(args, line=True):
     if byte_parallel:
         probe = measured_lds_peak(spv, ctx)
         roofline["lds"] = lds_object(updates / (sa_ms / 1e3),
-                                     sa_lds_bytes_per_update(max_degree, shape["words_per_lane"]), probe,
+                                     sa_lds_bytes_per_update(max_degree, shape["words_per_lane"],
+                                                             kernel.startswith("sa_held")), probe,
                                      "competing bound: LDS traffic of the sweep against the measured LDS peak")
 
     cpu = None
@@ -383,6 +399,8 @@ def part_residual_batch(args):
     dk = max(md for md, _ in bounds)
     if not byte_parallel:
         kernel = "batch_sa_kernel<1>"
+    elif shape["quads_per_item"] == 0 and held_body(insts, dk):
+        kernel = f"batch_sa_held_kernel<{2 * ((dk + 1) // 2)}, {insts[0].n_colours}>"
     elif dk in (4, 6, 8):
         # quads_per_item 0: the paired body (a lane holds both words of a pair of quads)
         kernel = f"batch_sa_paired_kernel<{dk}>" if shape["quads_per_item"] == 0 else f"batch_sa_kernel<0, {dk}>"

@@ -2,9 +2,9 @@
 // agreement, fixing, "Update J and h"), with the zero-bias gauge of Sec. II.C.
 //
 // Pipeline (all stream-ordered, no host round trip):
-//   1. elite_kernel   one workgroup: radix-selects the m-th smallest (E, row)
+//   1. elite          one workgroup: radix-selects the m-th smallest (E, row)
 //                     key and emits the elite rows in row order.
-//   2. bitmap_kernel  a wavefront takes 64 elite rows; for each variable a
+//   2. bitmap         a wavefront takes 64 elite rows; for each variable a
 //                     ballot of "s = +1" over the 64 lanes is one 64-bit word
 //                     of that variable's column bitmap P_i (W = ceil(m/64)
 //                     words per variable).  Counts are popcounts of P_i.
