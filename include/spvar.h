@@ -117,7 +117,10 @@ const char *spv_version(void);
  * SQA kernels (Sec. III.A, III.D.1; one colour class at a time) check, on every pass, that no spin
  * word is written by two tasks and that no task reads a neighbour word another
  * task of the pass writes, against a per-workgroup bitmap in LDS (8 KiB of LDS
- * per workgroup, taken from the planners' limit).  Conflicts are counted, never
+ * per workgroup, taken from the planners' limit).  The replica exchange of a
+ * split tempering ladder checks its boundary configuration's bytes against the
+ * words its in-group swaps store (a conflict counts as read-write, the exchange
+ * as a pass).  Conflicts are counted, never
  * trapped.  Waits for the device, then writes counts[0..3]: write-write
  * conflicts, read-write conflicts, class passes checked, launches whose spin
  * area exceeded the bitmap (unchecked); reset != 0 clears them.  SPV_EINVAL in

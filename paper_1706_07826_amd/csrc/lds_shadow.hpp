@@ -10,6 +10,8 @@
 //   2. barrier; every task tests the bits of the neighbour words it will read (a set
 //      bit is a read-write conflict: that neighbour changes during the pass),
 //   3. the pass itself, barrier, every task clears its bits, barrier.
+// A split tempering group's exchange is checked likewise: the words its in-group swaps
+// store whole against the words into which the boundary copy stores bytes.
 // Conflicts are counted, never trapped: the kernels run to completion and the host
 // reads the counts (write-write, read-write, passes checked, launches whose spin
 // area exceeds the bitmap).  In the normal build every hook compiles to nothing.

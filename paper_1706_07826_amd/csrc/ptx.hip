@@ -160,8 +160,6 @@ __host__ __device__ inline size_t ptx_layout(int n, int D, int K, int m, int cha
 
 // Slot pairs whose cluster moves run together (one forest and mask set each).
 constexpr int kIcmBatch = 4;
-// Boundary-message words a thread loads at once when copying a configuration in.
-constexpr int kCopyBatch = 4;
 
 __global__ void xw_zero_kernel(uint32_t *w, size_t count) {
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < count; i += (size_t)gridDim.x * blockDim.x)
@@ -232,6 +230,11 @@ __device__ __forceinline__ unsigned long long read_first(unsigned long long v) {
 template <int ND, bool BIG, int DK, int MV>
 __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
     constexpr int kBatch = MV == kMoveAny ? kIcmBatch : 1;  // slot pairs of a pass
+    // Sites whose message words a thread loads together in the boundary copy, so that their
+    // latencies overlap: an instance in LDS gives a thread one or two, one in global memory
+    // about eight (L = 10 cube, 32 slots: 10.1 ms per 1000 sweeps, with four 10.2; L = 20, 40
+    // slots x 2 chains, 300 sweeps: 14.9 ms, with two 15.0).
+    constexpr int kCopyBatch = BIG ? 8 : 2;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int cs[kMaxColours + 1];
     __shared__ int nacc;
@@ -485,6 +488,16 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
             for (int p = cs[c] + pt; active && p < pe; p += nstr) shadow::unmark(sh, (uint32_t)(p * nq + q));
             shadow::barrier();
         }
+    };
+
+    // Race-detection build: the words a thread's in-group swaps store, marked for the
+    // exchange; a byte stored by another thread into one is a conflict.
+    auto shadow_swaps = [&](bool before) {
+        for (int p = tid; p < n; p += T)
+            for (int w = 0; w < nq; ++w)
+                if (L_acc[w]) before ? shadow::mark(sh, (uint32_t)(p * nq + w)) : shadow::unmark(sh, (uint32_t)(p * nq + w));
+        if (before) shadow::count_pass(sh);
+        shadow::barrier();
     };
 
     for (int ls = 0; ls < a.sweeps; ++ls) {
@@ -835,6 +848,8 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
         {
             // accepted pairs swap their bytes word by word, a site's words by one thread
             // (a byte moves by one place, within its word or to the next one)
+            if constexpr (shadow::kOn)
+                if (nacc) shadow_swaps(true);
             if (nacc) {
                 lds_mu32 *const S3 = (lds_mu32 *)L_S;
                 for (int p = tid; p < n; p += T) {
@@ -856,38 +871,44 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
             }
             if (edge) {
                 // an accepted straddling pair takes the neighbour's published configuration
-                // (kCopyBatch words per thread loaded together; a word whose tag is not
-                // yet the expected one is waited for)
-                const int nwd = xmsg - 4;
+                // (kCopyBatch sites per thread loaded together; a word whose tag is not
+                // yet the expected one is waited for).  A swap stores words whole and this
+                // bytes of the same words (groups of 4 slots: the pair (1, 2) lies between
+                // the two boundary bytes), so a site is the same thread's in both, and no
+                // barrier lies between; two threads read a message word.  (A barrier between
+                // the two instead: 10.55 ms per 1000 sweeps of the L = 10 cube, 32 slots x 64
+                // runs, against 10.1.)
                 for (int sc = 0; sc < 2 * chains; ++sc) {
                     if (!L_cin[sc]) continue;
                     const int side = sc >= chains ? 1 : 0, ch = sc - side * chains;
                     const uint32_t *src = msg(side == 0 ? g - 1 : g + 1, side == 0 ? 1 : 0, ch) + 4;
                     unsigned char *rb = sbase(ch, side ? mg - 1 : 0);
-                    for (int w0 = tid; w0 < nwd; w0 += kCopyBatch * T) {
+                    for (int p0 = tid; p0 < n; p0 += kCopyBatch * T) {
                         uint32_t v[kCopyBatch];
 #pragma unroll
                         for (int u = 0; u < kCopyBatch; ++u) {
-                            const int w = w0 + u * T;
-                            v[u] = w < nwd ? __hip_atomic_load(src + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+                            const int p = p0 + u * T;
+                            v[u] = p < n ? __hip_atomic_load(src + (p >> 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
                         }
 #pragma unroll
                         for (int u = 0; u < kCopyBatch; ++u) {
-                            const int w = w0 + u * T;
-                            if (w >= nwd) continue;
-                            const int pay = (v[u] & 0xFFFF0000u) == tag ? (int)(v[u] & 0xFFFFu) : recv(src + w);
+                            const int p = p0 + u * T;
+                            if (p >= n) continue;
+                            const int pay = (v[u] & 0xFFFF0000u) == tag ? (int)(v[u] & 0xFFFFu) : recv(src + (p >> 1));
                             if (pay < 0) {
                                 stop = 1;
                                 continue;
                             }
-                            const uint32_t p = 2u * (uint32_t)w;
-                            rb[p * pst] = (unsigned char)(pay & 0xFF);
-                            if ((int)p + 1 < n) rb[(p + 1u) * pst] = (unsigned char)(pay >> 8);
+                            if constexpr (shadow::kOn)  // (its own thread's swap of the site is in order)
+                                if (p % T != tid) shadow::check(sh, (uint32_t)(p * nq) + (uint32_t)(rb - Sb) / 4u);
+                            rb[(uint32_t)p * pst] = (unsigned char)(pay >> (8 * (p & 1)));
                         }
                     }
                 }
             }
             __syncthreads();
+            if constexpr (shadow::kOn)
+                if (nacc) shadow_swaps(false);
             if (stop) break;
         }
 
