@@ -318,6 +318,8 @@ hipError_t launch_batch_sa(const BatchLaunch &L, hipStream_t s) {
     a.sweep_offset = L.sweep_offset;
     a.pairs_qw = L.pairs_qw;
     a.kmax = L.kmax;
+    // the held-sites and paired bodies sum couplings in bytes
+    if ((L.held || L.paired) && !sa_use_swar(L.nd, L.row_len)) return hipErrorInvalidValue;
     if (L.held) {
         const BatchFn f = held_fn(L.dk, L.c_max);
         if (!f) return hipErrorInvalidValue;

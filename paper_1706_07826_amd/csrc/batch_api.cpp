@@ -373,16 +373,19 @@ spv_status sample_batch_inst(spv_ctx *ctx, int32_t B, const Inst *problems, cons
         const bool fills = pl.lanes >= 64ll * 32 * c->num_cus;
         sh = Shape{!fills ? narrow : pl.cls_max > 256 ? 1024 : 512, 1, 1, false, true};
     }
-    const std::vector<long long> tkey = {pl.n_max, pl.D_max, pl.nd, B, pl.total_quads / 64};
-    bool have = false;
+    // A tuned shape serves batches of its size class that the same bodies are open to (what a
+    // body's LDS cannot hold of such a batch falls back below).
+    const Shape dflt = sh;
+    const std::vector<long long> tkey = {pl.n_max, pl.D_max, pl.nd, B, pl.total_quads / 64, swar, paired_ok, held_ok};
+    bool have = false, given = false;
     if (opts && opts->threads > 0 && (flags & SPV_BATCH_PAIRED)) {
         if (!paired_ok)
             return set_err(c, SPV_EINVAL, "the paired body needs byte-parallel images of 4, 6 or 8 records per site");
         sh = Shape{opts->threads, 2, opts->wgs_per_cu > 0 ? opts->wgs_per_cu : 1, true};
-        have = true;
+        have = given = true;
     } else if (opts && opts->threads > 0 && opts->quads_per_item > 0) {
         sh = Shape{opts->threads, opts->quads_per_item, opts->wgs_per_cu > 0 ? opts->wgs_per_cu : 4, false};
-        have = true;
+        have = given = true;
     }
     if (!have)
         for (auto &t : c->tuned)
@@ -457,15 +460,16 @@ spv_status sample_batch_inst(spv_ctx *ctx, int32_t B, const Inst *problems, cons
         return set_err(c, SPV_EINVAL, "batch shape threads=%d quads_per_item=%d wgs_per_cu=%d", sh.threads,
                        sh.qw, sh.wgs_per_cu);
     std::vector<int32_t> items;
-    if (!items_of(sh, &items)) {
-        if ((!sh.paired && !sh.held) || have)
-            return set_err(c, SPV_ECAPACITY, "largest instance (n=%d) needs more LDS than a workgroup has", pl.n_max);
-        // a default shape that does not fit gives way to the next: paired, then one word per lane
-        if (sh.held) sh = Shape{1024, 2, 1, true};
-        if (!sh.paired || !items_of(sh, &items)) sh = Shape{256, 2, 4, false};
-        if (!sh.paired && !items_of(sh, &items))
-            return set_err(c, SPV_ECAPACITY, "largest instance (n=%d) needs more LDS than a workgroup has", pl.n_max);
+    bool fits = items_of(sh, &items);
+    // a tuned or default shape that does not fit gives way: default, paired, one word per lane
+    for (const Shape &next : {dflt, Shape{1024, 2, 1, true}, Shape{256, 2, 4}}) {
+        if (fits || given) break;
+        if (next.paired && !paired_ok) continue;
+        sh = next;
+        fits = items_of(sh, &items);
     }
+    if (!fits)
+        return set_err(c, SPV_ECAPACITY, "largest instance (n=%d) needs more LDS than a workgroup has", pl.n_max);
     c->last_shape[0] = sh.threads;
     c->last_shape[1] = sh.paired || sh.held ? 0 : sh.qw;
     c->last_shape[2] = sh.wgs_per_cu;
