@@ -321,7 +321,10 @@ spv_status plan_pt_split(Ctx *c, int n, int D, int K, int runs, int chains, int 
         const int nq = ptx_words_per_site(K, m, chains);  // (one word per site when packed: fewer tasks)
         const long long tasks = (long long)n * nq;
         int threads = env_int("SPVAR_PT_THREADS", tasks >= 1536 ? 1024 : tasks >= 768 ? 512 : 256);
-        while (threads < nq) threads *= 2;
+        // a thread per word of a site, and per slot pair of an exchange (the LDS of a pair's two
+        // replicas keeps this below 1024)
+        const int pairs = chains * (m / 2 + (Gr > 1 ? 2 : 0));
+        while (threads < std::max(nq, pairs)) threads *= 2;
         if (threads > 1024) continue;
         const int icm_slots = icm_hi > icm_lo ? std::min(m, icm_hi - icm_lo) : 0;
         for (int big = env_int("SPVAR_PT_BIG", 0) ? 1 : 0; big < 2; ++big) {

@@ -274,14 +274,14 @@ __global__ __launch_bounds__(1024) void pt_kernel(PtArgs a) {
         {
             const int par = (int)(t & 1u);
             const int npairs = (K - par) / 2;
-            if (tid < chains * npairs) {
-                const int ch = tid / npairs, m = tid - ch * npairs, k = par + 2 * m;
+            for (int e = tid; e < chains * npairs; e += T) {
+                const int ch = e / npairs, m = e - ch * npairs, k = par + 2 * m;
                 const long long Dd = L.E[ch * K + k] - L.E[ch * K + k + 1];
                 if (swap_test(Dd, a.stab + (size_t)k * 7 * kDigitSize, a.snd[k], (uint32_t)k, t,
                               (uint32_t)(run * chains + ch), a.k0, a.k1)) {
-                    const long long e = L.E[ch * K + k];
+                    const long long x = L.E[ch * K + k];
                     L.E[ch * K + k] = L.E[ch * K + k + 1];
-                    L.E[ch * K + k + 1] = e;
+                    L.E[ch * K + k + 1] = x;
                     L.acc[atomicAdd(&nacc, 1)] = ch * K + k;
                 }
             }
