@@ -230,11 +230,13 @@ __device__ __forceinline__ unsigned long long read_first(unsigned long long v) {
 template <int ND, bool BIG, int DK, int MV>
 __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
     constexpr int kBatch = MV == kMoveAny ? kIcmBatch : 1;  // slot pairs of a pass
-    // Sites whose message words a thread loads together in the boundary copy, so that their
-    // latencies overlap: an instance in LDS gives a thread one or two, one in global memory
-    // about eight (L = 10 cube, 32 slots: 10.1 ms per 1000 sweeps, with four 10.2; L = 20, 40
-    // slots x 2 chains, 300 sweeps: 14.9 ms, with two 15.0).
-    constexpr int kCopyBatch = BIG ? 8 : 2;
+    // The boundary copy's message words a thread loads together, so that their latencies
+    // overlap: an instance in LDS gives a thread one or two sites, one in global memory about
+    // eight (L = 10 cube, 32 slots: 10.1 ms per 1000 sweeps, with four 10.2).  kCopySites: a
+    // thread takes one site of a message word, or, in a group of one slot, which swaps no
+    // pair of its own, both (L = 20, 40 slots x 2 chains, 300 sweeps: 14.7 ms, one 14.9).
+    constexpr int kCopySites = MV == kMovePacked ? 2 : 1;
+    constexpr int kCopyBatch = (BIG ? 8 : 2) / kCopySites;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int cs[kMaxColours + 1];
     __shared__ int nacc;
@@ -883,25 +885,31 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
                     const int side = sc >= chains ? 1 : 0, ch = sc - side * chains;
                     const uint32_t *src = msg(side == 0 ? g - 1 : g + 1, side == 0 ? 1 : 0, ch) + 4;
                     unsigned char *rb = sbase(ch, side ? mg - 1 : 0);
-                    for (int p0 = tid; p0 < n; p0 += kCopyBatch * T) {
+                    constexpr int NS = kCopySites;
+                    for (int p0 = NS * tid; p0 < n; p0 += kCopyBatch * NS * T) {
                         uint32_t v[kCopyBatch];
 #pragma unroll
                         for (int u = 0; u < kCopyBatch; ++u) {
-                            const int p = p0 + u * T;
+                            const int p = p0 + u * NS * T;
                             v[u] = p < n ? __hip_atomic_load(src + (p >> 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
                         }
 #pragma unroll
                         for (int u = 0; u < kCopyBatch; ++u) {
-                            const int p = p0 + u * T;
+                            const int p = p0 + u * NS * T;
                             if (p >= n) continue;
                             const int pay = (v[u] & 0xFFFF0000u) == tag ? (int)(v[u] & 0xFFFFu) : recv(src + (p >> 1));
                             if (pay < 0) {
                                 stop = 1;
                                 continue;
                             }
-                            if constexpr (shadow::kOn)  // (its own thread's swap of the site is in order)
-                                if (p % T != tid) shadow::check(sh, (uint32_t)(p * nq) + (uint32_t)(rb - Sb) / 4u);
-                            rb[(uint32_t)p * pst] = (unsigned char)(pay >> (8 * (p & 1)));
+#pragma unroll
+                            for (int s = 0; s < NS; ++s) {
+                                if (p + s >= n) continue;
+                                if constexpr (shadow::kOn)  // (its own thread's swap of the site is in order)
+                                    if ((p + s) % T != tid)
+                                        shadow::check(sh, (uint32_t)((p + s) * nq) + (uint32_t)(rb - Sb) / 4u);
+                                rb[(uint32_t)(p + s) * pst] = (unsigned char)(pay >> (8 * ((p + s) & 1)));
+                            }
                         }
                     }
                 }
