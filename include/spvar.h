@@ -338,13 +338,16 @@ spv_status spv_ispvar(spv_ctx *ctx, const spv_problem *P, const double *betas, i
  * random stream follows the temperature).
  * A run's ladder may be split over several workgroups of
  * consecutive slots (a multiple of 4 slots each, or with cluster moves on 2 or
- * 1; when K is no multiple of 4, only a run that one workgroup holds too) that decide the slot pairs straddling their boundaries from energies and
+ * 1; when K is no multiple of 4, only a run that one workgroup holds too) that
+ * decide the slot pairs straddling their boundaries from energies and
  * edge states published through global memory (the split is chosen from the
  * run count and the LDS footprint; results do not depend on it).  The
  * split launch is only made when all its workgroups fit on the device at
- * once; should a workgroup still wait for a neighbour beyond a bounded spin,
- * it stops and writes top_count = -1 for its lists (and spv_top_sample then
- * reports SPV_EINVAL).  SPV_ECAPACITY when no layout fits.
+ * once; should a workgroup still wait for a neighbour beyond a bounded spin
+ * (other work holds the device), it stops.  When K is a multiple of 4 it then
+ * writes top_count = -1 for its lists (and spv_top_sample reports SPV_EINVAL);
+ * otherwise the run is run again by one workgroup, which waits for no other, in
+ * the same call.  SPV_ECAPACITY when no layout fits.
  *
  * Checkpoint and resume: the outputs of a call (final_spins and the three
  * top-10 arrays) are its checkpoint.  A call given them as resume_* with the

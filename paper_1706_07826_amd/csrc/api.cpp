@@ -8,6 +8,7 @@
 #include <cstdio>
 #include <cstring>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "internal.hpp"
@@ -1085,8 +1086,27 @@ spv_status pt_inst(spv_ctx *ctx, const Inst *P, const spv_pt_params *prm, const 
     }
     const size_t b_top = al((size_t)runs * std::max(Ls, 1) * 10 * std::max(n, 1));
     const size_t n_grp = sp.use ? (size_t)runs * sp.G : 0;
-    const size_t b_xw = al(n_grp * 4 * chains * (size_t)ptx_msg_words(std::max(n, 1)) * 4);
-    st = ensure(c, c->pt, b_top + b_xw);
+    const size_t n_xw = n_grp * 4 * chains * (size_t)ptx_msg_words(std::max(n, 1));
+    // A ladder that is no multiple of four also fits one workgroup, and there it waits for no
+    // other.  Its runs whose groups abandon a wait (other work on the device keeps some of them
+    // from running) are run again that way behind the split launch, from a copy of the checkpoint
+    // where the outputs lie over it.
+    const bool redo = sp.use && sp.G > 1 && K % 4 != 0;
+    const size_t b_xw = al((n_xw + (redo ? runs : 0)) * 4);
+    PtResume again = rs;
+    size_t b_copy = 0;
+    auto copied = [&](const void *in, const void *o, size_t bytes) {
+        if (!redo || !in || in != o) return (size_t)0;
+        const size_t at = b_top + b_xw + b_copy;
+        b_copy += al(bytes);
+        return at;
+    };
+    const size_t lists = (size_t)runs * Ls, b_spins = (size_t)runs * cK * n;
+    const size_t c_spins = copied(rs.spins, out->final_spins, b_spins),
+                 c_tops = copied(rs.top_spins, out->top_spins, lists * 10 * n),
+                 c_topE = copied(rs.top_E, out->top_E, lists * 80),
+                 c_count = copied(rs.top_count, out->top_count, lists * 4);
+    st = ensure(c, c->pt, b_top + b_xw + b_copy);
     if (st) return st;
     st = ensure(c, c->image, image_words(std::max(n, 1), D) * 4);
     if (st) return st;
@@ -1128,7 +1148,22 @@ spv_status pt_inst(spv_ctx *ctx, const Inst *P, const spv_pt_params *prm, const 
         X.big = sp.big;
         X.spin_limit = pt_spin_limit();
         X.resume = rs;
-        return hip_check(c, launch_ptx(X, stream), "split pt launch");
+        if (redo) {
+            X.redo = reinterpret_cast<int32_t *>(X.xw + n_xw);
+            auto copy = [&](auto &p, size_t at, size_t bytes) {
+                if (at == 0 || e != hipSuccess) return;
+                e = hipMemcpyAsync(sc + at, p, bytes, hipMemcpyDeviceToDevice, stream);
+                p = reinterpret_cast<std::decay_t<decltype(p)>>(sc + at);
+            };
+            copy(again.spins, c_spins, b_spins);
+            copy(again.top_spins, c_tops, lists * 10 * n);
+            copy(again.top_E, c_topE, lists * 80);
+            copy(again.top_count, c_count, lists * 4);
+            if (e != hipSuccess) return hip_check(c, e, "checkpoint copy");
+        }
+        e = launch_ptx(X, stream);
+        if (e != hipSuccess || !redo) return hip_check(c, e, "split pt launch");
+        rs = again;
     }
     PtLaunch L;
     L.image = static_cast<const int32_t *>(c->image.p);
@@ -1154,6 +1189,7 @@ spv_status pt_inst(spv_ctx *ctx, const Inst *P, const spv_pt_params *prm, const 
     L.nqa = nqa;
     L.threads = threads;
     L.resume = rs;
+    if (redo) L.redo = reinterpret_cast<const int32_t *>(sbase + b_top) + n_xw;
     return hip_check(c, launch_pt(L, stream), "pt launch");
 }
 

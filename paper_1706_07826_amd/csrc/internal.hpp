@@ -376,6 +376,7 @@ struct PtLaunch {
     int nqa;               // quads per run window
     int threads;
     PtResume resume;
+    const int32_t *redo = nullptr;  // [runs]: only runs marked here (null: all)
 };
 size_t pt_lds_bytes(int n, int D, int K, int chains, int row_len, int nqa, int nw_icm);
 hipError_t launch_pt(const PtLaunch &L, hipStream_t s);
@@ -401,6 +402,7 @@ struct PtxLaunch {
     bool esum;                // one slot pair per group: cluster energy terms gathered in the joins
     unsigned spin_limit;
     PtResume resume;
+    int32_t *redo = nullptr;  // [runs], behind xw: runs with an abandoned wait are marked here, not in their lists
 };
 struct PtSplit {
     bool use = false, big = false, esum = false;

@@ -68,6 +68,7 @@ struct PtxArgs {
     int8_t *tops;          // [runs][Ls][10][n], position order
     uint32_t *xw;          // [runs][G][side 2][buf 2][chains][xmsg] tagged boundary messages
     PtResume rs;           // checkpoint to start from
+    int32_t *redo;         // [runs] or null: marks of runs with an abandoned wait
     int n, D, C, K, chains, sweeps, row_len, icm_lo, icm_hi, nw_icm, G, m, xmsg, esum;
     uint32_t sweep_offset, k0, k1;
     unsigned spin_limit;
@@ -1460,6 +1461,10 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
     }
 
     const int kc = max(K - half, s0), ncold = max(0, s0 + mg - kc);
+    if (stop && a.redo) {
+        if (tid == 0) a.redo[run] = 1;
+        return;
+    }
     if (stop) {
         // A neighbour never published: mark the group's lists as invalid.
         if (a.top_count)
@@ -1589,6 +1594,7 @@ hipError_t launch_ptx(const PtxLaunch &P, hipStream_t s) {
     a.tops = P.tops;
     a.rs = P.resume;
     a.xw = P.xw;
+    a.redo = P.redo;
     a.xmsg = ptx_msg_words(P.n);
     a.n = P.n;
     a.D = P.D;
@@ -1608,7 +1614,7 @@ hipError_t launch_ptx(const PtxLaunch &P, hipStream_t s) {
     a.k1 = (uint32_t)(P.seed >> 32);
     a.spin_limit = P.spin_limit;
     if (P.G > 1) {
-        const size_t words = (size_t)P.runs * P.G * 4 * P.chains * ptx_msg_words(P.n);
+        const size_t words = (size_t)P.runs * P.G * 4 * P.chains * ptx_msg_words(P.n) + (P.redo ? P.runs : 0);
         hipLaunchKernelGGL(xw_zero_kernel, dim3((unsigned)std::min<size_t>((words + 255) / 256, 4096)), dim3(256), 0,
                            s, P.xw, words);
         const hipError_t e = hipGetLastError();
