@@ -345,6 +345,7 @@ spv_status plan_pt_split(Ctx *c, int n, int D, int K, int runs, int chains, int 
                                    Gr, bpc * c->num_cus);
                 }
                 sp->use = true;
+                sp->optional = single_fits && !forced && (!k4 || Gr == 1);
                 sp->G = Gr;
                 sp->m = m;
                 sp->threads = threads;
@@ -358,7 +359,7 @@ spv_status plan_pt_split(Ctx *c, int n, int D, int K, int runs, int chains, int 
 }
 
 spv_status pt_lds_footprint(Ctx *c, const Inst *P, int K, int runs, int chains, int icm_lo, int icm_hi,
-                            int64_t *lds_total) {
+                            bool one_workgroup, int64_t *lds_total, int64_t *groups) {
     const int n = P->n, D = P->max_degree > 0 ? P->max_degree : 1;
     const int nd = digits_for(P->x_bound), row_len = table_row_len(P->x_bound);
     const bool icm = icm_hi > icm_lo;
@@ -370,11 +371,13 @@ spv_status pt_lds_footprint(Ctx *c, const Inst *P, int K, int runs, int chains, 
     spv_status st = plan_pt_split(c, n, D, K, runs, chains, row_len, nd, icm ? icm_lo : 0, icm ? icm_hi : 0,
                                   lds <= c->lds_max, &sp);
     if (st) return st;
+    if (one_workgroup && sp.optional) sp.use = false;
+    *groups = (int64_t)runs * (sp.use ? sp.G : 1);
     if (sp.use)
-        *lds_total = (int64_t)runs * sp.G *
+        *lds_total = *groups *
                      (int64_t)(ptx_lds_bytes({n, D, K, sp.m, chains, row_len, nd, sp.nw_icm, sp.big, sp.esum}) + 256);
     else
-        *lds_total = (int64_t)runs * (int64_t)lds;
+        *lds_total = *groups * (int64_t)lds;
     return SPV_OK;
 }
 
@@ -1010,7 +1013,7 @@ spv_status spv_ispvar(spv_ctx *ctx, const spv_problem *P0, const double *betas, 
 namespace spv {
 
 spv_status pt_inst(spv_ctx *ctx, const Inst *P, const spv_pt_params *prm, const spv_pt_out *out,
-                   hipStream_t stream) {
+                   hipStream_t stream, bool one_workgroup) {
     if (!ctx) return SPV_EINVAL;
     Ctx *c = &ctx->c;
     DeviceGuard g(c->device);
@@ -1047,6 +1050,7 @@ spv_status pt_inst(spv_ctx *ctx, const Inst *P, const spv_pt_params *prm, const 
     if ((st = plan_pt_split(c, n, D, K, runs, chains, row_len, nd, icm ? prm->icm_lo : 0, icm ? prm->icm_hi : 0,
                             lds <= c->lds_max, &sp)))
         return st;
+    if (one_workgroup && sp.optional) sp.use = false;
     if (!sp.use && lds > c->lds_max)
         return set_err(c, SPV_ECAPACITY, "PT run needs %zu B of LDS > %zu (n=%d, %d replicas)", lds, c->lds_max, n, cK);
     // Device tables: Metropolis rows per slot, swap rows per pair, swap digit counts
@@ -1085,7 +1089,7 @@ spv_status pt_inst(spv_ctx *ctx, const Inst *P, const spv_pt_params *prm, const 
         ptc.row_len = row_len;
     }
     const size_t b_top = al((size_t)runs * std::max(Ls, 1) * 10 * std::max(n, 1));
-    const size_t n_grp = sp.use ? (size_t)runs * sp.G : 0;
+    const size_t n_grp = sp.use && sp.G > 1 ? (size_t)runs * sp.G : 0;
     const size_t n_xw = n_grp * 4 * chains * (size_t)ptx_msg_words(std::max(n, 1));
     // A ladder that is no multiple of four also fits one workgroup, and there it waits for no
     // other.  Its runs whose groups abandon a wait (other work on the device keeps some of them

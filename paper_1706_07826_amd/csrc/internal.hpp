@@ -160,8 +160,9 @@ spv_status sample_inst(spv_ctx *ctx, const Inst *P, const double *betas, int32_t
 spv_status sqa_inst(spv_ctx *ctx, const Inst *P, const double *betas, const double *gammas, int32_t sweeps,
                     int32_t trotter, int32_t reads, uint64_t seed, int8_t *spins, int64_t *energies,
                     hipStream_t stream);
+// one_workgroup: a run whose planned launch is optional (PtSplit) takes one workgroup instead.
 spv_status pt_inst(spv_ctx *ctx, const Inst *P, const spv_pt_params *prm, const spv_pt_out *out,
-                   hipStream_t stream);
+                   hipStream_t stream, bool one_workgroup = false);
 spv_status sample_batch_inst(spv_ctx *ctx, int32_t B, const Inst *problems, const double *betas, int32_t sweeps,
                              const int32_t *reads, const uint64_t *seeds, int8_t *const *spins,
                              int64_t *const *energies, const spv_batch_opts *opts, hipStream_t stream);
@@ -406,14 +407,16 @@ struct PtxLaunch {
 };
 struct PtSplit {
     bool use = false, big = false, esum = false;
+    bool optional = false;  // the one-workgroup kernel serves as well: K off the multiples of four, or one group
     int G = 1, m = 0, threads = 256, nw_icm = 0;
 };
 spv_status plan_pt_split(Ctx *c, int n, int D, int K, int runs, int chains, int row_len, int nd, int icm_lo,
                          int icm_hi, bool single_fits, PtSplit *sp);
 unsigned pt_spin_limit();
-// LDS claimed by one spv_pt_sample launch with the shapes it would pick.
+// LDS claimed by one spv_pt_sample launch with the shapes it would pick (with one_workgroup
+// as pt_inst takes it), and its workgroups.
 spv_status pt_lds_footprint(Ctx *c, const Inst *P, int K, int runs, int chains, int icm_lo, int icm_hi,
-                            int64_t *lds_total);
+                            bool one_workgroup, int64_t *lds_total, int64_t *groups);
 // What a split launch's kernel and LDS layout depend on.
 struct PtxShape {
     int n, D, K, m, chains, row_len, nd, nw_icm;

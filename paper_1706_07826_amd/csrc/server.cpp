@@ -33,6 +33,7 @@ struct Record {
     spv::Inst inst;  // the request's problem as ingested at submission
     std::vector<double> betas, gammas;
     int64_t lds = 0, hbm = 0;
+    bool one_workgroup = false;  // tempering: one workgroup a run where that may be chosen (the budgets hold no more)
     State state = kPending;
     bool fix_pending = false;  // tempering request whose persistence step follows the sampling
     spv_result res{};
@@ -69,7 +70,7 @@ using namespace spv;
 namespace {
 
 // LDS and scratch a request claims while in flight (default launch shapes).
-void footprint(spv_server *s, const spv_request &r, const Inst &P, int64_t *lds, int64_t *hbm) {
+void footprint(spv_server *s, const spv_request &r, const Inst &P, bool one_workgroup, int64_t *lds, int64_t *hbm) {
     const int D = std::max(1, P.max_degree);
     const int nd = digits_for(P.x_bound), row_len = table_row_len(P.x_bound);
     int64_t L = 0, H = (int64_t)image_words(std::max(P.n, 1), D) * 4;
@@ -90,12 +91,19 @@ void footprint(spv_server *s, const spv_request &r, const Inst &P, int64_t *lds,
         H += (int64_t)r.sweeps * (rl * 4 + 4);
         R = r.reads;
     } else {
-        if (pt_lds_footprint(&s->parent->c, &P, r.K, r.runs, r.chains, r.icm_lo, r.icm_hi, &L) != SPV_OK)
+        int64_t groups = 0;
+        if (pt_lds_footprint(&s->parent->c, &P, r.K, r.runs, r.chains, r.icm_lo, r.icm_hi, one_workgroup, &L,
+                             &groups) != SPV_OK)
             L = 0;  // the launch itself reports the error
         R = (int64_t)r.runs * r.chains * (r.K / 2) * kTopK;
         H += (int64_t)r.K * row_len * 4 + (int64_t)r.K * 7 * kDigitSize * 4 + R * std::max(P.n, 1);
-        // boundary messages: at most K / 4 groups per run, or K with cluster moves on
-        const int64_t gmax = r.icm_hi > r.icm_lo ? r.K : r.K / 4;
+        // boundary messages: at most K / 4 groups per run, or K with cluster moves on (a ladder
+        // off the multiples of four: one more, and its runs' marks)
+        int64_t gmax = r.icm_hi > r.icm_lo ? r.K : r.K / 4;
+        if (groups > r.runs && r.K % 4 != 0) {
+            gmax = std::max<int64_t>(gmax, (r.K + 3) / 4);
+            H += (int64_t)r.runs * 4;
+        }
         H += (int64_t)r.runs * gmax * 4 * r.chains * (int64_t)ptx_msg_words(std::max(P.n, 1)) * 4;
         if (r.elite_frac > 0) H += R * (std::max(P.n, 1) + 8);  // assembled sample
     }
@@ -131,7 +139,7 @@ spv_status launch(Slot &sl, Record &rec) {
         prm.sweep_offset = 0;
         prm.icm_lo = r.icm_lo;
         prm.icm_hi = r.icm_hi;
-        st = pt_inst(x, &rec.inst, &prm, &r.pt_out, sl.stream);
+        st = pt_inst(x, &rec.inst, &prm, &r.pt_out, sl.stream, rec.one_workgroup);
         // The sample size (filled top-10 entries) is known once the run ends.
         rec.fix_pending = st == SPV_OK && r.elite_frac > 0;
     }
@@ -308,10 +316,15 @@ spv_status spv_server_submit(spv_server *s, const spv_request *req, uint64_t *ti
         const spv_status st = ingest(c, &r.problem, 1, kIngestColours, s->ingest_stream, &rec.inst);
         if (st) return st;
     }
-    footprint(s, r, rec.inst, &rec.lds, &rec.hbm);
+    footprint(s, r, rec.inst, false, &rec.lds, &rec.hbm);
+    auto over = [&]() { return rec.lds > s->lds_budget || (s->hbm_budget > 0 && rec.hbm > s->hbm_budget); };
+    if (r.kind == SPV_REQ_PT && over()) {
+        rec.one_workgroup = true;
+        footprint(s, r, rec.inst, true, &rec.lds, &rec.hbm);
+    }
     rec.res.lds_bytes = rec.lds;
     rec.res.hbm_bytes = rec.hbm;
-    if (rec.lds > s->lds_budget || (s->hbm_budget > 0 && rec.hbm > s->hbm_budget))
+    if (over())
         return set_err(c, SPV_EBUDGET, "request needs %lld B LDS / %lld B scratch, budgets %lld / %lld",
                        (long long)rec.lds, (long long)rec.hbm, (long long)s->lds_budget,
                        (long long)s->hbm_budget);
