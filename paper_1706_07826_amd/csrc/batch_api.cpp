@@ -275,7 +275,8 @@ namespace spv {
 
 spv_status sample_batch_inst(spv_ctx *ctx, int32_t B, const Inst *problems, const double *betas, int32_t sweeps,
                              const int32_t *reads, const uint64_t *seeds, int8_t *const *spins,
-                             int64_t *const *energies, const spv_batch_opts *opts, hipStream_t stream) {
+                             int64_t *const *energies, const spv_batch_opts *opts, hipStream_t stream,
+                             const spv_batch_opts *hint) {
     if (!ctx) return SPV_EINVAL;
     Ctx *c = &ctx->c;
     DeviceGuard g(c->device);
@@ -372,12 +373,14 @@ spv_status sample_batch_inst(spv_ctx *ctx, int32_t B, const Inst *problems, cons
         const int narrow = (pl.cls_max + 63) / 64 * 64;
         const bool fills = pl.lanes >= 64ll * 32 * c->num_cus;
         sh = Shape{!fills ? narrow : pl.cls_max > 256 ? 1024 : 512, 1, 1, false, true};
+    } else if (hint) {
+        sh = Shape{hint->threads, hint->quads_per_item, hint->wgs_per_cu};
     }
     // A tuned shape serves batches of its size class that the same bodies are open to (what a
     // body's LDS cannot hold of such a batch falls back below).
     const Shape dflt = sh;
     const std::vector<long long> tkey = {pl.n_max, pl.D_max, pl.nd, B, pl.total_quads / 64, swar, paired_ok, held_ok};
-    bool have = false, given = false;
+    bool have = hint != nullptr, given = false;
     if (opts && opts->threads > 0 && (flags & SPV_BATCH_PAIRED)) {
         if (!paired_ok)
             return set_err(c, SPV_EINVAL, "the paired body needs byte-parallel images of 4, 6 or 8 records per site");

@@ -163,9 +163,11 @@ spv_status sqa_inst(spv_ctx *ctx, const Inst *P, const double *betas, const doub
 // one_workgroup: a run whose planned launch is optional (PtSplit) takes one workgroup instead.
 spv_status pt_inst(spv_ctx *ctx, const Inst *P, const spv_pt_params *prm, const spv_pt_out *out,
                    hipStream_t stream, bool one_workgroup = false);
+// hint: the shape of batches that the held-sites body does not serve (null: the default or a tuned one).
 spv_status sample_batch_inst(spv_ctx *ctx, int32_t B, const Inst *problems, const double *betas, int32_t sweeps,
                              const int32_t *reads, const uint64_t *seeds, int8_t *const *spins,
-                             int64_t *const *energies, const spv_batch_opts *opts, hipStream_t stream);
+                             int64_t *const *energies, const spv_batch_opts *opts, hipStream_t stream,
+                             const spv_batch_opts *hint = nullptr);
 
 // Makes `dev` current for the lifetime of the guard.
 struct DeviceGuard {

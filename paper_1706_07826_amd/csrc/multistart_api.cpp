@@ -353,11 +353,10 @@ spv_status spv_multistart(spv_ctx *ctx, const spv_problem *P0, const spv_multist
                                            seeds[b], sps[b], ens[b], stream)))
                             return st;
                 } else if (!probs.empty()) {
-                    // Modified problems are small: where the batch's default body does not hold
-                    // their sites in registers, a workgroup just wide enough for one colour class x 2
+                    // Modified problems are small: where the batch's held-sites body does not
+                    // serve them, a workgroup just wide enough for one colour class x 2
                     // quad words, so each item's barriers stay cheap and many items share a CU.
-                    int cls = 1, n_big = 0;
-                    for (const Inst &q2 : probs) n_big = std::max(n_big, q2.n);
+                    int cls = 1;
                     for (const Inst &q2 : probs) cls = std::max(cls, (q2.n + q2.n_colours - 1) / q2.n_colours);
                     spv_batch_opts bo;
                     bo.threads = std::min(256, (2 * cls + 63) / 64 * 64);
@@ -365,7 +364,7 @@ spv_status spv_multistart(spv_ctx *ctx, const spv_problem *P0, const spv_multist
                     bo.wgs_per_cu = std::min(16, 1024 / bo.threads);
                     bo.flags = 0;
                     if ((st = sample_batch_inst(ctx, (int32_t)probs.size(), probs.data(), prm->betas, prm->sweeps,
-                                                reads.data(), seeds.data(), sps.data(), ens.data(), n_big <= 1024 ? nullptr : &bo, stream)))
+                                                reads.data(), seeds.data(), sps.data(), ens.data(), nullptr, stream, &bo)))
                         return st;
                 }
             }
