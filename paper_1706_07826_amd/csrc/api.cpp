@@ -295,12 +295,14 @@ spv_status plan_pt_split(Ctx *c, int n, int D, int K, int runs, int chains, int 
     const bool icm = icm_hi > icm_lo, forced = mode == 1 && k4;
     const int quads = (K + 3) / 4, maxg = icm ? K : quads;
     int G = env_int("SPVAR_PT_GROUPS", 0);
-    // Without cluster moves a small ladder off the quads' grid is not split: each group
-    // draws the quads at its ends whole, and below about 768 words a sweep's exchange
-    // messages cost more than its updates (300 sweeps, n x K x chains, split / one group:
-    // 64 x 6 x 1 1.88 / 1.61 ms, 125 x 10 x 2 2.83 / 2.78, 216 x 10 x 1 2.27 / 3.15,
-    // 64 x 30 x 2 2.74 / 4.13).
-    if (G <= 0 && !k4 && !icm && (long long)n * ((chains * K + 3) / 4) < 768) G = 1;
+    // Without cluster moves a short ladder of few sites off the quads' grid is not split: each
+    // group draws the quads at its ends whole, and with two or three groups a sweep's exchange
+    // messages cost more than the updates they spread (300 sweeps, n x K x chains, split / one
+    // group, ms: 64 x 6 x 1 2.06 / 1.77, 125 x 10 x 2 3.10 / 2.89, 216 x 10 x 1 2.21 / 2.15, 343
+    // x 10 x 1 2.76 / 2.66; 216 x 6 x 1 the other way, 1.98 / 2.16; above the line 216 x 10 x 2
+    // 2.69 / 2.87, 512 x 10 x 1 2.37 / 2.60, and longer ladders 64 x 14 x 2 2.98 / 3.39, 64 x 30
+    // x 1 2.45 / 3.37, 216 x 14 x 1 2.32 / 2.47).
+    if (G <= 0 && !k4 && !icm && quads <= 3 && (long long)n * ((chains * K + 3) / 4) < 1050) G = 1;
     if (G <= 0) G = std::max(1, std::min(maxg, c->num_cus / std::max(runs, 1)));
     G = std::min(G, maxg);
     // One group a run: with cluster moves the one-workgroup kernel (a wavefront per slot

@@ -49,3 +49,16 @@ def test_split_multiple_of_four_is_refused(spv, ctx):  # noqa: F811
     with pytest.raises(spv.SpvError, match="EBUDGET"):
         srv.submit_pt(P, betas, 2, 2, 30, 7, icm=(0, 16))
     srv.close()
+
+
+@pytest.mark.parametrize("L,K,chains,split", [(4, 10, 1, False), (4, 14, 2, True), (5, 10, 2, False), (6, 10, 2, True),
+                                              (4, 30, 1, True), (7, 10, 1, False)])
+def test_which_ladders_are_split(spv, ctx, monkeypatch, L, K, chains, split):  # noqa: F811
+    """Ladders off the multiples of four, without cluster moves: in one group with at most three
+    quads and few words a sweep, else split (the footprint counts every group's copy)."""
+    P = spv.Problem.from_instance(si.cubic_lattice(L, "gauss", seed=3, scale_log2=10))
+    betas = si.geometric_betas(0.2, 5.0, K)
+    planned = _lds(spv, ctx, P, betas, 2, chains, None)
+    monkeypatch.setenv("SPVAR_PT_GROUPS", "1")
+    one = _lds(spv, ctx, P, betas, 2, chains, None)
+    assert (planned > one) == split
