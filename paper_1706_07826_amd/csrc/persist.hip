@@ -292,7 +292,7 @@ __device__ __forceinline__ void bitmap(const int8_t *__restrict__ S, int n, int 
     if (w >= f.W || (int)blockIdx.y >= groups) return;
     const int lane = threadIdx.x;
     // the gauge's hash table for the next kernel: keys and counts zero, minima at the top
-    // (TS words of keys, TS / 2 of counts; TS < 4 n, so a workgroup clears a few words)
+    // (TS words of keys, TS / 2 of counts; TS < max(4 n, 65), so a workgroup clears a few words)
     if (clear)
         for (int k = (blockIdx.y * f.W + w) * 64 + lane; k < f.TS + f.TS / 2; k += 64 * f.W * groups) {
             f.tkey[k] = 0ull;
@@ -585,7 +585,9 @@ struct BitmapStep {
 };
 struct GaugeHashStep {
     static constexpr int kThreads = 256;
-    static __device__ __forceinline__ void run(const FixJob &j) { gauge_hash(j.a.n, j.a.m, j.f); }
+    static __device__ __forceinline__ void run(const FixJob &j) {
+        if (j.a.gauge_mode != 0) gauge_hash(j.a.n, j.a.m, j.f);  // (without a gauge the table is not cleared)
+    }
 };
 struct FixReduceStep {
     static constexpr int kThreads = 1024;
