@@ -3,7 +3,11 @@ against the oracle, bit for bit, and prints the detector's counts as one JSON li
 
 * "exchange": tempering ladders split into groups of 4 slots and more, whose in-group swaps store
   words that also hold boundary slots' bytes (instance in LDS and in global memory, one and two
-  chains, a ladder that is no multiple of four).
+  chains, a ladder that is no multiple of four);
+* "records_in_lds": the byte-parallel SA bodies with their records in LDS, one and two words per
+  lane, in one launch and streamed (the held-sites body, which takes such problems by default, off);
+* "held_sites": the held-sites SA body with one and several quads a workgroup, two to four colour
+  classes, streamed, and in a batched launch.
 
 Run by tests/test_gpu_lds_shadow_bodies.py in a process of its own, with a phase's name."""
 import json
@@ -18,7 +22,8 @@ sys.path.insert(0, ROOT)
 import oracle  # noqa: E402
 import paper_1706_07826_amd as spv  # noqa: E402
 import spvar_inputs as si  # noqa: E402
-from tests.lds_shadow_driver import say, with_env  # noqa: E402
+from tests.lds_shadow_driver import sample_case, say, with_env  # noqa: E402
+from tests.test_gpu_held import _layers  # noqa: E402
 
 
 def exchange(ctx):
@@ -39,12 +44,42 @@ def exchange(ctx):
     return dict(class_passes=class_passes)
 
 
+def records_in_lds(ctx):
+    inst = si.chimera(4, seed=3)
+    for words in (1, 2):
+        for stream in (0, 8):
+            sample_case(ctx, f"records_in_lds_w{words}", inst,
+                        {"SPVAR_SA_HELD": 0, "SPVAR_SA_WPL": words, "SPVAR_SA_THREADS": 256,
+                         "SPVAR_SA_STREAM": stream}, reads=300 if stream else 40)
+            shape = spv.spv_sample_last_shape(ctx)
+            assert shape["words_per_lane"] == words and (shape["chunks"] > 1) == (stream > 0)
+    return {}
+
+
+def held_sites(ctx):
+    for name, inst, env, reads in (("chimera", si.chimera(4, seed=3), {}, 40),
+                                   ("quads3", si.chimera(4, seed=3), {"SPVAR_SA_HELD": 3}, 50),
+                                   ("streamed", si.chimera(4, seed=3), {"SPVAR_SA_STREAM": 8}, 300),
+                                   ("three_classes", _layers([50, 50, 50], 2, 4, 3), {}, 40),
+                                   ("four_classes", _layers([40, 40, 40, 40], 2, 4, 4), {}, 40)):
+        sample_case(ctx, f"held_{name}", inst, env, reads=reads)
+    insts = [_layers([40, 40], 3, 6, 5, 4), _layers([9, 8], 3, 6, 6, 4), _layers([129, 64], 3, 6, 7, 4)]
+    reads, seeds, betas = [23, 400, 50], [5, 6, 7], si.linear_betas(0.05, 3.0, 25)
+    say("[shadow] held_batch")
+    sp, en = spv.spv_sample_batch(ctx, [spv.Problem.from_instance(i) for i in insts], betas, reads, seeds)
+    assert spv.spv_batch_last_shape(ctx)["quads_per_item"] == 0
+    for b, inst in enumerate(insts):
+        oS, oE = oracle.sa_sample(inst, betas, reads=reads[b], seed=seeds[b])
+        assert np.array_equal(sp[b].cpu().numpy(), oS) and np.array_equal(en[b].cpu().numpy(), oE), b
+    return {}
+
+
 def main():
     assert "race detection" in spv._lib.spv_version().decode(), spv._lib.spv_version()
     ctx = spv.Context(0)
     for phase in sys.argv[1:]:
         spv.spv_debug_lds_shadow(ctx, reset=True)
-        extra = {"exchange": exchange}[phase](ctx)
+        extra = dict(exchange=exchange, records_in_lds=records_in_lds, held_sites=held_sites)[phase](ctx)
         print(json.dumps(dict(phase=phase, **spv.spv_debug_lds_shadow(ctx, reset=True), **extra)), flush=True)
 
 

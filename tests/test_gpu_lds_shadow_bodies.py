@@ -32,3 +32,9 @@ def test_exchange():
     barrier interval stores whole."""
     d = _phase("exchange")
     assert d["passes"] > d["class_passes"]  # the exchanges with in-group swaps were checked too
+
+
+@pytest.mark.parametrize("phase", ["records_in_lds", "held_sites"])
+def test_sampling_bodies(phase):
+    """The byte-parallel SA bodies, each under a switch that makes the launch take it."""
+    assert _phase(phase)["passes"] > 1000
