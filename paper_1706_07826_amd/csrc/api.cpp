@@ -1098,7 +1098,7 @@ spv_status pt_inst(spv_ctx *ctx, const Inst *P, const spv_pt_params *prm, const 
     // from running) are run again that way behind the split launch, from a copy of the checkpoint
     // where the outputs lie over it.
     const bool redo = sp.use && sp.G > 1 && K % 4 != 0;
-    const size_t b_xw = al((n_xw + (redo ? runs : 0)) * 4);
+    const size_t b_xw = n_grp ? al((runs + n_xw) * 4) : 0;  // the runs' marks, then the messages
     PtResume again = rs;
     size_t b_copy = 0;
     auto copied = [&](const void *in, const void *o, size_t bytes) {
@@ -1147,7 +1147,7 @@ spv_status pt_inst(spv_ctx *ctx, const Inst *P, const spv_pt_params *prm, const 
         X.out = out;
         unsigned char *sc = sbase;
         X.tops = reinterpret_cast<int8_t *>(sc);
-        X.xw = reinterpret_cast<uint32_t *>(sc + b_top);
+        X.xw = reinterpret_cast<uint32_t *>(sc + b_top) + runs;
         X.G = sp.G;
         X.m = sp.m;
         X.threads = sp.threads;
@@ -1155,7 +1155,6 @@ spv_status pt_inst(spv_ctx *ctx, const Inst *P, const spv_pt_params *prm, const 
         X.spin_limit = pt_spin_limit();
         X.resume = rs;
         if (redo) {
-            X.redo = reinterpret_cast<int32_t *>(X.xw + n_xw);
             auto copy = [&](auto &p, size_t at, size_t bytes) {
                 if (at == 0 || e != hipSuccess) return;
                 e = hipMemcpyAsync(sc + at, p, bytes, hipMemcpyDeviceToDevice, stream);
@@ -1195,7 +1194,7 @@ spv_status pt_inst(spv_ctx *ctx, const Inst *P, const spv_pt_params *prm, const 
     L.nqa = nqa;
     L.threads = threads;
     L.resume = rs;
-    if (redo) L.redo = reinterpret_cast<const int32_t *>(sbase + b_top) + n_xw;
+    if (redo) L.redo = reinterpret_cast<const uint32_t *>(sbase + b_top) + runs;
     return hip_check(c, launch_pt(L, stream), "pt launch");
 }
 

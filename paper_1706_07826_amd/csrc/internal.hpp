@@ -379,7 +379,7 @@ struct PtLaunch {
     int nqa;               // quads per run window
     int threads;
     PtResume resume;
-    const int32_t *redo = nullptr;  // [runs]: only runs marked here (null: all)
+    const uint32_t *redo = nullptr;  // only runs r with a mark at redo[-1 - r] (null: all)
 };
 size_t pt_lds_bytes(int n, int D, int K, int chains, int row_len, int nqa, int nw_icm);
 hipError_t launch_pt(const PtLaunch &L, hipStream_t s);
@@ -399,13 +399,12 @@ struct PtxLaunch {
     const int32_t *snd;
     const spv_pt_out *out;
     int8_t *tops;             // [runs][Ls][10][n]
-    uint32_t *xw;             // [runs][G][2][2][chains][ptx_msg_words(n)]
+    uint32_t *xw;             // [runs][G][2][2][chains][ptx_msg_words(n)] behind [runs] marks, run r's at xw[-1 - r]
     int G, m, threads;
     bool big;
     bool esum;                // one slot pair per group: cluster energy terms gathered in the joins
     unsigned spin_limit;
     PtResume resume;
-    int32_t *redo = nullptr;  // [runs], behind xw: runs with an abandoned wait are marked here, not in their lists
 };
 struct PtSplit {
     bool use = false, big = false, esum = false;

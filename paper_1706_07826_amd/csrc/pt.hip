@@ -45,7 +45,7 @@ struct PtArgs {
     int32_t *top_count;
     int8_t *tops;  // [runs][L][10][n], position order
     PtResume rs;   // checkpoint to start from
-    const int32_t *redo;  // [runs] or null: runs to work on
+    const uint32_t *redo;  // null, or behind the runs' marks: run r is worked on if redo[-1 - r] is set
     int n, D, C, K, chains, sweeps, row_len, nqa, icm_lo, icm_hi, nw_icm;
     uint32_t sweep_offset, k0, k1;
 };
@@ -111,7 +111,7 @@ __global__ __launch_bounds__(1024) void pt_kernel(PtArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int cs[kMaxColours + 1];
     __shared__ int nacc;
-    if (a.redo && a.redo[blockIdx.x] == 0) return;
+    if (a.redo && *(a.redo - 1 - (int)blockIdx.x) == 0u) return;
     PtLds L;
     const int n = a.n, D = a.D, K = a.K, chains = a.chains, nqa = a.nqa;
     pt_layout(n, D, K, chains, a.row_len, nqa, a.nw_icm, &L, smem);

@@ -10,7 +10,7 @@
 // When K is no multiple of 4 the quads of a chain start at another slot in every
 // (run, chain), so a group holds every quad its slots of a chain touch and owns
 // some of their bytes, at an offset of the chain's own (26 slots x 2 chains x 8 runs of
-// the L = 6 cube with cluster moves, 300 sweeps: 54.3 ms in one workgroup a run, 5.2 ms
+// the L = 6 cube with cluster moves, 300 sweeps: 54.3 ms in one workgroup a run, 5.0 ms
 // as 26 groups of one slot).
 // A group of one slot reading its instance from the global image keeps both
 // chains' bytes of that slot in one word per site (byte c: chain c), each byte
@@ -19,7 +19,7 @@
 // partners (chain 0 and chain 1 at one slot) share its LDS.  A sweep is
 //   1. Metropolis on the group's replicas (colour classes in order),
 //   2. replica exchange of pairs (k, k+1), k = t mod 2.  Pairs inside the
-//      group are decided from LDS energies and swapped byte-wise; a pair that
+//      group are decided from LDS energies and swapped within a site's words; a pair that
 //      straddles a group boundary (on odd sweeps when m is even; the lower and
 //      the upper boundary on alternate sweeps when m = 1) is decided by both
 //      neighbours from the energies each publishes (with the edge
@@ -36,7 +36,8 @@
 //
 // Waits for a neighbour's words are bounded: a workgroup whose neighbour does
 // not publish within the spin limit stops and marks its lists with
-// top_count = -1.  The host only launches grids that fit on the device at once.
+// top_count = -1, or, when K is no multiple of 4, its run, which the one-workgroup
+// kernel then runs again.  The host only launches grids that fit on the device at once.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -66,9 +67,9 @@ struct PtxArgs {
     long long *top_E;
     int32_t *top_count;
     int8_t *tops;          // [runs][Ls][10][n], position order
-    uint32_t *xw;          // [runs][G][side 2][buf 2][chains][xmsg] tagged boundary messages
+    uint32_t *xw;          // [runs][G][side 2][buf 2][chains][xmsg] tagged boundary messages; before
+                           // them, from xw[-1] down, a mark per run with an abandoned wait (K % 4 != 0)
     PtResume rs;           // checkpoint to start from
-    int32_t *redo;         // [runs] or null: marks of runs with an abandoned wait
     int n, D, C, K, chains, sweeps, row_len, icm_lo, icm_hi, nw_icm, G, m, xmsg, esum;
     uint32_t sweep_offset, k0, k1;
     unsigned spin_limit;
@@ -1461,8 +1462,8 @@ __global__ __launch_bounds__(1024) void ptx_kernel(PtxArgs a) {
     }
 
     const int kc = max(K - half, s0), ncold = max(0, s0 + mg - kc);
-    if (stop && a.redo) {
-        if (tid == 0) a.redo[run] = 1;
+    if (stop && !k4) {
+        if (tid == 0) *(a.xw - 1 - run) = 1u;
         return;
     }
     if (stop) {
@@ -1594,7 +1595,6 @@ hipError_t launch_ptx(const PtxLaunch &P, hipStream_t s) {
     a.tops = P.tops;
     a.rs = P.resume;
     a.xw = P.xw;
-    a.redo = P.redo;
     a.xmsg = ptx_msg_words(P.n);
     a.n = P.n;
     a.D = P.D;
@@ -1614,9 +1614,9 @@ hipError_t launch_ptx(const PtxLaunch &P, hipStream_t s) {
     a.k1 = (uint32_t)(P.seed >> 32);
     a.spin_limit = P.spin_limit;
     if (P.G > 1) {
-        const size_t words = (size_t)P.runs * P.G * 4 * P.chains * ptx_msg_words(P.n) + (P.redo ? P.runs : 0);
+        const size_t words = (size_t)P.runs * (1 + (size_t)P.G * 4 * P.chains * ptx_msg_words(P.n));
         hipLaunchKernelGGL(xw_zero_kernel, dim3((unsigned)std::min<size_t>((words + 255) / 256, 4096)), dim3(256), 0,
-                           s, P.xw, words);
+                           s, P.xw - P.runs, words);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
