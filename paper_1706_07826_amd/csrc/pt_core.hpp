@@ -138,7 +138,12 @@ __device__ __forceinline__ void quad_sums(Rec rec, int D, int p, const uint32_t 
         for (int u = 0; u < kRecBatch; ++u) rr[u] = rec(k0 + u, p);
         core::neighbour_sum<kRecBatch, NB>(rr, sa, row, acc, b0);
     }
-    for (; k0 < D; ++k0) {
+    if (k0 + 2 <= D) {
+        const uint32_t rr[2] = {rec(k0, p), rec(k0 + 1, p)};
+        core::neighbour_sum<2, NB>(rr, sa, row, acc, b0);
+        k0 += 2;
+    }
+    if (k0 < D) {
         const uint32_t rr[1] = {rec(k0, p)};
         core::neighbour_sum<1, NB>(rr, sa, row, acc, b0);
     }
@@ -173,9 +178,11 @@ __device__ __forceinline__ void add_flip(long long &sum, int32_t x, uint32_t tak
     sum += (long long)x * (long long)(int32_t)taken;
 }
 
-// Lock-free union-find in LDS over 16-bit parents (parent[x] <= x always: a
-// root is only ever hooked under a smaller root, so every find terminates;
-// path splitting writes only ancestors, so concurrent finds stay valid).
+// Lock-free union-find in LDS over 16-bit parents.  parent[x] < x for every x that is no
+// root, so a chain strictly decreases, every find terminates and a root is the smallest
+// member of its tree.  A root is only ever hooked under a smaller node, which therefore lies
+// in another tree (uf_union hooks it under that tree's root, the join scan's first hook under
+// any member).  Path splitting writes only ancestors, so concurrent finds stay valid.
 __device__ __forceinline__ uint32_t uf_find(uint16_t *parent, uint32_t x) {
     uint32_t p = parent[x];
     while (p != x) {

@@ -57,7 +57,8 @@ __global__ __launch_bounds__(1024) void sqa_kernel(SqaArgs a) {
     __shared__ int best_s;
     __shared__ long long bestE_s;
     constexpr bool SITE = DK == kSiteRecs;
-    static_assert(DK == 0 || (SITE && !BIG), "site blocks hold kSiteRecs records in LDS");
+    static_assert(DK == 0 || !BIG, "compile-time record counts are of the LDS instance");
+    constexpr bool FEW = DK > 0 && !SITE;  // records neighbour-major, as when D is known at run time only
     constexpr int SH = core::field_shift<ND>;
     const int n = a.n, D = a.D, P = a.P, qw = P / 4, G8 = P / 8, T = blockDim.x, tid = threadIdx.x;
     const int read = blockIdx.x;
@@ -72,7 +73,7 @@ __global__ __launch_bounds__(1024) void sqa_kernel(SqaArgs a) {
         core::sa_bind_image(&L, it, cs);  // ends with a barrier
     } else {
         core::sa_layout(n, D, a.row_len, qw, &L, smem);
-        core::sa_load_instance<DK>(L, it, cs);  // ends with a barrier
+        core::sa_load_instance<SITE ? DK : 0>(L, it, cs);  // ends with a barrier
     }
     // record k of position p: nbr[p * rec_p + k * rec_k]
     const size_t rec_p = SITE ? (size_t)(DK + 2) : BIG ? (size_t)D : 1, rec_k = (BIG || SITE) ? 1 : (size_t)n;
@@ -98,7 +99,13 @@ __global__ __launch_bounds__(1024) void sqa_kernel(SqaArgs a) {
 
     const int q = tid % G8, slot = tid / G8, nslots = T / G8;
     const bool active = slot < nslots;
-    const uint32_t s_addr = core::swar_lds_addr(L.S), s_row = 4u * (uint32_t)qw;
+    uint32_t s_addr = core::swar_lds_addr(L.S);
+    const uint32_t s_row = 4u * (uint32_t)qw;
+    // (few records: their loop is short enough for an address stepped per read to show, so a
+    // site's addresses are taken from one opaque base instead)
+#ifdef __OPTIMIZE__
+    if constexpr (FEW) asm volatile("" : "+s"(s_addr));
+#endif
     // Race-detection build: each (class, parity) pass's slice-word writes, then its
     // reads (the ring neighbours' words of the other parity and the classical
     // neighbours' words), against the LDS bitmap.
@@ -152,8 +159,11 @@ __global__ __launch_bounds__(1024) void sqa_kernel(SqaArgs a) {
                 const int wa = par ? q : G8 + q;
                 const int wb = par ? (q + 1 == G8 ? 0 : q + 1) : G8 + (q == 0 ? G8 - 1 : q - 1);
                 for (int p = cs[c] + slot; active && p < pe; p += nslots) {
-                    const uint32_t *row = L.S + (size_t)p * qw;
-                    const uint32_t self = row[w], A = row[wa], B = row[wb];
+                    const uint32_t row = s_addr + __umul24((uint32_t)p, s_row);
+                    auto word = [&](int v) __attribute__((always_inline)) -> uint32_t {
+                        return FEW ? core::swar_ld32(row + 4u * (uint32_t)v) : L.S[(size_t)p * qw + v];
+                    };
+                    const uint32_t self = word(w), A = word(wa), B = word(wb);
                     // even word: k-1 = odd slice m-1 (A byte b-1, or B byte 3), k+1 = odd slice m (A byte b);
                     // odd word: k-1 = even slice m (A byte b), k+1 = even slice m+1 (A byte b+1, or B byte 0)
                     const uint32_t up = par ? A : __builtin_amdgcn_alignbyte(A, B, 3);
@@ -175,7 +185,14 @@ __global__ __launch_bounds__(1024) void sqa_kernel(SqaArgs a) {
                         hv = L.hpos[p];
                         ord = (uint32_t)L.ord[p];
                         start();
-                        core::neighbour_sum_any(L.nbr + p * rec_p, rec_k, D, s_addr + 4u * (uint32_t)w, s_row, f);
+                        if constexpr (FEW) {
+                            uint32_t r[DK];
+#pragma unroll
+                            for (int k = 0; k < DK; ++k) r[k] = L.nbr[(uint32_t)p + (uint32_t)k * (uint32_t)n];
+                            core::neighbour_sum(r, s_addr + 4u * (uint32_t)w, s_row, f);
+                        } else {
+                            core::neighbour_sum_any(L.nbr + p * rec_p, rec_k, D, s_addr + 4u * (uint32_t)w, s_row, f);
+                        }
                     }
                     if constexpr (SH == 0)
 #pragma unroll
@@ -189,7 +206,11 @@ __global__ __launch_bounds__(1024) void sqa_kernel(SqaArgs a) {
                     for (int b = 0; b < 4; ++b) x[b] = core::flip_cost(self, b, f[b]);
                     const uint32_t mask = core::metropolis_mask<ND>(x, tcur, ord, t, quad0 + (uint32_t)w, a.k0, a.k1,
                                                                     kTagSqa << 24, ndt);
-                    if (mask) L.S[(size_t)p * qw + w] = self ^ mask;
+                    if constexpr (FEW) {
+                        if (mask) core::swar_st32(row + 4u * (uint32_t)w, self ^ mask);
+                    } else {
+                        if (mask) L.S[(size_t)p * qw + w] = self ^ mask;
+                    }
                 }
                 if (c + 1 == a.C && par == 1) core::row_store(tnext, next_len, nrow);
                 __syncthreads();
@@ -261,14 +282,25 @@ hipError_t launch_sqa(const SqaLaunch &L, hipStream_t s) {
     a.k1 = (uint32_t)(L.seed >> 32);
     const size_t lds = sqa_lds_bytes(L.n, L.D, L.row_len, L.P, L.global_instance);
     if (L.P % 8 != 0 || L.P < 8 || L.threads % (L.P / 8) != 0 || L.reads < 1) return hipErrorInvalidValue;
+#define SPV_SQA_GO(...) hipLaunchKernelGGL((sqa_kernel<__VA_ARGS__>), dim3(L.reads), dim3(L.threads), lds, s, a)
+    // The record counts with straight-line loops: six (cubes, Chimera graphs; 500 sweeps of 1000
+    // reads on Chimera 8 x 8 4.8 ms, D at run time 5.5), and one to three, where the run-time loop
+    // costs as much as the records (n = 200, two records, 64 slices x 300 reads x 100 sweeps: 1.06
+    // ms, D at run time 1.15).
 #define SPV_SQA(ND_)                                                                                  \
     do {                                                                                              \
         if (L.global_instance)                                                                        \
-            hipLaunchKernelGGL((sqa_kernel<ND_, true>), dim3(L.reads), dim3(L.threads), lds, s, a);   \
-        else if (L.D == kSiteRecs)                                                              \
-            hipLaunchKernelGGL((sqa_kernel<ND_, false, kSiteRecs>), dim3(L.reads), dim3(L.threads), lds, s, a); \
+            SPV_SQA_GO(ND_, true);                                                                    \
+        else if (L.D == kSiteRecs)                                                                    \
+            SPV_SQA_GO(ND_, false, kSiteRecs);                                                        \
+        else if (L.D == 1)                                                                            \
+            SPV_SQA_GO(ND_, false, 1);                                                                \
+        else if (L.D == 2)                                                                            \
+            SPV_SQA_GO(ND_, false, 2);                                                                \
+        else if (L.D == 3)                                                                            \
+            SPV_SQA_GO(ND_, false, 3);                                                                \
         else                                                                                          \
-            hipLaunchKernelGGL((sqa_kernel<ND_>), dim3(L.reads), dim3(L.threads), lds, s, a);         \
+            SPV_SQA_GO(ND_);                                                                          \
     } while (0)
     switch (L.nd) {
         case 1:
@@ -284,6 +316,7 @@ hipError_t launch_sqa(const SqaLaunch &L, hipStream_t s) {
             return hipErrorInvalidValue;
     }
 #undef SPV_SQA
+#undef SPV_SQA_GO
     return hipGetLastError();
 }
 
