@@ -10,10 +10,9 @@
 //   2. replica exchange of pairs (k, k+1), k = t mod 2, decided from the
 //      energies held in LDS, configurations swapped byte-wise,
 //   3. Houdayer moves (chains 0/1): a wavefront per slot picks the seed with
-//      ballots, finds its component with a union-find over the disagreeing
-//      sites (no barrier: a wavefront owns its forest) and flips it in both
-//      replicas.  A breadth-first growth, a queue chunk and a ballot per record
-//      at a time, was a chain of dependent LDS reads as long as the cluster,
+//      ballots, finds its component (breadth-first, or with a union-find over
+//      the disagreeing sites; no barrier: a wavefront owns its slots' arrays)
+//      and flips it in both replicas,
 //   4. the colder half is offered to per-slot lists of the 10 lowest-energy
 //      distinct states (a wavefront per list: ballot compare, byte copy).
 // Replicas of a quad that belong to a neighbouring run (when chains*K is not
@@ -50,6 +49,19 @@ struct PtArgs {
     uint32_t sweep_offset, k0, k1;
 };
 
+// How a cluster is found.  Breadth-first growth takes a queue chunk and a ballot per record at
+// a time: cost as the cluster's depth.  The union-find takes every disagreeing edge, 64 sites
+// at a time: cost as the sites.  Measured (300 runs x 6 slots x 2 chains, cluster moves, 60
+// sweeps, ms, breadth-first / union-find): cube L = 3 1.94 / 1.54, 128 sites of degree 6 3.40 /
+// 1.87, L = 6 3.76 / 3.12, L = 7 4.49 / 4.90, 300 sites 2.33 / 2.78, 600 sites 4.63 / 5.38; 50
+// cliques of 5 sites 1.61 / 2.44.  So beyond kForestSites sites growth, up to there the
+// union-find, unless the slot's last cluster was small (and the sites are more than
+// kFewSites): then growth up to kSmallCluster sites, and the union-find should it grow further
+// (the cliques: 1.57).
+constexpr int kForestSites = 256;
+constexpr int kFewSites = 128;
+constexpr int kSmallCluster = 16;
+
 struct PtLds {
     uint32_t *nbr;
     int32_t *hpos, *ord, *pos;
@@ -64,7 +76,7 @@ struct PtLds {
     int32_t *Lord;     // [L][10]
     int32_t *acc;      // [cK]
     uint32_t *dis;     // [nw_icm][nwords] disagreement bits by position
-    uint16_t *parent;  // [nw_icm][n] union-find forests over positions
+    uint16_t *parent;  // [nw_icm][n] union-find forest over positions, or queue of a growth
 };
 
 __host__ __device__ inline size_t al16(size_t x) { return (x + 15) & ~(size_t)15; }
@@ -234,6 +246,7 @@ __global__ __launch_bounds__(1024) void pt_kernel(PtArgs a) {
         }
     };
 
+    unsigned long long small_slots = 0;  // this wavefront's slots (in its order, the first 64) whose last cluster was small
     for (int ls = 0; ls < a.sweeps; ++ls) {
         const uint32_t t = a.sweep_offset + (uint32_t)ls;
         // 1. Metropolis on every slot.
@@ -307,7 +320,8 @@ __global__ __launch_bounds__(1024) void pt_kernel(PtArgs a) {
         if (a.nw_icm > 0 && wid < a.nw_icm) {
             uint32_t *dis = L.dis + (size_t)wid * nwords;
             uint16_t *parent = L.parent + (size_t)wid * n;
-            for (int k = a.icm_lo + wid; k < a.icm_hi; k += a.nw_icm) {
+            int nth = 0;
+            for (int k = a.icm_lo + wid; k < a.icm_hi; k += a.nw_icm, ++nth) {
                 const int la = k, lb = K + k;
                 const int ra = r0 + la, rb = r0 + lb;
                 const size_t qa_ = (size_t)((ra >> 2) - qf), qb_ = (size_t)((rb >> 2) - qf);
@@ -345,35 +359,101 @@ __global__ __launch_bounds__(1024) void pt_kernel(PtArgs a) {
                     }
                     seen += cnt;
                 }
-                // join the ends of every J != 0 edge between disagreeing sites (from its smaller end)
-                for (int p = lane; p < n; p += 64) {
-                    if (!differs(p)) continue;
-                    for (int kk = 0; kk < D; ++kk) {
-                        const uint32_t rec = L.nbr[(size_t)kk * n + p];
-                        const int u = (int)(rec >> 16);
-                        if (u > p && (rec & 0xffffu) != 0u && differs(u)) ptc::uf_union(parent, (uint32_t)p, (uint32_t)u);
-                    }
-                }
-                __builtin_amdgcn_wave_barrier();
-                // Energy change and flip of the seed's component.  A neighbour outside it agrees
-                // in both replicas and keeps its value, so a site is flipped as soon as it is
-                // summed; replica B's spin is -s_A and its field the same, so its change is -dA.
-                const uint32_t root = ptc::uf_find(parent, (uint32_t)seed_p);
+                // Energy change and flip of a cluster site p.  A neighbour (J != 0) outside the
+                // cluster agrees in both replicas and keeps its value, so a site is flipped as
+                // soon as it is summed; replica B's spin is -s_A and its field the same, so its
+                // change is -dA.
                 long long dA = 0;
-                for (int p = lane; p < n; p += 64) {
-                    if (!differs(p) || ptc::uf_find(parent, (uint32_t)p) != root) continue;
+                auto flip = [&](int p, auto agrees) __attribute__((always_inline)) {
                     int32_t f = L.hpos[p];
                     for (int kk = 0; kk < D; ++kk) {
                         const uint32_t rec = L.nbr[(size_t)kk * n + p];
                         const int u = (int)(rec >> 16);
-                        if ((rec & 0xffffu) != 0u && !differs(u))
+                        if ((rec & 0xffffu) != 0u && agrees(u))
                             f += (int32_t)(int16_t)(rec & 0xffffu) * (int32_t)(int8_t)*byteA(u);
                     }
                     const int sA = (int)(int8_t)*byteA(p);
                     dA -= 2ll * sA * f;
                     *byteA(p) = (unsigned char)(-sA);
                     *byteB(p) = (unsigned char)sA;
+                };
+                const bool was_small = n > kFewSites && nth < 64 && ((small_slots >> nth) & 1ull);
+                int size = 0;
+                bool grown = false;
+                if (n > kForestSites || was_small) {
+                    // A site's bit is cleared when it enters the queue.
+                    uint16_t *queue = parent;
+                    const int limit = n > kForestSites ? n : kSmallCluster;
+                    if (lane == 0) {
+                        dis[seed_p >> 5] &= ~(1u << (seed_p & 31));
+                        queue[0] = (uint16_t)seed_p;
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                    int head = 0;
+                    size = 1;
+                    while (head < size && size <= limit) {
+                        const int chunk = min(64, size - head);
+                        const int v = lane < chunk ? (int)queue[head + lane] : 0;
+                        int tail = size;
+                        for (int kk = 0; kk < D; ++kk) {
+                            uint32_t u = 0;
+                            bool added = false;
+                            if (lane < chunk) {
+                                const uint32_t rec = L.nbr[(size_t)kk * n + v];
+                                u = rec >> 16;
+                                const uint32_t bit = 1u << (u & 31u);
+                                if ((rec & 0xffffu) != 0u && differs((int)u)) added = (atomicAnd(&dis[u >> 5], ~bit) & bit) != 0u;
+                            }
+                            const unsigned long long m = __ballot(added);
+                            if (added) queue[tail + __popcll(m & lanemask_lt())] = (uint16_t)u;
+                            tail += __popcll(m);
+                        }
+                        head += chunk;
+                        size = tail;
+                        __builtin_amdgcn_wave_barrier();
+                    }
+                    grown = head == size;
+                    if (grown) {
+                        for (int e = lane; e < size; e += 64)
+                            flip(queue[e], [=](int u) __attribute__((always_inline)) { return *byteA(u) == *byteB(u); });
+                    } else {
+                        // too large: bits and forest as before the growth
+                        for (int e = lane; e < size; e += 64) {
+                            const int v = queue[e];
+                            atomicOr(&dis[v >> 5], 1u << (v & 31));
+                        }
+                        __builtin_amdgcn_wave_barrier();
+                        for (int p = lane; p < n; p += 64) parent[p] = (uint16_t)p;
+                    }
+                    __builtin_amdgcn_wave_barrier();
                 }
+                if (!grown) {
+                    // join the ends of every J != 0 edge between disagreeing sites, from its
+                    // larger end (the first class, lowest in position, has none): a site still
+                    // its own root is hooked under its first such neighbour at once
+                    for (int p = cs[1] + lane; p < n; p += 64) {
+                        if (!differs(p)) continue;
+                        bool fresh = true;
+                        for (int kk = 0; kk < D; ++kk) {
+                            const uint32_t rec = L.nbr[(size_t)kk * n + p];
+                            const uint32_t u = rec >> 16;
+                            if (u >= (uint32_t)p || (rec & 0xffffu) == 0u || !differs((int)u)) continue;
+                            if (!(fresh && ptc::cas16(parent + p, (uint32_t)p, u))) ptc::uf_union(parent, (uint32_t)p, u);
+                            fresh = false;
+                        }
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                    const uint32_t root = ptc::uf_find(parent, (uint32_t)seed_p);
+                    size = 0;
+                    for (int p0 = 0; p0 < n; p0 += 64) {
+                        const int p = p0 + lane;
+                        const bool in = p < n && differs(p) && ptc::uf_find(parent, (uint32_t)p) == root;
+                        size += __popcll(__ballot(in));
+                        if (in) flip(p, [=](int u) __attribute__((always_inline)) { return !differs(u); });
+                    }
+                }
+                if (nth < 64)
+                    small_slots = size <= kSmallCluster / 2 ? small_slots | (1ull << nth) : small_slots & ~(1ull << nth);
                 dA = wave_sum(dA);
                 if (lane == 0) {
                     L.E[la] += dA;
