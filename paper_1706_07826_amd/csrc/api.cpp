@@ -287,28 +287,52 @@ static int env_int(const char *name, int dflt) {
 unsigned pt_spin_limit() { return (unsigned)env_int("SPVAR_PT_SPIN", 1 << 24); }
 
 spv_status plan_pt_split(Ctx *c, int n, int D, int K, int runs, int chains, int row_len, int nd, int icm_lo,
-                         int icm_hi, bool single_fits, PtSplit *sp) {
+                         int icm_hi, const PtSingle &single, PtSplit *sp) {
     sp->use = false;
     const int mode = env_int("SPVAR_PT_SPLIT", -1);
     const bool k4 = K % 4 == 0;
-    if (mode == 0 || n < 1 || (!k4 && !single_fits)) return SPV_OK;
+    if (mode == 0 || n < 1 || (!k4 && !single.fits)) return SPV_OK;
     const bool icm = icm_hi > icm_lo, forced = mode == 1 && k4;
     const int quads = (K + 3) / 4, maxg = icm ? K : quads;
     int G = env_int("SPVAR_PT_GROUPS", 0);
-    // Without cluster moves a short ladder of few sites off the quads' grid is not split: each
-    // group draws the quads at its ends whole, and with two or three groups a sweep's exchange
-    // messages cost more than the updates they spread (300 sweeps, n x K x chains, split / one
-    // group, ms: 64 x 6 x 1 2.06 / 1.77, 125 x 10 x 2 3.10 / 2.89, 216 x 10 x 1 2.21 / 2.15, 343
-    // x 10 x 1 2.76 / 2.66; 216 x 6 x 1 the other way, 1.98 / 2.16; above the line 216 x 10 x 2
-    // 2.69 / 2.87, 512 x 10 x 1 2.37 / 2.60, and longer ladders 64 x 14 x 2 2.98 / 3.39, 64 x 30
-    // x 1 2.45 / 3.37, 216 x 14 x 1 2.32 / 2.47).
-    if (G <= 0 && !k4 && !icm && quads <= 3 && (long long)n * ((chains * K + 3) / 4) < 1050) G = 1;
-    if (G <= 0) G = std::max(1, std::min(maxg, c->num_cus / std::max(runs, 1)));
+    const long long words = (long long)n * ((chains * K + 3) / 4);
+    if (G <= 0) {
+        G = std::max(1, std::min(maxg, c->num_cus / std::max(runs, 1)));
+        // Where the one-workgroup kernel also serves, it or one group is taken where measured to
+        // be the faster (60 or 300 sweeps, sites x slots x chains x runs, ms).
+        // Cluster moves, K off the quads' grid: two groups have several slot pairs each and are
+        // slower than three (128 x 10 x 2 x 90 runs, one workgroup / 2 / 3 groups: 3.6 / 4.2 /
+        // 2.8), and few sites do not repay a split into so few (32 x 10 x 2 x 90: 1.52 / 2.40 /
+        // 1.62).
+        // Other ladders off the grid: each group draws the quads at its ends whole.  Sites of
+        // no straight-line record count pay it in a kernel that holds every body (split or one
+        // group / one workgroup: 32 x 13 x 1 x 1 0.55 / 0.41, 120 x 3 x 2 x 40 0.51 / 0.42, 250 x
+        // 3 x 2 x 1 0.91 of it; but 250 x 10 x 1 1.17 and 32 x 30 x 2 1.37 times as fast).  With
+        // two or three groups a sweep's exchange messages cost more than the updates they spread
+        // (split / one group: 64 x 6 x 1 2.06 / 1.77, 125 x 10 x 2 3.10 / 2.89, 216 x 10 x 1 2.21
+        // / 2.15, 343 x 10 x 1 2.76 / 2.66; 216 x 6 x 1 the other way, 1.98 / 2.16; above the line
+        // 216 x 10 x 2 2.69 / 2.87, 512 x 10 x 1 2.37 / 2.60, and longer ladders 64 x 14 x 2 2.98 /
+        // 3.39, 64 x 30 x 1 2.45 / 3.37).
+        if (!k4 && icm) {
+            if (G == 2) G = std::min(3, maxg);
+            if (n < 64 && G <= 3) return SPV_OK;
+        } else if (!k4) {
+            const bool line = D == kSiteRecs;
+            if (!line && (n < 64 ? G < 5 || words < 250 : quads <= 2 && words < 512)) return SPV_OK;
+            if (quads <= 3 && words < 1050) G = 1;
+        } else if (!icm && G <= 2 && single.fits && !forced && D != kSiteRecs &&
+                   (n < 64 || (n < 128 && quads <= 2))) {
+            // one or two groups / one workgroup: 32 x 4 x 2 x 300 0.56 / 0.52, 32 x 8 x 1 x 1 0.55 /
+            // 0.46, 32 x 24 x 1 x 90 0.77 / 0.66, 120 x 8 x 1 x 20 0.60 / 0.56; 250 x 4 x 1 x 140 1.10
+            // times as fast in one group
+            return SPV_OK;
+        }
+    }
     G = std::min(G, maxg);
     // One group a run: with cluster moves the one-workgroup kernel (a wavefront per slot
     // pair), else this kernel with the instance in LDS (16 slots of 512 sites, 160 runs,
     // 100 sweeps: 1.00 ms against 1.88 in the one-workgroup kernel).
-    if (single_fits && G == 1 && icm && !forced) return SPV_OK;
+    if (single.fits && G == 1 && icm && !forced) return SPV_OK;
     for (;; ++G) {
         if (G > maxg) {
             if (!k4) return SPV_OK;
@@ -331,7 +355,7 @@ spv_status plan_pt_split(Ctx *c, int n, int D, int K, int runs, int chains, int 
         if (threads > 1024) continue;
         const int icm_slots = icm_hi > icm_lo ? std::min(m, icm_hi - icm_lo) : 0;
         for (int big = env_int("SPVAR_PT_BIG", 0) ? 1 : 0; big < 2; ++big) {
-            if (Gr == 1 && big && single_fits && !forced) return SPV_OK;
+            if (Gr == 1 && big && single.fits && !forced) return SPV_OK;
             for (int nw = std::min(icm_slots, 4); nw >= (icm_slots ? 1 : 0); --nw)
             for (int esum = nw == 1 && env_int("SPVAR_PT_ESUM", 1) ? 1 : 0; esum >= 0; --esum) {
                 const PtxShape shape{n, D, K, m, chains, row_len, nd, nw, big != 0, esum != 0};
@@ -340,6 +364,28 @@ spv_status plan_pt_split(Ctx *c, int n, int D, int K, int runs, int chains, int 
                 int bpc = 0;
                 hipError_t e = ptx_max_groups_resident(shape, threads, lds, &bpc);
                 if (e != hipSuccess) return hip_check(c, e, "occupancy query");
+                // One group a run: narrower workgroups where they let more runs be resident
+                // at once, and the one-workgroup kernel where its runs take fewer rounds of the
+                // device (tables and lists of this one take more LDS; 27 x 32 x 2, 300 runs: 2.08 ms
+                // in two rounds, 1.46 in one).
+                if (Gr == 1 && !forced) {
+                    for (int t = threads / 2; t >= std::max({256, nq, pairs}) && bpc * c->num_cus < runs; t /= 2) {
+                        int b = 0;
+                        if ((e = ptx_max_groups_resident(shape, t, lds, &b)) != hipSuccess)
+                            return hip_check(c, e, "occupancy query");
+                        if (b > bpc) {
+                            bpc = b;
+                            threads = t;
+                        }
+                    }
+                    if (single.fits && bpc * c->num_cus < runs) {
+                        int b = 0;
+                        if ((e = pt_max_runs_resident(nd, single.threads, single.lds, &b)) != hipSuccess)
+                            return hip_check(c, e, "occupancy query");
+                        auto rounds = [&](int per_cu) { return (runs - 1) / std::max(1, per_cu * c->num_cus); };
+                        if (rounds(b) < rounds(bpc)) return SPV_OK;
+                    }
+                }
                 // (a run of one group waits for no other)
                 if (Gr > 1 && (long long)bpc * c->num_cus < (long long)runs * Gr) {
                     if (!k4) return SPV_OK;
@@ -347,7 +393,7 @@ spv_status plan_pt_split(Ctx *c, int n, int D, int K, int runs, int chains, int 
                                    Gr, bpc * c->num_cus);
                 }
                 sp->use = true;
-                sp->optional = single_fits && !forced && (!k4 || Gr == 1);
+                sp->optional = single.fits && !forced && (!k4 || Gr == 1);
                 sp->G = Gr;
                 sp->m = m;
                 sp->threads = threads;
@@ -371,7 +417,7 @@ spv_status pt_lds_footprint(Ctx *c, const Inst *P, int K, int runs, int chains, 
     const size_t lds = pt_lds_bytes(n, D, K, chains, row_len, nqa, nw_icm) + 256;
     PtSplit sp;
     spv_status st = plan_pt_split(c, n, D, K, runs, chains, row_len, nd, icm ? icm_lo : 0, icm ? icm_hi : 0,
-                                  lds <= c->lds_max, &sp);
+                                  {lds <= c->lds_max, threads, lds}, &sp);
     if (st) return st;
     if (one_workgroup && sp.optional) sp.use = false;
     *groups = (int64_t)runs * (sp.use ? sp.G : 1);
@@ -1050,7 +1096,7 @@ spv_status pt_inst(spv_ctx *ctx, const Inst *P, const spv_pt_params *prm, const 
     const size_t lds = pt_lds_bytes(n, D, K, chains, row_len, nqa, nw_icm) + 256;
     PtSplit sp;
     if ((st = plan_pt_split(c, n, D, K, runs, chains, row_len, nd, icm ? prm->icm_lo : 0, icm ? prm->icm_hi : 0,
-                            lds <= c->lds_max, &sp)))
+                            {lds <= c->lds_max, threads, lds}, &sp)))
         return st;
     if (one_workgroup && sp.optional) sp.use = false;
     if (!sp.use && lds > c->lds_max)

@@ -382,6 +382,7 @@ struct PtLaunch {
     const uint32_t *redo = nullptr;  // only runs r with a mark at redo[-1 - r] (null: all)
 };
 size_t pt_lds_bytes(int n, int D, int K, int chains, int row_len, int nqa, int nw_icm);
+hipError_t pt_max_runs_resident(int nd, int threads, size_t lds, int *runs_per_cu);
 hipError_t launch_pt(const PtLaunch &L, hipStream_t s);
 
 // Tempering with each run's ladder split into G groups of m slots, one
@@ -411,8 +412,14 @@ struct PtSplit {
     bool optional = false;  // the one-workgroup kernel serves as well: K off the multiples of four, or one group
     int G = 1, m = 0, threads = 256, nw_icm = 0;
 };
+// The one-workgroup kernel's launch of the same job: whether its LDS fits, and its shape.
+struct PtSingle {
+    bool fits;
+    int threads;
+    size_t lds;
+};
 spv_status plan_pt_split(Ctx *c, int n, int D, int K, int runs, int chains, int row_len, int nd, int icm_lo,
-                         int icm_hi, bool single_fits, PtSplit *sp);
+                         int icm_hi, const PtSingle &single, PtSplit *sp);
 unsigned pt_spin_limit();
 // LDS claimed by one spv_pt_sample launch with the shapes it would pick (with one_workgroup
 // as pt_inst takes it), and its workgroups.

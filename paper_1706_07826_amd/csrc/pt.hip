@@ -560,6 +560,12 @@ size_t pt_lds_bytes(int n, int D, int K, int chains, int row_len, int nqa, int n
     return pt_layout(n, D, K, chains, row_len, nqa, nw_icm, nullptr, nullptr);
 }
 
+hipError_t pt_max_runs_resident(int nd, int threads, size_t lds, int *runs_per_cu) {
+    void (*const f)(PtArgs) = nd == 1 ? pt_kernel<1> : nd == 2 ? pt_kernel<2> : nd == 3 ? pt_kernel<3> : nullptr;
+    if (!f) return hipErrorInvalidValue;
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(runs_per_cu, f, threads, lds);
+}
+
 hipError_t launch_pt(const PtLaunch &P, hipStream_t s) {
     PtArgs a;
     a.image = P.image;

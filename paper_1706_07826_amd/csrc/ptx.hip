@@ -105,9 +105,13 @@ struct PtxLds {
 // Pending-join buffer per wavefront (64 appended at most on top of < 64 pending).
 constexpr int kJoinBuf = 128;
 
-// Quad words a group of m slots holds per chain: with K a multiple of 4 its slots start
-// on a quad's boundary (or lie inside one quad), else at any byte.
-__host__ __device__ inline int ptx_chain_words(int K, int m) { return (m + (K % 4 == 0 ? 3 : 6)) / 4; }
+// Quad words a group of m slots holds per chain.  With K a multiple of 4 its slots start on a
+// quad's boundary (or lie inside one quad), with K and m even at byte 0 or 2 of a quad, else at
+// any byte; a group has no more slots than the ladder.
+__host__ __device__ inline int ptx_chain_words(int K, int m) {
+    const int last = K % 4 == 0 ? 3 : K % 2 == 0 && m % 2 == 0 ? 5 : 6;  // bytes before the slots, and 3
+    return ((m < K ? m : K) + last) / 4;
+}
 __host__ __device__ inline bool ptx_packed(bool big, int m, int chains) { return big && m == 1 && chains == 2; }
 
 __host__ __device__ inline size_t ptx_layout(int n, int D, int K, int m, int chains, int row_len, int nw_icm, bool big,
