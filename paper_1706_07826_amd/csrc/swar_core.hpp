@@ -213,14 +213,18 @@ __device__ __forceinline__ swar_u16x2 swar_mad8(uint32_t P, swar_u16x2 c) {
 
 // 4x = -4 s f for the four replicas of a word, as two pairs of int16 (replicas 0, 1 and 2, 3):
 // 4f = 4 cp + 8 P_b fits 16 bits (|f| <= x_bound <= 255), and the spin byte masks, widened to
-// 16 bits, negate it where the spin is +1.  `cp2` holds 4 cp in both halves.
+// 16 bits, negate it where the spin is +1.  `cp2` holds 4 cp in both halves.  MAD: 8 P + c as
+// one instruction; with records from global memory the two of the compiler are 1 to 2 % faster
+// (3375 sites, 1500 reads x 150 sweeps: 1.22 ms against 1.24).
+template <bool MAD = true>
 __device__ __forceinline__ void swar_x16(uint32_t P, uint32_t self, uint32_t cp2, swar_i16x2 *lo, swar_i16x2 *hi) {
     const uint32_t Plo = __builtin_amdgcn_perm(P, P, 0x0C010C00u);  // bytes P0, 0, P1, 0
     const uint32_t Phi = __builtin_amdgcn_perm(P, P, 0x0C030C02u);  // bytes P2, 0, P3, 0
     const uint32_t mlo = __builtin_amdgcn_perm(self, self, 0x01010000u);
     const uint32_t mhi = __builtin_amdgcn_perm(self, self, 0x03030202u);
     const swar_u16x2 c = __builtin_bit_cast(swar_u16x2, cp2);
-    const swar_u16x2 flo = swar_mad8(Plo, c), fhi = swar_mad8(Phi, c);
+    const swar_u16x2 flo = MAD ? swar_mad8(Plo, c) : __builtin_bit_cast(swar_u16x2, Plo) * (unsigned short)8 + c;
+    const swar_u16x2 fhi = MAD ? swar_mad8(Phi, c) : __builtin_bit_cast(swar_u16x2, Phi) * (unsigned short)8 + c;
     const swar_u16x2 ml = __builtin_bit_cast(swar_u16x2, mlo), mh = __builtin_bit_cast(swar_u16x2, mhi);
     *lo = __builtin_bit_cast(swar_i16x2, (swar_u16x2)((flo ^ ml) - ml));
     *hi = __builtin_bit_cast(swar_i16x2, (swar_u16x2)((fhi ^ mh) - mh));
@@ -408,7 +412,7 @@ __device__ void swar_run(const SwarLds &L, const SaItem &a, const int *cs, const
 #pragma unroll
                 for (int b = 0; b < W; ++b) {
                     swar_i16x2 xlo, xhi;  // 4x
-                    swar_x16(P[b], self[b], co.x, &xlo, &xhi);
+                    swar_x16<!BIG>(P[b], self[b], co.x, &xlo, &xhi);
                     // Random words are drawn for every replica; x <= 0 flips regardless of them.
                     const dev::Words4 r = dev::philox(co.y, t, (uint32_t)(q0 + qa + b), 2u << 24, a.k0, a.k1);
                     // byte offsets 4x into the row (x may be <= 0: the entry is read and ignored)
@@ -475,13 +479,13 @@ __device__ void swar_run(const SwarLds &L, const SaItem &a, const int *cs, const
 // lane (class size x qw <= threads; DK records a site).  A lane keeps its site of every
 // class in registers (neighbour addresses, couplings, constants), so LDS holds only the
 // acceptance rows and the spins, a word costs its six or so neighbour reads, four threshold
-// reads and 72 vector instructions, and a pass of a workgroup that has its SIMDs to itself
+// reads and 74 vector instructions, and a pass of a workgroup that has its SIMDs to itself
 // is a short chain of latencies: half of a word's random rounds run behind the neighbour
 // reads and half behind the threshold reads, and the next sweep's acceptance row is loaded
 // a sweep ahead.
 // Measured at Chimera 8 x 8, 10,000 reads x 2000 sweeps: 5.5 ms against 6.5 for the body
-// with records in LDS, the vector units busy 0.93 of the time at a clock the load brings
-// down to about 2 GHz.  Two quads per lane (8-byte accesses, half the barriers) was
+// with records in LDS, the vector units busy 0.92 of the time at a clock the load brings
+// down from 2.4 to about 2.15 GHz.  Two quads per lane (8-byte accesses, half the barriers) was
 // slower there, 5.8 ms: its registers leave five waves per SIMD instead of eight.
 template <int DK, int NC>
 struct SwarHeld {
