@@ -674,6 +674,10 @@ spv_status sample_inst(spv_ctx *ctx, const Inst *P, const double *betas, int32_t
     // Quads per workgroup: whole waves for small classes; two when the quads outnumber the
     // CUs and the workgroup stays within 512 threads (N = 216, 10,000 reads: 1.66 ms, one
     // quad 1.84; N = 512: 2.8 either way, four 3.5).
+    // Left to the bodies above: four classes of 513 to 768 variables too many for the LDS beside
+    // their records, when the device is full.  A CU's registers hold one such workgroup of 9 to 12
+    // waves in place of 16 (N = 2400 / 2800, 12,000 reads x 60 sweeps: 1.71 / 1.75 ms against 1.53
+    // / 1.62; 3000 reads 0.47 / 0.48 against 0.69 / 0.70).
     const int held_qw = sa_held_env();
     const bool shape_forced = sa_qw_env() > 0 || sa_threads_env() > 0 || sa_wpl_env() > 0 || sa_big_env();
     if (held_qw != 0 && !shape_forced && swar && P->n_colours >= 2 && P->n_colours <= 4 &&
@@ -686,7 +690,9 @@ spv_status sample_inst(spv_ctx *ctx, const Inst *P, const double *betas, int32_t
         if (counted != n) cmax = n;  // not counted
         int q = held_qw > 0 ? held_qw : std::max(1, 64 / cmax);
         if (held_qw < 0 && q == 1 && (reads + 3) / 4 > c->num_cus && 2 * cmax <= 512) q = 2;
-        if (cmax * q <= 1024 && sa_held_lds_bytes(n, q) + 256 <= c->lds_max) {
+        const bool idle = big && held_qw < 0 && P->n_colours > 2 && cmax > 512 && cmax <= 768 &&
+                          (reads + 3) / 4 >= 5 * c->num_cus;
+        if (!idle && cmax * q <= 1024 && sa_held_lds_bytes(n, q) + 256 <= c->lds_max) {
             L.held = true;
             L.qw = qw = q;
             L.wpl = 1;

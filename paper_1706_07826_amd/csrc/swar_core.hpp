@@ -214,8 +214,9 @@ __device__ __forceinline__ swar_u16x2 swar_mad8(uint32_t P, swar_u16x2 c) {
 // 4x = -4 s f for the four replicas of a word, as two pairs of int16 (replicas 0, 1 and 2, 3):
 // 4f = 4 cp + 8 P_b fits 16 bits (|f| <= x_bound <= 255), and the spin byte masks, widened to
 // 16 bits, negate it where the spin is +1.  `cp2` holds 4 cp in both halves.  MAD: 8 P + c as
-// one instruction; with records from global memory the two of the compiler are 1 to 2 % faster
-// (3375 sites, 1500 reads x 150 sweeps: 1.22 ms against 1.24).
+// one instruction; with records from global memory and one word a lane the two of the compiler
+// are 1 to 2 % faster (3375 sites, 300 reads x 150 sweeps: 1.215 ms against 1.240; two words a
+// lane 3 % slower, 2400 sites, 12,000 reads x 60 sweeps: 1.58 against 1.53).
 template <bool MAD = true>
 __device__ __forceinline__ void swar_x16(uint32_t P, uint32_t self, uint32_t cp2, swar_i16x2 *lo, swar_i16x2 *hi) {
     const uint32_t Plo = __builtin_amdgcn_perm(P, P, 0x0C010C00u);  // bytes P0, 0, P1, 0
@@ -412,7 +413,7 @@ __device__ void swar_run(const SwarLds &L, const SaItem &a, const int *cs, const
 #pragma unroll
                 for (int b = 0; b < W; ++b) {
                     swar_i16x2 xlo, xhi;  // 4x
-                    swar_x16<!BIG>(P[b], self[b], co.x, &xlo, &xhi);
+                    swar_x16<!BIG || W == 2>(P[b], self[b], co.x, &xlo, &xhi);
                     // Random words are drawn for every replica; x <= 0 flips regardless of them.
                     const dev::Words4 r = dev::philox(co.y, t, (uint32_t)(q0 + qa + b), 2u << 24, a.k0, a.k1);
                     // byte offsets 4x into the row (x may be <= 0: the entry is read and ignored)
