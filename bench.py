@@ -644,7 +644,8 @@ def serving_roofline_and_cpu(args, ctx, kinds):
     probe = measured_lds_peak(spv, ctx)
     roofline = {"bound": "alu", "achieved": round(achieved, 4), "peak": round(PEAK_VALU_TSLOTS, 3),
                 "unit": "Tslot/s", "frac": round(achieved / PEAK_VALU_TSLOTS, 5), "traffic": None,
-                "kernel": f"ptx_kernel<{digits}, true, {md}>", "kernel_ms": round(ms, 3),
+                # (digits, instance in global memory, records, one packed slot pair a workgroup)
+                "kernel": f"ptx_kernel<{digits}, true, {md}, 2>", "kernel_ms": round(ms, 3),
                 "slots_per_update": round(spu, 3),
                 "lds": lds_object(upd / (ms / 1e3), pt_lds_bytes_per_update(md, digits, False), probe,
                                   "LDS traffic of the Metropolis updates against the measured LDS peak"),

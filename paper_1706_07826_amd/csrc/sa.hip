@@ -816,9 +816,10 @@ hipError_t launch_energy(const int32_t *image, int n, int D, const int8_t *spins
     if (R <= 0) return hipSuccess;
     long long *e = reinterpret_cast<long long *>(E);
     const size_t lds = (size_t)n * 2 * kEnergyRows;
-    // Few rows of few sites: a row per workgroup has every gather in flight at once (n = 125,
-    // 137 rows: 36.8 against 37.1 us a call; n = 288, 1000 rows: 42.0 and 42.6; n = 512, 4000
-    // rows: 51.5 and 43.8).
+    // Few rows of few sites: a row per workgroup has every gather in flight at once and no
+    // barrier after staging (kernel trace, median us, row / four rows a workgroup: n = 64, 137
+    // rows 4.05 / 4.7; n = 125, 137 rows 4.2 / 4.7; n = 288, 1000 rows 6.0 / 6.3; n = 512, 300
+    // rows 5.8 / 6.3; n = 512, 1000 rows 7.0 / 6.6; a call at n = 512, 4000 rows 51.5 / 43.8).
     if (lds > kEnergyLds || (n <= 512 && R <= 1024))
         hipLaunchKernelGGL(energy_kernel, dim3(R), dim3(256), 0, s, image, n, D, spins, R, e);
     else
