@@ -295,6 +295,7 @@ spv_status plan_pt_split(Ctx *c, int n, int D, int K, int runs, int chains, int 
     const bool icm = icm_hi > icm_lo, forced = mode == 1 && k4;
     const int quads = (K + 3) / 4, maxg = icm ? K : quads;
     int G = env_int("SPVAR_PT_GROUPS", 0);
+    const bool shaped = G > 0 || env_int("SPVAR_PT_THREADS", 0) > 0;  // a shape asked for is kept
     const long long words = (long long)n * ((chains * K + 3) / 4);
     if (G <= 0) {
         G = std::max(1, std::min(maxg, c->num_cus / std::max(runs, 1)));
@@ -368,7 +369,7 @@ spv_status plan_pt_split(Ctx *c, int n, int D, int K, int runs, int chains, int 
                 // at once, and the one-workgroup kernel where its runs take fewer rounds of the
                 // device (tables and lists of this one take more LDS; 27 x 32 x 2, 300 runs: 2.08 ms
                 // in two rounds, 1.46 in one).
-                if (Gr == 1 && !forced) {
+                if (Gr == 1 && !forced && !shaped) {
                     for (int t = threads / 2; t >= std::max({256, nq, pairs}) && bpc * c->num_cus < runs; t /= 2) {
                         int b = 0;
                         if ((e = ptx_max_groups_resident(shape, t, lds, &b)) != hipSuccess)

@@ -10,7 +10,7 @@
 // When K is no multiple of 4 the quads of a chain start at another slot in every
 // (run, chain), so a group holds every quad its slots of a chain touch and owns
 // some of their bytes, at an offset of the chain's own (26 slots x 2 chains x 8 runs of
-// the L = 6 cube with cluster moves, 300 sweeps: 54.3 ms in one workgroup a run, 5.0 ms
+// the L = 6 cube with cluster moves, 300 sweeps: 54.3 ms in one workgroup a run, 5.2 ms
 // as 26 groups of one slot).
 // A group of one slot reading its instance from the global image keeps both
 // chains' bytes of that slot in one word per site (byte c: chain c), each byte
